@@ -64,9 +64,10 @@ typedef enum moa_dtype {
 
 /* How the contraction is carried out. Every path computes Eq. 3; they
  * differ in arithmetic:
- *  ONF          -- scalar fused multiply-add, k ascending for every element
- *                  (the paper's loop order); FP64 or FP32. Bitwise equal to
- *                  the same loop with one fma per step.
+ *  ONF          -- fused multiply-add, k ascending for every element (the
+ *                  paper's loop order); FP64 or FP32. Bitwise equal to the
+ *                  scalar loop with one fma per step (carried out by the FP64
+ *                  and FP32 matrix-core steps, which chain one fma per k).
  *  MFMA_F32     -- FP32 matrix-core tiles (v_mfma_f32_32x32x2_f32), FP32
  *                  accumulation. F32 only. Variants 0, 1 copy A's rows and
  *                  B's columns into 64-byte records (scratch of 4 (m + p) n
@@ -134,8 +135,8 @@ typedef enum moa_path {
  * Every path takes any combination; a column-major C is computed as
  * C^T = B^T A^T with a row-major result (no copies). The split-BF16, FP8 and
  * FP32 matrix-core ring paths condition a column-major operand with the other
- * packer; the ONF kernel reads it along its contiguous extent and transposes
- * it into its LDS slab, its k loop unchanged (bitwise the same result). The
+ * packer; the ONF kernel lays it down in LDS along its contiguous extent, its
+ * k loop unchanged (bitwise the same result). The
  * register-staged FP32 variant (MOA_FLAG_VARIANT(2)) takes row-major operands
  * only (MOA_ERR_UNSUPPORTED otherwise). Grouped launches run members with a
  * column-major operand singly; prepared groups refuse them. */
@@ -167,7 +168,7 @@ typedef struct moa_plan_info {
     int32_t tile_m, tile_n;   /* C block per workgroup (rows x cols) */
     int32_t tile_k;           /* k slab staged in LDS per step */
     int32_t wave_m, wave_n;   /* C block per wavefront */
-    int32_t lane_m, lane_n;   /* C block per lane (ONF) or 0 (matrix cores) */
+    int32_t lane_m, lane_n;   /* C elements per lane, rows x columns (ONF) or 0 */
     int32_t threads;          /* threads per workgroup */
     int32_t lds_bytes;        /* LDS per workgroup */
     int64_t workgroups;       /* grid size */

@@ -128,9 +128,12 @@ class TraceScope {
 // and returns the first HIP error.
 hipError_t launch_onf(const moa_gemm_desc &d, const Plan &plan, hipStream_t stream);
 int onf_variant_count(moa_dtype t);
-void onf_variant_shape(moa_dtype t, int v, Plan *p);
-int onf_ring_variant(moa_dtype t);           // the direct-load ring kernel (row-major operands)
-bool onf_ring_fits(moa_dtype t, int64_t n, int64_t p);
+// `staged`: the register-staged kernel of the block instead of the matrix-core one
+void onf_variant_shape(moa_dtype t, int v, bool staged, Plan *p);
+int onf_ring_variant(moa_dtype t);           // the 128 x 128 block with 32 x 128 waves (row-major operands)
+// Whether the matrix-core kernel's 32-bit offsets hold the operands of `d` (row-major result).
+bool onf_mm_fits(const moa_gemm_desc &d, int variant);
+int onf_default_variant(const moa_gemm_desc &d, bool ring_ok);
 
 // FP32 matrix cores: variants 0, 1 run the record ring (workspace for the
 // records), mfma_f32_staged_variant() the register-staged kernel (none).

@@ -1,24 +1,27 @@
-// Plain ONF kernel: Eq. 3 with one fused multiply-add per (i, j, k), k in
+// Plain ONF kernels: Eq. 3 with one fused multiply-add per (i, j, k), k in
 // ascending order for every element of C.
 //
 // The paper's generic program walks row i of C and, for each k, adds the
 // scalar A[i,k] times the contiguous row k of B (Fig. 1, section "From Normal
 // Form to C Program"). Its dimension lifting (section "Dimension Lifting to
 // Machine Coordinates") splits i over processors and j over register groups,
-// and the k (sigma) loop into blocks. On gfx950 the same splits become:
+// and the k (sigma) loop into blocks. Two kernels carry out the splits, with
+// the same bits:
+//  * onf_mm_kernel (below, the one that runs): the matrix-core steps whose
+//    element results are fma chains over ascending k;
+//  * onf_kernel: scalar fma, register-staged slabs and 64-bit addresses, for
+//    products whose rows exceed the matrix-core kernel's 32-bit offsets:
 //   i -> (workgroup row block of TM rows, lane row group; R rows per lane,
 //         strided by the TR row groups of the workgroup)
 //   j -> (workgroup column block of TN columns, lane column group; VJ columns
 //         per lane in VJ/VW runs of VW contiguous elements = one 16-byte
 //         vector each)
 //   k -> (LDS slab of BK, in-slab index)
-// Rows of A and B enter LDS as contiguous 16-byte vectors (coalesced row
-// reads, the contiguous access Eq. 3 prescribes), double-buffered through
-// registers. A column-major operand (the paper's gamma_col layout) is read
-// along its contiguous extent and transposed on the way into the same
-// row-major LDS slab, so the k loop below is the same for every layout. Each lane keeps its R x VJ block of C in registers for the whole
-// k loop, so the k-sum of every element is the plain ascending sequence of
-// fma(A[i,k], B[k,j], acc) -- bitwise the paper's loop with fma.
+//    Rows of A and B enter LDS as contiguous 16-byte vectors, double-buffered
+//    through registers; a column-major operand (the paper's gamma_col layout)
+//    is read along its contiguous extent and transposed on the way into the
+//    same row-major slab. Each lane keeps its R x VJ block of C in registers
+//    for the whole k loop.
 #include "moa_internal.h"
 #include "ring_gemm.h"
 
@@ -295,245 +298,331 @@ __global__ __launch_bounds__(256) void onf_kernel(const T *__restrict__ A,
     }
 }
 
-// ONF on a direct-load LDS ring. A slab is one 64-byte row of A per row of
-// the block (BK = 8 doubles or 16 floats of k) and the matching BK rows of B;
-// the slabs go from memory straight into LDS (`buffer_load ... lds`), so no
-// registers hold them in flight and a lane can keep a large block of C:
-// 128 x 128 blocks, 8 x 8 per lane (8 + 8 elements of LDS per k for 64
-// FMAs: 2 bytes per FMA in FP64, which the LDS delivers at the FP64 FMA rate,
-// 1 byte in FP32; a 16 x 8 FP32 lane block would need more than 256
-// registers). Per slab:
-//   A: TM rows of 64 bytes, 16-byte chunk c of row r at physical chunk
-//      c ^ ((r / 4) mod 4) (conflict-free reads by rows of lanes);
-//   B: the slab's BK rows of TN elements, contiguous.
-// Lane (tr, tc) owns rows tr + TR q of the block and, for each 16-byte chunk
-// g of its columns, elements (g TC + tc) (16 / size) + u. Rows past m and
-// slab rows past n read as zeros (buffer ranges); columns past p are never
-// stored. The k loop is the same ascending fma sequence per element as the
-// register-staged kernel, and the last slab stops at n (no padded steps), so
-// results are bitwise the same.
-// Ring depth and workgroups per CU: FP32 three 16 KiB stages and three
-// workgroups per CU (the kernel fits 128 VGPRs), FP64 four stages and two
-// (its 64 FP64 accumulators per lane would spill at three).
-constexpr int ONF64_NST = 4, ONF32_NST = 3;
-template <typename T> constexpr int ring_occupancy() { return sizeof(T) == 4 ? 3 : 2; }
-
-// N elements of T as one vector register value
-template <typename T, int N> struct ExtVec { typedef T type __attribute__((ext_vector_type(N))); };
-
-template <typename T, int TM, int TN, int R, int VJ, int NST>
-__device__ __forceinline__ void onf_ring_block(const T *__restrict__ A, const T *__restrict__ B, T *__restrict__ C,
-                                               int64_t m, int64_t n, int64_t p, int accumulate, int vec_c,
-                                               uint8_t *lds) {
-    constexpr int ES = (int)sizeof(T), BK = 64 / ES, EPC = 16 / ES;   // k per slab, elements per 16-byte chunk
-    constexpr int TR = TM / R, TC = TN / VJ, GC = VJ / EPC;           // lane rows, lane columns, chunks per lane
-    constexpr int A_BYTES = TM * 64, B_BYTES = BK * TN * ES, STAGE = A_BYTES + B_BYTES;
-    constexpr int LPW = STAGE / 1024 / 4;                                // KiB loads per wave per slab
-    constexpr int RPL = 1024 / (TN * ES), CPR = TN * ES / 16;           // B rows per load, chunks per B row
-    static_assert(TR * TC == 256 && STAGE % 4096 == 0 && VJ % EPC == 0 && RPL >= 1, "shape of the ONF ring");
-    static_assert(NST >= 3 && NST <= 4, "waits cover up to two later slabs");
-    const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int tr = t / TC, tc = t % TC;
-    const int64_t i0 = (int64_t)blockIdx.y * TM, j0 = (int64_t)blockIdx.x * TN;
-    auto col = [&](int v) { return (v / EPC * TC + tc) * EPC + v % EPC; };   // lane column v in the block
-
-    // the accumulate form starts from C
-    T acc[R][VJ];
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-#pragma unroll
-        for (int v = 0; v < VJ; ++v) acc[q][v] = T(0);
-    if (accumulate) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const int64_t i = i0 + tr + TR * q;
-            if (i >= m) continue;
-#pragma unroll
-            for (int v = 0; v < VJ; ++v) {
-                const int64_t j = j0 + col(v);
-                if (j < p) acc[q][v] = C[i * p + j];
-            }
-        }
+// ONF on the matrix cores. One step of v_mfma_f64_16x16x4 (or
+// v_mfma_f32_16x16x4) adds to every element of a 16 x 16 block of C four
+// fused multiply-adds, one after another with k ascending and one rounding
+// each: D = fma(a3, b3, fma(a2, b2, fma(a1, b1, fma(a0, b0, C)))), subnormals,
+// signed zeros and infinities included (compared bit for bit with
+// __builtin_fma chains over such values). Issued slab by slab with k
+// ascending they are Eq. 3's loop itself, so the results are bitwise those of
+// the scalar loop, at the matrix-core rate: 256 lanes' worth of fma per
+// instruction instead of 64, so the vector ALU's operand traffic (8 + 8 LDS
+// elements per lane for 64 fma) is gone and what bounds the kernel is the
+// matrix rate itself (78.6 TF in FP64, 157.3 in FP32). Measured, vector kernel
+// of the same blocks and direct-to-LDS ring before: 8192^3 FP32 12.2 -> 7.7 ms
+// (90 -> 143 TF), FP64 22.7 -> 16.7 ms (48 -> 66 TF), 1999 x 1531 x 2113 FP64
+// 461 -> 244 us, 256^3 FP64 18.7 -> 6.7 us per call.
+//
+// A workgroup of four waves owns a TM x TN block of C, a wave WM x WN of it as
+// 16 x 16 blocks. k is walked in stages of SUB sub-slabs of 64 bytes of k per
+// row (8 doubles, 16 floats), which go from memory straight into an LDS ring of
+// NST stages (`buffer_load ... lds`, 1 KiB per load). An operand is laid down
+// by its contiguous extent, so every layout runs the same loop:
+//   k-contiguous (row-major A, column-major B): one 64-byte row per row of the
+//     block, 16-byte chunk c of row r at chunk c ^ ((r / 4) mod 4);
+//   k-strided (row-major B, column-major A): BK rows of the block's extent,
+//     row k turned by 64 bytes (FP32) or 128 bytes (FP64) times k mod 4.
+// Both make the 64 lanes of a fragment read (16 rows x 4 k) cover the 64 banks
+// evenly. Rows past the operand's end read as zeros (buffer ranges); what lies
+// past m or p feeds only elements that are never stored. In the last, partial
+// stage k >= n enters as (-0) * (+0): a step that adds -0, which changes no
+// value, not even a -0 sum.
+template <typename T> struct Mm;
+template <> struct Mm<double> {
+    typedef double acc_t __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc_t mfma(double a, double b, acc_t c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
+    // C row of register r (its column is lane mod 16)
+    static __device__ __forceinline__ int row(int r, int lane) { return 4 * r + (lane >> 4); }
+};
+template <> struct Mm<float> {
+    typedef float acc_t __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc_t mfma(float a, float b, acc_t c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
+};
 
-    const int64_t rows_live = m - i0 < TM ? m - i0 : TM;
-    const int64_t a_range = rows_live * n * ES;
-    const int64_t b_total = n * p - j0;        // elements from B + j0 to the end of B
-    const int64_t S = (n + BK - 1) / BK;
+// One operand's share of a sub-slab: W rows (or columns) of the block, KC
+// whether k is its contiguous extent.
+template <typename T, int W, bool KC> struct MmOperand {
+    static constexpr int ES = (int)sizeof(T), BK = 64 / ES, EPC = 16 / ES;
+    static constexpr int BYTES = W * 64;                     // W rows of 64 bytes, or BK rows of W elements
+    static constexpr int LOADS = BYTES / 1024;
+    static constexpr int CPR = W * ES / 16;                  // 16-byte chunks of a k-strided row
+    static_assert(BYTES % 1024 == 0 && CPR <= 64, "whole loads of at most one row each");
 
-    // Both resources start at the slab (A: column k0 of the block's first
-    // row, B: row k0) and end where the live data ends, so each lane's vector
-    // offset is the same for every slab: computed once, in registers no later
-    // instruction overwrites.
-    int voff[LPW];
-#pragma unroll
-    for (int q = 0; q < LPW; ++q) {
-        const int g = wave * LPW + q;                     // wave-uniform
-        if (g < A_BYTES / 1024) {
+    // Vector offset of lane `lane` in load g of a sub-slab; live: rows of the
+    // block inside the operand (KC), ld: the operand's leading extent.
+    static __device__ __forceinline__ int voffset(int g, int lane, int64_t live, int64_t ld) {
+        if constexpr (KC) {
             const int r = 16 * g + (lane >> 2);
             const int c = (lane & 3) ^ ((lane >> 4) & 3);
-            voff[q] = r < rows_live ? (int)(((int64_t)r * n + EPC * c) * ES) : ring::kDeadVoffset;
+            return r < live ? (int)((r * ld + EPC * c) * ES) : ring::kDeadVoffset;
         } else {
-            const int row = (g - A_BYTES / 1024) * RPL + lane / CPR;
-            voff[q] = (int)(((int64_t)row * p + EPC * (lane % CPR)) * ES);
+            const int k = g * (64 / CPR) + lane / CPR;
+            const int c = (lane % CPR + CPR - (ES * (k & 3)) % CPR) % CPR;
+            return (int)((k * ld + EPC * c) * ES);
         }
     }
-    auto issue_to = [&](uint8_t *buf, int64_t s) {     // buf: stage s mod NST
-        const int64_t k0 = s * BK;
-        const int64_t a_left = a_range - k0 * ES, b_left = (b_total - k0 * p) * ES;
-        const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(A + i0 * n + k0), (short)0, (int)(a_left > 0 ? a_left : 0), 0x00020000);
-        const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(B + j0 + k0 * p), (short)0, (int)(b_left < 0x7FFFFFFF ? b_left : 0x7FFFFFFF), 0x00020000);
+    // Byte offset of (row r, k) in the sub-slab.
+    static __device__ __forceinline__ int at(int r, int k) {
+        if constexpr (KC)
+            return r * 64 + (((k / EPC) ^ ((r >> 2) & 3)) << 4) + (k % EPC) * ES;
+        else
+            return k * (W * ES) + (((r / EPC + ES * (k & 3)) % CPR) << 4) + (r % EPC) * ES;
+    }
+};
+
+template <typename T, int TM, int TN, int WM, int WN, int SUB, int NST> struct MmCfg {
+    static constexpr int ES = (int)sizeof(T), BK = 64 / ES;
+    static constexpr int SUB_BYTES = (TM + TN) * 64, STAGE = SUB * SUB_BYTES, LDS = NST * STAGE;
+    static constexpr int LPW = STAGE / 1024 / 4;             // loads per wave and stage
+    static_assert(STAGE % 4096 == 0 && (NST - 2) * LPW <= 63, "whole loads per wave, countable");
+    static_assert((TM / WM) * (TN / WN) == 4, "four waves");
+};
+
+template <typename T, int TM, int TN, int WM, int WN, int SUB, int NST, int GK, bool A_COL, bool B_COL>
+__device__ __forceinline__ void onf_mm_block(const T *__restrict__ A, const T *__restrict__ B, T *__restrict__ C,
+                                             int64_t m, int64_t n, int64_t p, int accumulate, int tiles_m, int tiles_n,
+                                             uint8_t *lds) {
+    using G = MmCfg<T, TM, TN, WM, WN, SUB, NST>;
+    using OA = MmOperand<T, TM, !A_COL>;
+    using OB = MmOperand<T, TN, B_COL>;
+    using M = Mm<T>;
+    constexpr int ES = G::ES, BK = G::BK, LPW = G::LPW, FM = WM / 16, FN = WN / 16, KS = BK / 4;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave / (TN / WN), wn = wave % (TN / WN);
+    int tm, tn;
+    ring::block_of(tiles_m, tiles_n, &tm, &tn);
+    const int64_t i0 = (int64_t)tm * TM, j0 = (int64_t)tn * TN;
+    const int lr = lane & 15, lk = lane >> 4;               // a fragment's row and k of this lane
+
+    // Load x = wave LPW + q of a stage brings KiB g of its sub-slab u. Its
+    // lanes' offsets are the same in every stage; the resource starts at the
+    // sub-slab and ends where the operand ends, and moves on by one stage per
+    // issue (64-bit scalars: base, bytes left, bytes per stage).
+    const int64_t lda = A_COL ? m : n, ldb = B_COL ? n : p;
+    const int64_t a_live = m - i0 < TM ? m - i0 : TM, b_live = p - j0 < TN ? p - j0 : TN;
+    const char *a_base = reinterpret_cast<const char *>(A + (A_COL ? i0 : i0 * n));
+    const char *b_base = reinterpret_cast<const char *>(B + (B_COL ? j0 * n : j0));
+    const int64_t a_end = (A_COL ? n * m - i0 : a_live * n) * ES;     // bytes from the base to the live end
+    const int64_t b_end = (B_COL ? b_live * n : n * p - j0) * ES;
+    const int64_t a_step = (A_COL ? m : 1) * BK * ES, b_step = (B_COL ? 1 : p) * BK * ES;   // bytes per sub-slab
+    constexpr int KIB = G::SUB_BYTES / 1024;
+    int voff[LPW];
+    const char *src[LPW];
+    int64_t left[LPW], step_bytes[LPW], k_of[LPW];
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+        const int x = wave * LPW + q, u = x / KIB, g = x % KIB;         // wave-uniform
+        const bool a = g < OA::LOADS;
+        voff[q] = a ? OA::voffset(g, lane, a_live, lda) : OB::voffset(g - OA::LOADS, lane, b_live, ldb);
+        const int64_t one = a ? a_step : b_step;
+        src[q] = (a ? a_base : b_base) + u * one;
+        left[q] = (a ? a_end : b_end) - u * one;
+        step_bytes[q] = SUB * one;
+        k_of[q] = n - u * BK;                                           // k left from this load's first
+    }
+    auto clip = [](int64_t x) {                                         // 0 .. 2^31 - 1, in 32-bit scalar steps
+        const int hi = (int)(x >> 32);
+        const uint32_t lo = min((uint32_t)x, 0x7FFFFFFFu);
+        return hi < 0 ? 0 : hi > 0 ? 0x7FFFFFFF : (int)lo;
+    };
+    // The next stage into buf. Past the end the ranges are empty: the loads
+    // touch no memory but keep the count of loads in flight.
+    auto issue_next = [&](uint8_t *buf) {
 #pragma unroll
         for (int q = 0; q < LPW; ++q) {
-            const int g = wave * LPW + q;
-            if (g < A_BYTES / 1024)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (ring::lds_void_t *)(buf + g * 1024), 16, voff[q], 0,
-                                                         0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    b_rsrc, (ring::lds_void_t *)(buf + A_BYTES + (g - A_BYTES / 1024) * 1024), 16, voff[q], 0, 0, 0);
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)src[q], (short)0, (int)(k_of[q] >> 32) < 0 || k_of[q] == 0 ? 0 : clip(left[q]), 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rsrc, (ring::lds_void_t *)(buf + (wave * LPW + q) * 1024), 16, voff[q], 0, 0, 0);
+            src[q] += step_bytes[q];
+            left[q] -= step_bytes[q];
+            k_of[q] -= SUB * BK;
         }
     };
 
-    // the 16-byte chunk of A row r holding k .. k + EPC - 1 (k a multiple of EPC)
-    using chunk_t = typename ExtVec<T, EPC>::type;
-    auto a_chunk = [&](const uint8_t *buf, int r, int k) {
-        return *reinterpret_cast<const chunk_t *>(buf + r * 64 + (((k / EPC) ^ ((r >> 2) & 3)) << 4));
-    };
-    // a lane's VJ elements of B row k
-    auto b_row = [&](const uint8_t *bs, int k, T (&b)[VJ]) {
+    typename M::acc_t acc[FM][FN];
 #pragma unroll
-        for (int g = 0; g < GC; ++g) {
-            const chunk_t v = *reinterpret_cast<const chunk_t *>(bs + k * TN * ES + (g * TC + tc) * 16);
+    for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int u = 0; u < EPC; ++u) b[g * EPC + u] = v[u];
+        for (int b = 0; b < FN; ++b) acc[a][b] = typename M::acc_t{};
+
+    // Fragments are read one unit (GK steps of 4 k) ahead of the matrix-core
+    // steps that use them, also across stages: the last unit of a stage is
+    // multiplied after the next stage's barrier, behind the reads of its first
+    // unit. Two register sets, unit un in set un mod 2. The first stage finds
+    // (-0) * (+0) in set 1, which changes no sum.
+    constexpr int UNITS = SUB * KS / GK;
+    static_assert(KS % GK == 0 && UNITS % 2 == 0, "whole units, an even number per stage");
+    T av[2][GK][FM], bv[2][GK][FN];
+#pragma unroll
+    for (int ks = 0; ks < GK; ++ks) {
+#pragma unroll
+        for (int a = 0; a < FM; ++a) av[1][ks][a] = -T(0);
+#pragma unroll
+        for (int b = 0; b < FN; ++b) bv[1][ks][b] = T(0);
+    }
+    // `live`: k of this stage that exist (TAIL: fewer than the stage holds)
+    auto read_unit = [&](const uint8_t *buf, int un, int64_t live, auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+        const int u = un * GK / KS;
+        const uint8_t *as = buf + u * G::SUB_BYTES, *bs = as + OA::BYTES;
+#pragma unroll
+        for (int ks = 0; ks < GK; ++ks) {
+            const int k = 4 * (un * GK % KS + ks) + lk;
+            const bool dead = TAIL && u * BK + k >= live;
+#pragma unroll
+            for (int a = 0; a < FM; ++a) {
+                const T x = *reinterpret_cast<const T *>(as + OA::at(wm * WM + a * 16 + lr, k));
+                av[un & 1][ks][a] = dead ? -T(0) : x;
+            }
+#pragma unroll
+            for (int b = 0; b < FN; ++b) {
+                const T x = *reinterpret_cast<const T *>(bs + OB::at(wn * WN + b * 16 + lr, k));
+                bv[un & 1][ks][b] = dead ? T(0) : x;
+            }
         }
     };
+    auto mma_set = [&](int set) {
+#pragma unroll
+        for (int ks = 0; ks < GK; ++ks)
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b) acc[a][b] = M::mfma(av[set][ks][a], bv[set][ks][b], acc[a][b]);
+    };
 
-    // one whole slab (BK k, ascending) from `buf`
-    auto compute_full = [&](const uint8_t *buf) {
-        const uint8_t *bs = buf + A_BYTES;
+    // The stage a step's loads fill and the stage it reads are disjoint LDS,
+    // passed as restrict pointers so that the fragment reads need not wait for
+    // those loads (the explicit wait orders each stage's own loads).
+    auto step = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ cur) {
+        issue_next(dma);
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += EPC) {
-            chunk_t av[R];
+        for (int un = 0; un < UNITS; ++un) {
+            read_unit(cur, un, 0, std::false_type{});
+            mma_set((un & 1) ^ 1);
+        }
+    };
+    constexpr int STEP_K = SUB * BK;
+    const int64_t S = (n + STEP_K - 1) / STEP_K, full = n / STEP_K;
+    if (S > 0)
+        for (int q = 0; q < NST - 1; ++q) issue_next(lds + q * G::STAGE);
+    // the accumulate form starts from C, read while the ring fills
+    if (accumulate) {
 #pragma unroll
-            for (int q = 0; q < R; ++q) av[q] = a_chunk(buf, tr + TR * q, kk);
+        for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                T b[VJ];
-                b_row(bs, kk + e, b);
+            for (int b = 0; b < FN; ++b) {
+                const int64_t j = j0 + wn * WN + b * 16 + lr;
 #pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const T a = av[q][e];
-#pragma unroll
-                    for (int v = 0; v < VJ; ++v) acc[q][v] = fma_t(a, b[v], acc[q][v]);
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t i = i0 + wm * WM + a * 16 + M::row(r, lane);
+                    if (i < m && j < p) acc[a][b][r] = C[i * p + j];
                 }
             }
-        }
-    };
-    // the last, partial slab: k values 0 .. kc - 1 only (no padded steps)
-    auto compute_tail = [&](const uint8_t *buf, int kc) {
-        const uint8_t *bs = buf + A_BYTES;
-        for (int kk = 0; kk < kc; ++kk) {
-            T a[R], b[VJ];
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const chunk_t c = a_chunk(buf, tr + TR * q, kk - kk % EPC);
-                a[q] = c[kk % EPC];
-            }
-            b_row(bs, kk, b);
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-#pragma unroll
-                for (int v = 0; v < VJ; ++v) acc[q][v] = fma_t(a[q], b[v], acc[q][v]);
-        }
-    };
-
-    // One step: the stage the step's loads fill (slab s + NST - 1) and the
-    // stage it computes (slab s) are disjoint LDS, passed as restrict
-    // pointers so that the compiler sees the reads need not wait for those
-    // loads, which are meant to stay in flight (the explicit wait before the
-    // barrier orders slab s's own loads).
-    auto step = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ cur, int64_t s) {
-        if (s + NST - 1 < S) issue_to(dma, s + NST - 1);
-        compute_full(cur);
-    };
-    // Per slab: slab s has landed in every wave and every wave is done with
-    // slab s - 1, whose stage slab s + NST - 1 then takes.
-    const int64_t full = n / BK;
-    for (int q = 0; q < NST - 1; ++q)
-        if (q < S) issue_to(lds + q * STAGE, q);
-    for (int64_t s = 0; s < full; ++s) {
-        // slab s landed; at most NST - 2 later slabs of this wave in flight
-        const int64_t ahead = S - 1 - s < NST - 2 ? S - 1 - s : NST - 2;
-        if (ahead >= 2) __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(2 * LPW));
-        else if (ahead == 1) __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(LPW));
-        else __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0));
-        ring::ring_barrier();
-        step(lds + ((s + NST - 1) % NST) * STAGE, lds + (s % NST) * STAGE, s);
-    }
-    if (full < S) {
         __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0));
-        ring::ring_barrier();
-        compute_tail(lds + (full % NST) * STAGE, (int)(n - full * BK));
     }
-
+    int rd = 0, wr = NST - 1;                               // ring slots of stages s and s + NST - 1
+    for (int64_t s = 0; s < full; ++s) {
+        // stage s landed in every wave; every wave has read stage s - 1 (its
+        // last unit's reads too: lgkmcnt(0))
+        __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm((NST - 2) * LPW) & ~(0xF << 8));
+        ring::ring_barrier();
+        step(lds + wr * G::STAGE, lds + rd * G::STAGE);
+        rd = rd + 1 == NST ? 0 : rd + 1;
+        wr = wr + 1 == NST ? 0 : wr + 1;
+    }
+    mma_set(1);
+    // also the last loads' wait: none may land in LDS after the workgroup ends
+    __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0));
+    if (full < S) {
+        ring::ring_barrier();
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int64_t i = i0 + tr + TR * q;
-        if (i >= m) continue;
-#pragma unroll
-        for (int g = 0; g < GC; ++g) {
-            const int64_t j = j0 + (g * TC + tc) * EPC;
-            if (vec_c && j + EPC <= p) {
-                chunk_t v;
-#pragma unroll
-                for (int u = 0; u < EPC; ++u) v[u] = acc[q][g * EPC + u];
-                *reinterpret_cast<chunk_t *>(C + i * p + j) = v;
-            } else {
-#pragma unroll
-                for (int u = 0; u < EPC; ++u)
-                    if (j + u < p) C[i * p + j + u] = acc[q][g * EPC + u];
-            }
+        for (int un = 0; un < UNITS; ++un) {
+            if (un * GK * 4 >= n - full * STEP_K) break;
+            read_unit(lds + rd * G::STAGE, un, n - full * STEP_K, std::true_type{});
+            mma_set(un & 1);
         }
     }
+
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = i0 + wm * WM + a * 16 + M::row(r, lane);
+            if (i >= m) continue;
+#pragma unroll
+            for (int b = 0; b < FN; ++b) {
+                const int64_t j = j0 + wn * WN + b * 16 + lr;
+                if (j < p) C[i * p + j] = acc[a][b][r];
+            }
+        }
 }
 
-template <typename T, int TM, int TN, int R, int VJ, int NST>
-__global__ __launch_bounds__(256, ring_occupancy<T>()) void onf_ring_kernel(const T *__restrict__ A, const T *__restrict__ B,
-                                                         T *__restrict__ C, int64_t m, int64_t n, int64_t p,
-                                                         int accumulate, int vec_c) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[NST * (TM * 64 + 64 / sizeof(T) * TN * sizeof(T))];
-    onf_ring_block<T, TM, TN, R, VJ, NST>(A, B, C, m, n, p, accumulate, vec_c, lds);
+// Workgroups per CU: two, which keep the matrix cores fed through each other's
+// barriers (the 128 x 128 FP64 block holds 128 accumulator registers).
+template <typename T, int TM, int TN, int WM, int WN, int SUB, int NST, int GK, bool A_COL, bool B_COL>
+__global__ __launch_bounds__(256, 2) void onf_mm_kernel(const T *__restrict__ A, const T *__restrict__ B,
+                                                        T *__restrict__ C, int64_t m, int64_t n, int64_t p,
+                                                        int accumulate, int tiles_m, int tiles_n) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[MmCfg<T, TM, TN, WM, WN, SUB, NST>::LDS];
+    onf_mm_block<T, TM, TN, WM, WN, SUB, NST, GK, A_COL, B_COL>(A, B, C, m, n, p, accumulate, tiles_m, tiles_n, lds);
 }
 
-template <typename T, int TM, int TN, int R, int VJ, int NST>
-hipError_t launch_ring(const moa_gemm_desc &d, hipStream_t st) {
+template <typename T, int TM, int TN, int WM, int WN, int SUB, int NST, int GK, bool ANY_LAYOUT>
+hipError_t launch_mm(const moa_gemm_desc &d, hipStream_t st) {
     const T *A = static_cast<const T *>(d.A);
     const T *B = static_cast<const T *>(d.B);
     T *C = static_cast<T *>(d.C);
-    const int vec_c = (d.p % (16 / (int)sizeof(T)) == 0) && ((uintptr_t)C % 16 == 0);
-    dim3 grid((unsigned)((d.p + TN - 1) / TN), (unsigned)((d.m + TM - 1) / TM));
-    hipLaunchKernelGGL((onf_ring_kernel<T, TM, TN, R, VJ, NST>), grid, dim3(256), 0, st, A, B, C, d.m, d.n, d.p,
-                       d.accumulate, vec_c);
+    const int tiles_m = (int)((d.m + TM - 1) / TM), tiles_n = (int)((d.p + TN - 1) / TN);
+    const dim3 grid((unsigned)((int64_t)tiles_m * tiles_n)), bl(256);
+    const bool ac = ANY_LAYOUT && (d.flags & MOA_FLAG_A_COL), bc = ANY_LAYOUT && (d.flags & MOA_FLAG_B_COL);
+    if constexpr (ANY_LAYOUT) {
+        if (ac && bc)
+            hipLaunchKernelGGL((onf_mm_kernel<T, TM, TN, WM, WN, SUB, NST, GK, true, true>), grid, bl, 0, st, A, B, C, d.m,
+                               d.n, d.p, d.accumulate, tiles_m, tiles_n);
+        else if (ac)
+            hipLaunchKernelGGL((onf_mm_kernel<T, TM, TN, WM, WN, SUB, NST, GK, true, false>), grid, bl, 0, st, A, B, C,
+                               d.m, d.n, d.p, d.accumulate, tiles_m, tiles_n);
+        else if (bc)
+            hipLaunchKernelGGL((onf_mm_kernel<T, TM, TN, WM, WN, SUB, NST, GK, false, true>), grid, bl, 0, st, A, B, C,
+                               d.m, d.n, d.p, d.accumulate, tiles_m, tiles_n);
+    }
+    if (!ac && !bc)
+        hipLaunchKernelGGL((onf_mm_kernel<T, TM, TN, WM, WN, SUB, NST, GK, false, false>), grid, bl, 0, st, A, B, C, d.m,
+                           d.n, d.p, d.accumulate, tiles_m, tiles_n);
     return hipGetLastError();
 }
-
-struct OnfShape { int tm, tn, bk, r, vj; };
 
 // Instantiation tables. The first entry per type is the paper's static block
 // for the 32 KB vector L1 (three blocks of A, B and C): 1024 FP64 components
 // (32 x 32) and 2048 FP32 components (32 x 64). Larger entries trade LDS for
-// register blocking; the planner picks among them.
-// The last entry per type is the direct-load ring kernel above (row-major
-// operands).
-constexpr OnfShape kF64[] = {{32, 32, 16, 2, 2}, {64, 64, 16, 4, 4}, {64, 128, 16, 4, 8}, {128, 128, 16, 8, 8},
-                             {128, 128, 8, 8, 8}};
-constexpr OnfShape kF32[] = {{32, 64, 16, 2, 4}, {64, 64, 16, 4, 4}, {64, 128, 16, 4, 8}, {128, 128, 16, 8, 8},
-                             {128, 128, 16, 8, 8}};
+// register blocking; the planner picks among them. Per entry: the block, the
+// wave's part of it and the LDS ring (sub-slabs per stage, stages) of the
+// matrix-core kernel, then slab and lane block of the register-staged kernel
+// (0: none, the last entry per type, which takes row-major operands only).
+// The small blocks take deep stages: their products are short of workgroups,
+// so what counts is how much of k is on its way at once, whole 128-byte lines
+// per row and few barriers in the k walk (FP64 64 x 64, 1000^3: 37 us with four
+// sub-slabs per stage, 50 with one); three stages beat more (the rest of LDS
+// holds further workgroups: FP64 32 x 32, 1999 x 1531 x 2113: 244 us with
+// three, 284 with six).
+struct OnfShape { int tm, tn, wm, wn, sub, nst, bk, r, vj; };
+constexpr OnfShape kF64[] = {{32, 32, 16, 16, 4, 3, 16, 2, 2},
+                             {64, 64, 32, 32, 4, 3, 16, 4, 4},
+                             {64, 128, 32, 64, 2, 3, 16, 4, 8},
+                             {128, 128, 64, 64, 1, 3, 16, 8, 8},
+                             {128, 128, 32, 128, 1, 4, 0, 8, 8}};
+constexpr OnfShape kF32[] = {{32, 64, 16, 32, 2, 3, 16, 2, 4},
+                             {64, 64, 32, 32, 2, 3, 16, 4, 4},
+                             {64, 128, 32, 64, 1, 3, 16, 4, 8},
+                             {128, 128, 64, 64, 1, 3, 16, 8, 8},
+                             {128, 128, 32, 128, 1, 3, 0, 8, 8}};
 
 template <typename T, int TM, int TN, int BK, int R, int VJ>
 hipError_t launch_one(const moa_gemm_desc &d, hipStream_t st) {
@@ -559,47 +648,94 @@ int onf_variant_count(moa_dtype t) {
                         : (int)(sizeof(kF32) / sizeof(kF32[0]));
 }
 
-void onf_variant_shape(moa_dtype t, int v, Plan *p) {
+void onf_variant_shape(moa_dtype t, int v, bool staged, Plan *p) {
     const OnfShape s = (t == MOA_F64) ? kF64[v] : kF32[v];
     const int es = (t == MOA_F64) ? 8 : 4;
     p->variant = v;
     p->tile_m = s.tm;
     p->tile_n = s.tn;
-    p->tile_k = s.bk;
-    p->lane_m = s.r;
-    p->lane_n = s.vj;
-    p->wave_m = s.r * (64 / (s.tn / s.vj));
-    p->wave_n = s.tn;
     p->threads = 256;
-    p->lds_bytes = 2 * (s.tm * (s.bk + 16 / es) + s.bk * s.tn) * es;
-    if (v == onf_ring_variant(t)) p->lds_bytes = (t == MOA_F64 ? ONF64_NST : ONF32_NST) * (s.tm + s.tn) * s.bk * es;
+    if (staged) {
+        p->tile_k = s.bk;
+        p->lane_m = s.r;
+        p->lane_n = s.vj;
+        p->wave_m = s.r * (64 / (s.tn / s.vj));
+        p->wave_n = s.tn;
+        p->lds_bytes = 2 * (s.tm * (s.bk + 16 / es) + s.bk * s.tn) * es;
+        return;
+    }
+    p->tile_k = s.sub * 64 / es;
+    p->wave_m = s.wm;
+    p->wave_n = s.wn;
+    p->lane_m = s.wm / 4;               // 4 rows of each 16 x 16 block
+    p->lane_n = s.wn / 16;              // 1 column
+    p->lds_bytes = s.nst * s.sub * (s.tm + s.tn) * 64;
 }
 
 int onf_ring_variant(moa_dtype t) { return onf_variant_count(t) - 1; }
 
-// The ring kernel's 32-bit buffer offsets: 130 rows of n elements of A,
-// BK + 1 rows of p elements of B (BK 8 in FP64, 16 in FP32).
-bool onf_ring_fits(moa_dtype t, int64_t n, int64_t p) {
-    return t == MOA_F64 ? 130 * n * 8 < 0x7FFFFFFF && 9 * p * 8 < 0x7FFFFFFF
-                        : 130 * n * 4 < 0x7FFFFFFF && 17 * p * 4 < 0x7FFFFFFF;
+// The planner's block: the one whose workgroups, dealt out over the CUs, leave
+// the busiest CU the least to do -- ceil(blocks / CUs) times the block's area,
+// weighted by the block's measured time per element of C (4096^3: FP64 2.28 ms
+// with 32 x 32 blocks, 2.12 with 64 x 64 and the larger ones; FP32 1.13 ms with
+// 32 x 64, 1.03 with 64 x 64, 1.02 with 64 x 128, 0.99 with 128 x 128). The
+// matrix cores are shared by a CU's workgroups, so a CU with two blocks takes
+// twice as long as its neighbours with one: 1999 x 1531 x 2113 in FP64 has 272
+// blocks of 128 x 128 and takes 403 us with them, 258 with 64 x 64 and 244 with
+// 32 x 32; 256^3 takes 41, 11 and 4.8 us. Ties go to the larger block. 128 x 128 blocks only where every CU gets
+// one; FP64 without the row-major variant stops at 64 x 128.
+int onf_default_variant(const moa_gemm_desc &d, bool ring_ok) {
+    constexpr double kWeight64[] = {1.07, 1.0, 1.0, 1.0, 1.0}, kWeight32[] = {1.13, 1.035, 1.03, 1.0, 1.0};
+    const bool f64 = d.dtype == MOA_F64;
+    const OnfShape *shapes = f64 ? kF64 : kF32;
+    const double *weight = f64 ? kWeight64 : kWeight32;
+    const int ring = onf_ring_variant((moa_dtype)d.dtype);
+    int best = 0;
+    double best_cost = 0;
+    for (int v = ring; v >= 0; --v) {
+        if (v == ring ? !ring_ok : v == ring - 1 && (f64 || ring_ok)) continue;
+        const OnfShape s = shapes[v];
+        const int64_t blocks = ((d.m + s.tm - 1) / s.tm) * ((d.p + s.tn - 1) / s.tn);
+        if (s.tm * s.tn == 128 * 128 && blocks < kNumCUs) continue;
+        const double cost = (double)((blocks + kNumCUs - 1) / kNumCUs) * s.tm * s.tn * weight[v];
+        if (best_cost == 0 || cost < best_cost) {
+            best = v;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// The matrix-core kernel's 32-bit buffer offsets: a k-contiguous operand spans
+// the block's rows of n elements, a k-strided one the k of a sub-slab times its
+// leading extent. Products beyond that run the register-staged kernel of the
+// same block (64-bit addresses); the last entry has none and is refused there.
+bool onf_mm_fits(const moa_gemm_desc &d, int v) {
+    const OnfShape s = d.dtype == MOA_F64 ? kF64[v] : kF32[v];
+    const int64_t es = d.dtype == MOA_F64 ? 8 : 4, bk = 64 / es, lim = 0x7FFFFFFF;
+    if (d.m > lim || d.n > lim || d.p > lim) return false;
+    const int64_t a = (d.flags & MOA_FLAG_A_COL) ? (bk + 1) * d.m : (int64_t)(s.tm + 2) * d.n;
+    const int64_t b = (d.flags & MOA_FLAG_B_COL) ? (int64_t)(s.tn + 2) * d.n : (bk + 1) * d.p;
+    return a * es < lim && b * es < lim;
 }
 
 hipError_t launch_onf(const moa_gemm_desc &d, const Plan &plan, hipStream_t st) {
+    const bool mm = onf_mm_fits(d, plan.variant);
     if (d.dtype == MOA_F64) {
         switch (plan.variant) {
-        case 0: return launch_one<double, 32, 32, 16, 2, 2>(d, st);
-        case 1: return launch_one<double, 64, 64, 16, 4, 4>(d, st);
-        case 2: return launch_one<double, 64, 128, 16, 4, 8>(d, st);
-        case 3: return launch_one<double, 128, 128, 16, 8, 8>(d, st);
-        default: return launch_ring<double, 128, 128, 8, 8, ONF64_NST>(d, st);
+        case 0: return mm ? launch_mm<double, 32, 32, 16, 16, 4, 3, 2, true>(d, st) : launch_one<double, 32, 32, 16, 2, 2>(d, st);
+        case 1: return mm ? launch_mm<double, 64, 64, 32, 32, 4, 3, 1, true>(d, st) : launch_one<double, 64, 64, 16, 4, 4>(d, st);
+        case 2: return mm ? launch_mm<double, 64, 128, 32, 64, 2, 3, 1, true>(d, st) : launch_one<double, 64, 128, 16, 4, 8>(d, st);
+        case 3: return mm ? launch_mm<double, 128, 128, 64, 64, 1, 3, 1, true>(d, st) : launch_one<double, 128, 128, 16, 8, 8>(d, st);
+        default: return launch_mm<double, 128, 128, 32, 128, 1, 4, 1, false>(d, st);
         }
     }
     switch (plan.variant) {
-    case 0: return launch_one<float, 32, 64, 16, 2, 4>(d, st);
-    case 1: return launch_one<float, 64, 64, 16, 4, 4>(d, st);
-    case 2: return launch_one<float, 64, 128, 16, 4, 8>(d, st);
-    case 3: return launch_one<float, 128, 128, 16, 8, 8>(d, st);
-    default: return launch_ring<float, 128, 128, 8, 8, ONF32_NST>(d, st);
+    case 0: return mm ? launch_mm<float, 32, 64, 16, 32, 2, 3, 2, true>(d, st) : launch_one<float, 32, 64, 16, 2, 4>(d, st);
+    case 1: return mm ? launch_mm<float, 64, 64, 32, 32, 2, 3, 2, true>(d, st) : launch_one<float, 64, 64, 16, 4, 4>(d, st);
+    case 2: return mm ? launch_mm<float, 64, 128, 32, 64, 1, 3, 1, true>(d, st) : launch_one<float, 64, 128, 16, 4, 8>(d, st);
+    case 3: return mm ? launch_mm<float, 128, 128, 64, 64, 1, 3, 1, true>(d, st) : launch_one<float, 128, 128, 16, 8, 8>(d, st);
+    default: return launch_mm<float, 128, 128, 32, 128, 1, 3, 1, false>(d, st);
     }
 }
 

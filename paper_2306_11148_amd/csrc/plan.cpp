@@ -206,9 +206,9 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
     case MOA_PATH_ONF: {
         pl.kernel = d.dtype == MOA_F64 ? K_ONF_F64 : K_ONF_F32;
         const int nv = onf_variant_count((moa_dtype)d.dtype);
-        // the ring kernels read row-major operands with 32-bit offsets
+        // the last variant reads row-major operands with 32-bit offsets
         const int ring = onf_ring_variant((moa_dtype)d.dtype);
-        const bool ring_ok = !has_col_operand(d) && onf_ring_fits((moa_dtype)d.dtype, d.n, d.p);
+        const bool ring_ok = !has_col_operand(d) && onf_mm_fits(d, ring);
         int v = 0;
         if (forced >= 0) {
             if (forced >= nv) return fail(MOA_ERR_INVALID, "variant %d out of range (ONF has %d)", forced, nv);
@@ -218,25 +218,10 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
             v = forced;
         } else if ((v = tuned_variant(d, pl.path)) >= 0 && (v != ring || ring_ok)) {
             pl.tuned = true;
-        } else if (ring_ok && [&] {
-                       Plan r;
-                       onf_variant_shape((moa_dtype)d.dtype, ring, &r);
-                       return tiles_for(d.m, d.p, r.tile_m, r.tile_n) >= kNumCUs;
-                   }()) {
-            v = ring;
         } else {
-            v = 0;
-            // register-staged blocks: the largest that still gives every CU a
-            // block; FP64 stops at 64 x 128 (its 128 x 128 block needs more
-            // registers than two waves per SIMD allow and measured slower)
-            const int top = d.dtype == MOA_F64 ? 2 : ring - 1;
-            for (int c = top; c >= 0; --c) {
-                Plan t;
-                onf_variant_shape((moa_dtype)d.dtype, c, &t);
-                if (tiles_for(d.m, d.p, t.tile_m, t.tile_n) >= kNumCUs) { v = c; break; }
-            }
+            v = onf_default_variant(d, ring_ok);
         }
-        onf_variant_shape((moa_dtype)d.dtype, v, &pl);
+        onf_variant_shape((moa_dtype)d.dtype, v, !onf_mm_fits(d, v), &pl);
         if ((d.m + pl.tile_m - 1) / pl.tile_m > 65535)
             return fail(MOA_ERR_SHAPE, "m = %lld exceeds the ONF grid limit", (long long)d.m);
         break;
