@@ -364,9 +364,8 @@ def grouped_section(torch, moa, inputs, reps=10):
                                   "used": plan["variant"], "tuned": plan["tuned"],
                                   "autotune_best_ms": round(tuned_ms, 4),
                                   "ms_by_kernel": variant_ms,
-                                  "kernels": {0: "128x128 split once, 3/CU", 1: "128x128 split once, 2 plane sets, 2/CU",
-                                              2: "128x128 split in registers, 2/CU", 3: "64x128 split once, 4/CU",
-                                              4: "128x64 split once, 4/CU"}},
+                                  "kernels": {0: "128x128, five stages, 2/CU", 1: "64x64, 4/CU", 2: "128x128, three stages, 2/CU",
+                                              3: "64x128, 3/CU", 4: "128x64, 4/CU"}},
             "contraction_kernel_ms": round(t_k / n_k, 4) if n_k else None,
             "roofline": {"bound": "sum over products of max(matrix-core, HBM) time", "ideal_ms": round(roof_ms, 4),
                          "frac": round(roof_ms / best, 4)}}

@@ -75,7 +75,10 @@ typedef enum moa_dtype {
  *                  variant 2 stages through registers and takes no scratch.
  *  SPLIT_BF16   -- each FP32 input x is split into hi = RNE_bf16(x) and
  *                  lo = RNE_bf16(x - hi); C = hi.hi + hi.lo + lo.hi on BF16
- *                  matrix cores with FP32 accumulation. F32 only.
+ *                  matrix cores with FP32 accumulation. F32 only. Products of
+ *                  few blocks are split on the way through LDS instead of being
+ *                  conditioned first (same bits; moa_plan_query describes the
+ *                  conditioned form).
  *  FP8_SCALED   -- row i of A is scaled by 2^e_i and column j of B by 2^f_j
  *                  (e the largest integer with amax * 2^e <= 448), rounded
  *                  to OCP E4M3, multiplied on FP8 matrix cores with FP32
@@ -225,17 +228,17 @@ moa_status moa_gemm_grouped(const moa_gemm_desc *descs, int64_t count,
 /* The persistent split-BF16 kernel of a grouped launch (the dimension lift of
  * section "Dimension Lifting to Machine Coordinates" applied to a work list
  * of blocks from many products):
- *   0  128 x 128 blocks, each slab split once into one LDS plane set, three
- *      workgroups per CU;
- *   1  128 x 128, two plane sets and a deeper ring, two per CU;
- *   2  128 x 128, split in registers by every wave that reads a fragment,
- *      two per CU;
- *   3  64 x 128 blocks, split once, four per CU;
- *   4  128 x 64 blocks, split once, four per CU.
+ *   0  128 x 128 blocks, a ring of five slabs, two workgroups per CU;
+ *   1  64 x 64 blocks, four per CU;
+ *   2  128 x 128 blocks, a ring of three slabs, two per CU;
+ *   3  64 x 128 blocks, three per CU;
+ *   4  128 x 64 blocks, four per CU.
  * moa_gemm_grouped and moa_group_create use the autotuner's record for the
  * members' class if there is one, else the static rule: the block among 2, 3
  * and 4 with the fewest slab steps over the members, weighted by the
- * measured time of one slab step of that block. moa_gemm_grouped_variant runs
+ * measured time of one slab step of that block; where the longest k walk has
+ * 32 slabs or more, the block among 1 to 4 with the shortest estimated finish.
+ * moa_gemm_grouped_variant runs
  * moa_gemm_grouped with `variant` forced (-1: that choice); MOA_ERR_INVALID
  * for a variant outside -1 .. 4. */
 #define MOA_GROUPED_VARIANTS 5

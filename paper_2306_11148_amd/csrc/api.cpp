@@ -89,7 +89,7 @@ moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixe
         return fail(MOA_ERR_NOMEM, "the product needs %lld bytes of scratch, the fixed scratch array holds %lld",
                     (long long)pl.workspace_bytes, (long long)fixed_bytes);
     void *ws = fixed_ws;
-    const bool cached = !fixed_ws && pl.path != MOA_PATH_ONF;
+    const bool cached = !fixed_ws && pl.path != MOA_PATH_ONF && pl.raw_block < 0;
     if (cached && (s = scratch_alloc(&ws, pl.workspace_bytes, stream)) != MOA_OK) return s;
     hipError_t e = hipSuccess;
     switch (pl.path) {

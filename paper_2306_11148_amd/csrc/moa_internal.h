@@ -46,6 +46,7 @@ struct Plan {
     bool tuned = false;
     int split_k = 1;          // k chunks summed by separate workgroups (ring paths)
     int64_t partial_offset = 0;   // byte offset of the split-k partials in the workspace
+    int raw_block = -1;       // split-BF16 without conditioning: its block (-1: conditioned)
 };
 
 // A descriptor with a column-major C rewritten as the product C^T = B^T A^T
@@ -151,8 +152,8 @@ void split_bf16_shape(int variant, Plan *p);
 int split_bf16_variant_count();
 int split_bf16_default_variant(int64_t m, int64_t p);   // the planner's default block
 int64_t split_bf16_workspace_bytes(int64_t m, int64_t n, int64_t p);
-// Grouped split-BF16: all `members` in one conditioning pass and one
-// persistent launch. `host_staging` is pinned memory of at least
+int split_raw_block(const moa_gemm_desc &d);            // block without conditioning, -1: conditioned
+// Grouped split-BF16: all `members` in one persistent launch. `host_staging` is pinned memory of at least
 // split_grouped_desc_bytes(count) bytes that stays untouched until the
 // stream has passed this call.
 int64_t split_grouped_workspace_bytes(const moa_gemm_desc *const *members, int count);
@@ -164,9 +165,8 @@ int64_t split_grouped_desc_bytes(const moa_gemm_desc *const *members, int count)
 // space (null: the table goes up by a copy instead of being read in place).
 hipError_t launch_split_grouped(const moa_gemm_desc *const *members, int count, int variant, void *workspace,
                                 void *host_staging, const void *host_staging_dev, hipStream_t stream);
-// Persistent split-BF16 kernels of a grouped launch (blocks 128 x 128 split
-// once with three or two blocks per CU, 128 x 128 split in registers,
-// 64 x 128, 128 x 64), the static rule's choice among them, and the choice a
+// Persistent split-BF16 kernels of a grouped launch (blocks 128 x 128 with two
+// ring depths, 64 x 64, 64 x 128, 128 x 64), the static rule's choice, and the choice a
 // grouped launch makes: `forced` when >= 0, else the autotuner's record for
 // the members' class, else the static rule.
 int split_grouped_variant_count();

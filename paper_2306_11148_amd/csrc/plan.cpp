@@ -265,6 +265,10 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
         pl.workspace_bytes = split_bf16_workspace_bytes(d.m, d.n, d.p);
         pl.split_k = split_k_of(d, (d.n + 15) / 16);
         if (pl.split_k > 1) split_bf16_shape(0, &pl);   // split-k runs the first block variant
+        // Products of few blocks run without conditioning unless a flag or the
+        // autotuner names a record-ring block. The plan's other fields stay those
+        // of the conditioned form (fixed scratch refuses the same products).
+        else if (forced < 0 && !pl.tuned && split_k_requested(d) == 0) pl.raw_block = split_raw_block(d);
         // 256 record rows of (n/16) 64-byte records must stay below 2^31 bytes
         // (32-bit buffer offsets of one tile).
         if ((d.n + 15) / 16 > 131071)

@@ -17,11 +17,15 @@
 // 2. Contraction (matrix-core bound): the record-tile ring of ring_gemm.h
 //    (blocked form of Fig. 2) with three BF16 matrix-core steps per slab and
 //    block pair, FP32 accumulation.
+//
+// Products of few blocks and grouped products skip stage 1: raw_gemm.h streams
+// the FP32 operands and splits them on the way, with the same bits.
 #include <algorithm>
 #include <cstring>
 #include <vector>
 
 #include "moa_internal.h"
+#include "raw_gemm.h"
 #include "ring_gemm.h"
 #include "tile_common.h"
 
@@ -235,26 +239,9 @@ ring::Operands split_operands(const uint8_t *Ap, const uint8_t *Bp, float *C, in
 // Independent products share one launch. Members are listed longest k walk
 // first; their tiles form one work list (member g owns tile ids
 // [first[g], first[g+1])), and persistent workgroups claim tile ids from an
-// atomic counter until the list is exhausted.
-//
-// Grouped members skip the conditioning pass: a tile streams the FP32 slabs
-// of its rows of A and columns of B straight from memory into an LDS ring
-// (direct loads, as the record ring does with records) and splits them into
-// hi/lo BF16 with split_pair, as the conditioning kernels do -- either once
-// per element into LDS planes (conv_tile, the default kernels) or in
-// registers by every wave that reads a fragment (raw_tile). Every element of
-// every member receives exactly the operation sequence of the single-product
-// kernel -- the same hi/lo values, zero past n, the same matrix-core steps
-// slab by slab -- so grouped and single results are bitwise equal, whichever
-// kernel and block shape run.
-//
-// LDS stage of one slab (16 k) of raw_tile:
-//   A: BM rows of 64 bytes (16 FP32), 16-byte chunk c of row r at physical
-//      chunk c ^ ((r / 4) mod 4) (the record ring's swizzle);
-//   B: the slab's 16 rows of BN FP32, loaded in pairs (k, k + 8) per KiB: row
-//      k at bytes [0, 4 BN) of pair k mod 8, row k + 8 at [4 BN, 8 BN) rotated
-//      by 128 bytes, so that the two halves of a wave (k and k + 8 of the same
-//      columns) read disjoint banks.
+// atomic counter until the list is exhausted. Grouped members skip the
+// conditioning pass: every tile is a block of raw_gemm.h, so grouped and single
+// results are bitwise equal, whichever kernel and block shape run.
 struct GroupMember {
     const float *A, *B;
     float *C;
@@ -262,218 +249,6 @@ struct GroupMember {
     int64_t first_tile;                 // first contraction work-list id of this member
     int32_t tiles_n, accumulate;
 };
-
-template <int BM, int BN, int WM, int WN, int NST>
-struct RawCfg {
-    static constexpr int WAVES_N = BN / WN, NW = (BM / WM) * WAVES_N;
-    static constexpr int FM = WM / 32, FN = WN / 32;
-    static constexpr int A_BYTES = BM * 64, B_BYTES = SLAB * BN * 4;
-    static constexpr int STAGE = A_BYTES + B_BYTES;
-    static constexpr int LOADS = STAGE / 1024;            // KiB direct loads per slab
-    static constexpr int LPW = LOADS / NW;
-    static constexpr int LDS = NST * STAGE;
-    static_assert(NW == 4 && BN == 128 && BM % 16 == 0 && LOADS % NW == 0, "shape of the raw ring");
-};
-
-// 8 FP32 values -> hi and lo BF16 fragments
-__device__ __forceinline__ void split8(const float (&x)[8], bf16x8_t &hi, bf16x8_t &lo) {
-    uint4 h, l;
-    split_pair(x[0], x[1], &h.x, &l.x);
-    split_pair(x[2], x[3], &h.y, &l.y);
-    split_pair(x[4], x[5], &h.z, &l.z);
-    split_pair(x[6], x[7], &h.w, &l.w);
-    hi = __builtin_bit_cast(bf16x8_t, h);
-    lo = __builtin_bit_cast(bf16x8_t, l);
-}
-
-// A wave's FM x FN blocks of 32 x 32 accumulators to C (rows from i0,
-// columns from j0), skipping what lies past m or p. The accumulate form
-// (ACC) reads a block's 16 values of C before any store, so the loads are in
-// flight together; the overwrite form has no trace of it.
-template <bool ACC, int FM, int FN>
-__device__ __forceinline__ void store_blocks(const GroupMember &d, int64_t i0, int64_t j0,
-                                             const f32x16_t (&acc)[FM][FN]) {
-    const int lane = threadIdx.x & 63;
-    const int64_t p = d.p;
-    ring::global_f32 *C = (ring::global_f32 *)d.C;
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b) {
-            const int64_t j = j0 + b * 32 + (lane & 31);
-            if (j >= p) continue;
-            float old[16];
-            if constexpr (ACC) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t i = i0 + a * 32 + mfma32_row(r, lane);
-                    if (i < d.m) old[r] = C[i * p + j];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t i = i0 + a * 32 + mfma32_row(r, lane);
-                if (i < d.m) {
-                    float v = acc[a][b][r];
-                    if constexpr (ACC) v += old[r];
-                    C[i * p + j] = v;
-                }
-            }
-        }
-}
-
-template <int FM, int FN>
-__device__ __forceinline__ void store_block(const GroupMember &d, int64_t i0, int64_t j0,
-                                            const f32x16_t (&acc)[FM][FN]) {
-    if (d.accumulate)
-        store_blocks<true, FM, FN>(d, i0, j0, acc);
-    else
-        store_blocks<false, FM, FN>(d, i0, j0, acc);
-}
-
-template <int BM, int BN, int WM, int WN, int NST>
-__device__ __forceinline__ void raw_tile(const GroupMember &d, int64_t i0, int64_t j0, uint8_t *lds) {
-    using G = RawCfg<BM, BN, WM, WN, NST>;
-    constexpr int FM = G::FM, FN = G::FN, STAGE = G::STAGE, LPW = G::LPW;
-    const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave / G::WAVES_N, wn = wave % G::WAVES_N;
-    const int L = (int)d.S;
-    const int64_t n = d.n, p = d.p;
-
-    // Both resources start at the slab (A: column k0 of the tile's first row,
-    // B: row k0) and end where the live data ends, so each lane's vector
-    // offset is the same for every slab (computed once, in registers that no
-    // later instruction overwrites). Rows past m and k past the last live
-    // row's end are out of range (zeros); k past n inside earlier rows reads
-    // the next row and is masked when split.
-    const int64_t rows_live = d.m - i0 < BM ? d.m - i0 : BM;
-    const int64_t a_range = rows_live * n * 4;
-    const float *a_tile = d.A + i0 * n;
-    const float *b_tile = d.B + j0;
-    const int64_t b_total = n * p - j0;                  // elements from b_tile to the end of B
-    int voff[LPW];
-#pragma unroll
-    for (int q = 0; q < LPW; ++q) {
-        const int g = wave * LPW + q;                    // wave-uniform load index
-        if (g < BM / 16) {
-            const int r = 16 * g + (lane >> 2);
-            const int c = (lane & 3) ^ ((lane >> 4) & 3);
-            voff[q] = r < rows_live ? (int)(((int64_t)r * n + 4 * c) * 4) : ring::kDeadVoffset;
-        } else {
-            const int h = g - BM / 16;                   // pair h: rows h and h + 8 of the slab
-            const int upper = lane >> 5;
-            const int gc = upper ? ((lane & 31) + 8) & 31 : lane & 31;
-            voff[q] = (int)(((int64_t)(h + 8 * upper) * p + 4 * gc) * 4);
-        }
-    }
-
-    auto issue_to = [&](uint8_t *buf, int s) {         // buf: stage s mod NST
-        const int64_t k0 = (int64_t)s * SLAB;
-        const int64_t a_left = a_range - k0 * 4, b_left = (b_total - k0 * p) * 4;
-        const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(a_tile + k0), (short)0, (int)(a_left > 0 ? a_left : 0), 0x00020000);
-        const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(b_tile + k0 * p), (short)0,
-            (int)(b_left < 0x7FFFFFFF ? (b_left > 0 ? b_left : 0) : 0x7FFFFFFF), 0x00020000);
-#pragma unroll
-        for (int q = 0; q < LPW; ++q) {
-            const int g = wave * LPW + q;
-            if (g < BM / 16)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (ring::lds_void_t *)(buf + g * 1024), 16, voff[q],
-                                                         0, 0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc,
-                                                         (ring::lds_void_t *)(buf + G::A_BYTES + (g - BM / 16) * 1024),
-                                                         16, voff[q], 0, 0, 0);
-        }
-    };
-
-    const int frow = lane & 31, fhalf = lane >> 5;
-    float ra[FM][8], rb[FN][8];
-    // raw fragments of a slab (in buf): A rows (8 k of half fhalf), B columns (8 k rows)
-    auto read_raw_from = [&](const uint8_t *buf) {
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int r = wm * WM + a * 32 + frow;
-            const int sw = (r >> 2) & 3;
-            const float4 lo4 = *reinterpret_cast<const float4 *>(buf + r * 64 + (((2 * fhalf) ^ sw) << 4));
-            const float4 hi4 = *reinterpret_cast<const float4 *>(buf + r * 64 + (((2 * fhalf + 1) ^ sw) << 4));
-            ra[a][0] = lo4.x; ra[a][1] = lo4.y; ra[a][2] = lo4.z; ra[a][3] = lo4.w;
-            ra[a][4] = hi4.x; ra[a][5] = hi4.y; ra[a][6] = hi4.z; ra[a][7] = hi4.w;
-        }
-        const uint8_t *bb = buf + G::A_BYTES;
-#pragma unroll
-        for (int b = 0; b < FN; ++b) {
-            const int cb = wn * WN + b * 32 + frow;
-            const int off = fhalf ? 512 + ((((cb >> 2) + 24) & 31) << 4) + ((cb & 3) << 2) : cb << 2;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) rb[b][e] = *reinterpret_cast<const float *>(bb + e * 1024 + off);
-        }
-    };
-    SplitMode::Frags<FM, FN> f;
-    // split into fragments; k past n (the last slab) counts as zero
-    auto convert = [&](int s) {
-        const int64_t kb = (int64_t)s * SLAB + 8 * fhalf;
-        if (kb + 8 > n) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (kb + e >= n) {
-#pragma unroll
-                    for (int a = 0; a < FM; ++a) ra[a][e] = 0.0f;
-#pragma unroll
-                    for (int b = 0; b < FN; ++b) rb[b][e] = 0.0f;
-                }
-        }
-#pragma unroll
-        for (int a = 0; a < FM; ++a) split8(ra[a], f.ah[a], f.al[a]);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) split8(rb[b], f.bh[b], f.bl[b]);
-    };
-
-    f32x16_t acc[FM][FN];
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b) acc[a][b] = f32x16_t{};
-
-    auto wait_loads = [&](int stages) {
-        switch (stages <= 0 ? 0 : stages >= 2 ? 2 : stages) {
-        case 0: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(LPW)); break;
-        default: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(2 * LPW)); break;
-        }
-    };
-    static_assert(NST >= 3 && NST <= 4, "up to two slabs in flight");
-
-    // the loads of a step fill one stage while the fragments of the next
-    // slab are read from another: disjoint LDS, passed as restrict pointers
-    // so that the reads need not wait for those loads
-    auto step = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ src, int s) {
-        if (s + NST - 1 < L) issue_to(dma, s + NST - 1);
-        read_raw_from(src);
-    };
-    if (L > 0) {
-        for (int q = 0; q < NST - 1; ++q)
-            if (q < L) issue_to(lds + q * STAGE, q);
-        wait_loads(min(NST - 2, L - 1));
-        ring::ring_barrier();
-        read_raw_from(lds);
-        convert(0);
-        for (int s = 0; s < L; ++s) {
-            if (s + 1 < L) {
-                // slab s + 1 landed in every wave; the buffer of slab s - 1 is free
-                wait_loads(min(NST - 3, L - s - 2));
-                ring::ring_barrier();
-                step(lds + ((s + NST - 1) % NST) * STAGE, lds + ((s + 1) % NST) * STAGE, s);
-            }
-            SplitMode::mma<FM, FN>(f, acc);
-            if (s + 1 < L) convert(s + 1);
-        }
-    }
-    __syncthreads();                    // every wave done with the ring before the next tile's loads
-    store_block<FM, FN>(d, i0 + wm * WM, j0 + wn * WN, acc);
-}
 
 // Work-list claims, XCD by XCD. The tile list is cut into eight segments of
 // about equal work, one per XCD (workgroups go to the XCDs round-robin by id),
@@ -494,289 +269,33 @@ __device__ __forceinline__ int64_t claim_tile(unsigned long long *ctr, const int
 }
 
 template <int BM, int BN, int WM, int WN, int NST>
+__device__ __forceinline__ void grouped_tile(const GroupMember &d, int64_t local, uint8_t *lds) {
+    const int64_t tm = local / d.tiles_n, tn = local - tm * d.tiles_n;
+    const raw::Operands op{d.A, d.B, d.C, d.m, d.n, d.p, d.accumulate};
+    raw::block<BM, BN, WM, WN, NST, true, false>(op, __builtin_amdgcn_readfirstlane((int)tm) * (int64_t)BM,
+                                                 __builtin_amdgcn_readfirstlane((int)tn) * (int64_t)BN, lds);
+}
+
+template <int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(256, 2) void split_grouped_kernel(const GroupMember *__restrict__ g,
                                                                const int32_t *__restrict__ tile_owner,
                                                                const int64_t *__restrict__ bounds,
                                                                unsigned long long *__restrict__ counter) {
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[RawCfg<BM, BN, WM, WN, NST>::LDS];
-    __shared__ int64_t s_tile;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[raw::Cfg<BM, BN, WM, WN, NST>::LDS];
+    // the claimed tile id lives in the ring's last slot, whose first load is
+    // issued behind the tile's first barrier
+    int64_t *s_tile = reinterpret_cast<int64_t *>(lds + (NST - 1) * raw::Cfg<BM, BN, WM, WN, NST>::STAGE);
     int seg = 0;
     for (;;) {
-        __syncthreads();                // nobody still reads s_tile
-        if (threadIdx.x == 0) s_tile = claim_tile(counter, bounds, seg);
-        __syncthreads();
-        const int64_t tile = s_tile;
-        if (tile < 0) break;
-        const int k = __builtin_amdgcn_readfirstlane(tile_owner[tile]);
-        const GroupMember &d = g[k];
-        const int64_t local = tile - d.first_tile;
-        const int64_t tm = local / d.tiles_n, tn = local - tm * d.tiles_n;
-        raw_tile<BM, BN, WM, WN, NST>(d, __builtin_amdgcn_readfirstlane((int)tm) * (int64_t)BM,
-                                      __builtin_amdgcn_readfirstlane((int)tn) * (int64_t)BN, lds);
-    }
-}
-
-// Grouped block that splits every element of a slab once. The FP32 slab
-// lands in an LDS ring by direct loads as above (A swizzled; B as plain rows
-// of BN FP32); one pass of the whole workgroup turns it into hi and lo BF16
-// planes in a second, double-buffered LDS area; the four waves (2 x 2, each
-// BM/2 x BN/2) read their matrix-core fragments straight from the planes.
-// Per slab and wave this costs a quarter of the splits of the raw ring (no
-// element is split by two waves) and one barrier, which at once publishes
-// the planes just written, confirms the next raw slab landed in every wave
-// and frees the raw stage just split for the next load.
-//
-// Plane layout, per plane (A hi, A lo, B hi, B lo): [half h][row or column]
-// [8 BF16 of k in 8h .. 8h + 7], i.e. 16 bytes per row and half, so that a
-// fragment (32 rows, two halves) is two runs of 512 contiguous bytes.
-template <int BM, int BN, int NST, int NCV> struct ConvCfg {
-    static constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
-    static constexpr int RAW_A = BM * 64, RAW_B = SLAB * BN * 4, RAW = RAW_A + RAW_B;
-    static constexpr int PL_A = BM * 32, PL_B = BN * 32;       // bytes of one A or B plane
-    static constexpr int CONV = 2 * (PL_A + PL_B);
-    static constexpr int LOADS = RAW / 1024, LPW = LOADS / 4;  // KiB direct loads per slab, per wave
-    static constexpr int UNITS = 2 * (BM + BN);                // half rows of A, half columns of B
-    static constexpr int LDS = NST * RAW + NCV * CONV;
-    static_assert((BM == 64 || BM == 128) && (BN == 64 || BN == 128), "blocks of the split-once ring");
-    static_assert(LOADS % 4 == 0 && NST >= 2 && NST <= 4 && (NCV == 1 || NCV == 2), "shape of the split-once ring");
-};
-
-template <int BM, int BN, int NST, int NCV>
-__device__ __forceinline__ void conv_tile(const GroupMember &d, int64_t i0, int64_t j0, uint8_t *lds) {
-    using G = ConvCfg<BM, BN, NST, NCV>;
-    constexpr int FM = G::FM, FN = G::FN, LPW = G::LPW;
-    const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int L = (int)d.S;
-    const int64_t n = d.n, p = d.p;
-    uint8_t *const raw = lds;
-    uint8_t *const conv = lds + NST * G::RAW;
-
-    const int64_t rows_live = d.m - i0 < BM ? d.m - i0 : BM;
-    const int64_t a_range = rows_live * n * 4;
-    const float *a_tile = d.A + i0 * n;
-    const float *b_tile = d.B + j0;
-    const int64_t b_total = n * p - j0;                  // elements from b_tile to the end of B
-
-    // Slab s into raw stage s mod NST. Both resources start at the slab (A:
-    // column k0 of the tile's first row; B: row k0) and end where the live
-    // data ends, so the lanes' vector offsets stay the same for every slab --
-    // computed once here, in registers that no later instruction overwrites
-    // (a register the direct loads still read would make the compiler wait for
-    // every load in flight before reusing it). A: 16 rows of 64 bytes per
-    // load, rows past m dead, k past n in the last live row out of range
-    // (zeros), k past n inside earlier rows reads the next row (masked when
-    // split). B: 1024 / (4 BN) rows per load; rows past n (and columns past p
-    // on the last row) are out of range and load as zeros.
-    int voff[LPW];
-#pragma unroll
-    for (int q = 0; q < LPW; ++q) {
-        const int g = wave * LPW + q;
-        if (g < BM / 16) {
-            const int r = 16 * g + (lane >> 2);
-            const int c = (lane & 3) ^ ((lane >> 4) & 3);
-            voff[q] = r < rows_live ? (int)(((int64_t)r * n + 4 * c) * 4) : ring::kDeadVoffset;
-        } else {
-            constexpr int CPR = BN / 4;                     // 16-byte chunks per B row
-            const int row = (g - BM / 16) * (1024 / (4 * BN)) + lane / CPR;
-            voff[q] = (int)(((int64_t)row * p + 4 * (lane % CPR)) * 4);
-        }
-    }
-    auto issue_to = [&](uint8_t *buf, int s) {       // buf: raw stage s mod NST
-        const int64_t k0 = (int64_t)s * SLAB;
-        const int64_t a_left = a_range - k0 * 4, b_left = (b_total - k0 * p) * 4;
-        const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(a_tile + k0), (short)0, (int)(a_left > 0 ? a_left : 0), 0x00020000);
-        const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(b_tile + k0 * p), (short)0,
-            (int)(b_left < 0x7FFFFFFF ? (b_left > 0 ? b_left : 0) : 0x7FFFFFFF), 0x00020000);
-#pragma unroll
-        for (int q = 0; q < LPW; ++q) {
-            const int g = wave * LPW + q;
-            if (g < BM / 16)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (ring::lds_void_t *)(buf + g * 1024), 16, voff[q],
-                                                         0, 0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc,
-                                                         (ring::lds_void_t *)(buf + G::RAW_A + (g - BM / 16) * 1024),
-                                                         16, voff[q], 0, 0, 0);
-        }
-    };
-
-    // Split raw slab s (in buf) into the plane set cv; k past n counts as zero.
-    auto convert_from = [&](const uint8_t *buf, uint8_t *cv, int s) {
-        const int64_t k0 = (int64_t)s * SLAB;
-#pragma unroll
-        for (int i = 0; i < (G::UNITS + 255) / 256; ++i) {
-            const int ub = wave * 64 + 256 * i;     // first unit of this wave: units split per wave
-            if (ub >= G::UNITS) break;
-            const int u = ub + lane;
-            float x[8];
-            int h, dst;
-            const bool is_a = ub < 2 * BM;
-            if (is_a) {
-                h = ub / BM;
-                const int r = u - h * BM;
-                const int sw = (r >> 2) & 3;
-                const float4 v0 = *reinterpret_cast<const float4 *>(buf + r * 64 + (((2 * h) ^ sw) << 4));
-                const float4 v1 = *reinterpret_cast<const float4 *>(buf + r * 64 + (((2 * h + 1) ^ sw) << 4));
-                x[0] = v0.x; x[1] = v0.y; x[2] = v0.z; x[3] = v0.w;
-                x[4] = v1.x; x[5] = v1.y; x[6] = v1.z; x[7] = v1.w;
-                dst = h * BM * 16 + r * 16;
-            } else {
-                h = (ub - 2 * BM) / BN;
-                const int c = u - 2 * BM - h * BN;
-                const uint8_t *bb = buf + G::RAW_A + c * 4;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const float *>(bb + (8 * h + e) * BN * 4);
-                dst = 2 * G::PL_A + h * BN * 16 + c * 16;
-            }
-            if (k0 + SLAB > n) {
-                const int live = (int)(n - k0) - 8 * h;     // live k of this unit's 8 (can be <= 0)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (e >= live) x[e] = 0.0f;
-            }
-            bf16x8_t hi, lo;
-            split8(x, hi, lo);
-            const int plane = is_a ? G::PL_A : G::PL_B;
-            *reinterpret_cast<bf16x8_t *>(cv + dst) = hi;
-            *reinterpret_cast<bf16x8_t *>(cv + dst + plane) = lo;
-        }
-    };
-
-    const int frow = lane & 31, fhalf = lane >> 5;
-    SplitMode::Frags<FM, FN> f;
-    auto read_frags_from = [&](const uint8_t *cv) {
-#pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            const int off = fhalf * BM * 16 + (wm * G::WM + a * 32 + frow) * 16;
-            f.ah[a] = *reinterpret_cast<const bf16x8_t *>(cv + off);
-            f.al[a] = *reinterpret_cast<const bf16x8_t *>(cv + G::PL_A + off);
-        }
-#pragma unroll
-        for (int b = 0; b < FN; ++b) {
-            const int off = 2 * G::PL_A + fhalf * BN * 16 + (wn * G::WN + b * 32 + frow) * 16;
-            f.bh[b] = *reinterpret_cast<const bf16x8_t *>(cv + off);
-            f.bl[b] = *reinterpret_cast<const bf16x8_t *>(cv + G::PL_B + off);
-        }
-    };
-
-    f32x16_t acc[FM][FN];
-#pragma unroll
-    for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b) acc[a][b] = f32x16_t{};
-
-    auto wait_loads = [&](int slabs) {          // at most `slabs` later slabs of this wave in flight
-        switch (slabs <= 0 ? 0 : slabs >= 3 ? 3 : slabs) {
-        case 0: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(LPW)); break;
-        case 2: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(2 * LPW)); break;
-        default: __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(3 * LPW)); break;
-        }
-    };
-    static_assert(3 * LPW <= 63, "vmcnt counts up to 63 operations");
-    // Barrier that also publishes this wave's plane writes (LDS stores done).
-    auto plane_barrier = [] {
-        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0); vector-memory and export counts not waited on
-        ring::ring_barrier();
-    };
-
-    // One slab step. The stage the step's direct loads fill (dma: raw stage
-    // s mod NST, split by every wave before this step), the stage it splits
-    // (src: slab s + 1) and the plane sets are disjoint LDS, passed as
-    // restrict pointers: that lets the compiler see that reading src or the
-    // planes need not wait for the loads into dma, which are meant to stay in
-    // flight (the explicit waits above order each slab's loads before its
-    // split).
-    // The matrix-core steps of slab s are issued as soon as its fragments are
-    // in registers, before the split of slab s + 1, so that they run while
-    // this wave splits; the wave issues them at raised priority, so that the
-    // other workgroups' split work does not hold them back.
-    auto mma_step = [&] {
-        __builtin_amdgcn_s_setprio(1);
-        SplitMode::mma<FM, FN>(f, acc);
-        __builtin_amdgcn_s_setprio(0);
-    };
-    auto step1 = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ src, uint8_t *__restrict__ planes,
-                     int s) {
-        // one plane set: a second barrier between reading it and overwriting
-        // it with the next slab
-        if (s + NST < L) issue_to(dma, s + NST);
-        read_frags_from(planes);
-        mma_step();
-        if (s + 1 < L) {
-            wait_loads((NST - 1 < L - 2 - s) ? NST - 1 : L - 2 - s);
-            plane_barrier();
-            convert_from(src, planes, s + 1);
-        }
-    };
-    auto step2 = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ src,
-                     const uint8_t *__restrict__ planes_r, uint8_t *__restrict__ planes_w, int s) {
-        // two plane sets: one barrier makes the planes of s complete, raw
-        // slab s + 1 landed and the planes of s - 1 (the set this step
-        // writes) read by every wave
-        if (s + 1 < L) wait_loads((NST - 2 < L - 2 - s) ? NST - 2 : L - 2 - s);
-        plane_barrier();
-        if (s + NST < L) issue_to(dma, s + NST);
-        read_frags_from(planes_r);
-        mma_step();
-        if (s + 1 < L) convert_from(src, planes_w, s + 1);
-    };
-
-    // Ring fill and the split of slab 0 (stage 0), while the later stages'
-    // loads stay in flight (disjoint: restrict, as in the steps).
-    auto prologue = [&](uint8_t *__restrict__ st0, uint8_t *__restrict__ later, uint8_t *__restrict__ planes) {
-        issue_to(st0, 0);
-        for (int q = 1; q < NST; ++q)
-            if (q < L) issue_to(later + (q - 1) * G::RAW, q);
-        wait_loads((NST < L ? NST : L) - 1);
-        ring::ring_barrier();
-        convert_from(st0, planes, 0);
-    };
-
-    if (L > 0) {
-        prologue(raw, raw + G::RAW, conv);
-        for (int s = 0; s < L; ++s) {
-            uint8_t *dma = raw + (s % NST) * G::RAW;
-            const uint8_t *src = raw + ((s + 1) % NST) * G::RAW;
-            if (NCV == 2) {
-                step2(dma, src, conv + (s & 1) * G::CONV, conv + ((s + 1) & 1) * G::CONV, s);
-            } else {
-                plane_barrier();
-                step1(dma, src, conv, s);
-            }
-        }
-    }
-    __syncthreads();                    // every wave done with both LDS areas before the next tile
-    store_block<FM, FN>(d, i0 + wm * G::WM, j0 + wn * G::WN, acc);
-}
-
-template <int BM, int BN, int NST, int NCV, int OCC>
-__global__ __launch_bounds__(256, OCC) void split_grouped_conv_kernel(const GroupMember *__restrict__ g,
-                                                                    const int32_t *__restrict__ tile_owner,
-                                                                    const int64_t *__restrict__ bounds,
-                                                                    unsigned long long *__restrict__ counter) {
-    using G = ConvCfg<BM, BN, NST, NCV>;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
-    // the claimed tile id lives in the last plane set, which no wave writes
-    // before the first barrier of a tile
-    int64_t *s_tile = reinterpret_cast<int64_t *>(lds + NST * G::RAW + (NCV - 1) * G::CONV);
-    int seg = 0;
-    for (;;) {
-        __syncthreads();                // nobody still reads the tile id (or the planes)
+        __syncthreads();                // nobody still reads the ring
         if (threadIdx.x == 0) *s_tile = claim_tile(counter, bounds, seg);
         __syncthreads();
-        const int64_t tile = *s_tile;
+        const int64_t claimed = *s_tile;
+        const int64_t tile = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)claimed) |
+                                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(claimed >> 32)) << 32);
         if (tile < 0) break;
         const int k = __builtin_amdgcn_readfirstlane(tile_owner[tile]);
-        const GroupMember &d = g[k];
-        const int64_t local = tile - d.first_tile;
-        const int64_t tm = local / d.tiles_n, tn = local - tm * d.tiles_n;
-        conv_tile<BM, BN, NST, NCV>(d, __builtin_amdgcn_readfirstlane((int)tm) * (int64_t)BM,
-                               __builtin_amdgcn_readfirstlane((int)tn) * (int64_t)BN, lds);
+        grouped_tile<BM, BN, WM, WN, NST>(g[k], tile - g[k].first_tile, lds);
     }
 }
 
@@ -817,7 +336,58 @@ hipError_t launch_shape(const moa_gemm_desc &d, const uint8_t *Ap, const uint8_t
     return hipGetLastError();
 }
 
+// Blocks of the kernel without conditioning, and what one 16-k step of them
+// takes on a CU that holds b of them: fixed + b * each, in ns (fitted to
+// 512^3 .. 3072^3 and 1531 x 2029 x 1237; one to nine blocks per CU).
+struct RawBlock { int bm, bn; double fixed, each; };
+constexpr RawBlock kRaw[] = {{64, 64, 130, 150}, {64, 128, 130, 240}, {128, 64, 130, 240}, {128, 128, 100, 380}};
+
+template <int BM, int BN, int WM, int WN, int NST>
+hipError_t launch_raw(const moa_gemm_desc &d, hipStream_t st) {
+    const raw::Operands op{static_cast<const float *>(d.A), static_cast<const float *>(d.B), static_cast<float *>(d.C),
+                           d.m, d.n, d.p, d.accumulate};
+    const int tiles_m = (int)((d.m + BM - 1) / BM), tiles_n = (int)((d.p + BN - 1) / BN);
+    const dim3 grid((unsigned)(tiles_m * tiles_n)), bl(256);
+    const bool a_kc = !(d.flags & MOA_FLAG_A_COL), b_kc = (d.flags & MOA_FLAG_B_COL) != 0;
+    if (a_kc && b_kc)
+        hipLaunchKernelGGL((raw::single_kernel<BM, BN, WM, WN, NST, true, true>), grid, bl, 0, st, op, tiles_m, tiles_n);
+    else if (a_kc)
+        hipLaunchKernelGGL((raw::single_kernel<BM, BN, WM, WN, NST, true, false>), grid, bl, 0, st, op, tiles_m, tiles_n);
+    else if (b_kc)
+        hipLaunchKernelGGL((raw::single_kernel<BM, BN, WM, WN, NST, false, true>), grid, bl, 0, st, op, tiles_m, tiles_n);
+    else
+        hipLaunchKernelGGL((raw::single_kernel<BM, BN, WM, WN, NST, false, false>), grid, bl, 0, st, op, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+// The block a product takes without conditioning, -1 for the conditioned path:
+// the one whose busiest CU is done first, for products of at most three 128 x
+// 128 blocks per CU. Beyond that the record ring's larger blocks gain more than
+// the two conditioning launches cost (us, without / with conditioning: 192 x
+// 320 x 160 8 / 26, 512^3 11 / 29, 1024^3 21 / 46, 1531 x 2029 x 1237 48 / 84,
+// 2048^3 65 / 80, 3072^3 230 / 230, 4096^3 434 / 355). Operands whose offsets
+// inside a block exceed 32 bits stay on the conditioned path.
+int split_raw_block(const moa_gemm_desc &d) {
+    if (((d.m + 127) / 128) * ((d.p + 127) / 128) > 3 * kNumCUs) return -1;
+    int best = -1;
+    double best_ns = 0;
+    for (int v = 0; v < (int)(sizeof(kRaw) / sizeof(kRaw[0])); ++v) {
+        const RawBlock r = kRaw[v];
+        const int64_t lim = 0x7FFFFFFF / 4;
+        const int64_t a = (d.flags & MOA_FLAG_A_COL) ? (raw::SLAB + 1) * d.m : (int64_t)(r.bm + 1) * d.n;
+        const int64_t b = (d.flags & MOA_FLAG_B_COL) ? (int64_t)(r.bn + 1) * d.n : (raw::SLAB + 1) * d.p;
+        if (a >= lim || b >= lim || 9 * d.p >= lim) continue;
+        const int64_t blocks = ((d.m + r.bm - 1) / r.bm) * ((d.p + r.bn - 1) / r.bn);
+        const double ns = r.fixed + (double)((blocks + kNumCUs - 1) / kNumCUs) * r.each;
+        if (best < 0 || ns < best_ns) {
+            best = v;
+            best_ns = ns;
+        }
+    }
+    return best;
+}
 
 int split_bf16_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }
 
@@ -888,6 +458,15 @@ hipError_t launch_split_pack(const moa_gemm_desc &d, void *ws, hipStream_t st) {
 }
 
 hipError_t launch_split_bf16(const moa_gemm_desc &d, const Plan &plan, void *ws, hipStream_t st) {
+    if (plan.raw_block >= 0) {
+        TraceScope ts(MOA_K_SPLIT_BF16, st);
+        switch (plan.raw_block) {
+        case 0: return launch_raw<64, 64, 32, 32, 4>(d, st);
+        case 1: return launch_raw<64, 128, 32, 64, 3>(d, st);
+        case 2: return launch_raw<128, 64, 64, 32, 3>(d, st);
+        default: return launch_raw<128, 128, 64, 64, 3>(d, st);
+        }
+    }
     hipError_t e;
     {
         TraceScope ts(MOA_K_SPLIT_PACK, st);
@@ -915,18 +494,19 @@ namespace {
 __global__ void zero_counters_kernel(unsigned long long *x) {
     if (threadIdx.x < 8) x[4 * threadIdx.x] = 0ull;
 }
-constexpr int GB_M = 128, GW_M = 64, GW_N = 64, G_NST = 4;   // largest grouped block rows; raw-ring waves, depth
+constexpr int GB_M = 128;              // largest grouped block rows
 
-// Persistent kernels of a grouped launch: block, workgroups per CU, and the
-// relative time of one slab step of a block (measured on 256 x n x 256
-// members), which the static rule weighs slab steps with.
-struct GroupedKernel { int bm, bn, occ; double step_cost; };
+// Persistent kernels of a grouped launch: block, workgroups per CU, time of
+// one slab step of a block on a full CU (us of CU time: the 512 products of the
+// batching workload over their steps, tile changes included) and of a block
+// alone on its CU (512^3 .. 2048^3).
+struct GroupedKernel { int bm, bn, occ; double step_us, alone_us; };
 constexpr GroupedKernel kGroupedK[] = {
-    {128, 128, 3, 1.00},   // 0: split once into one plane set, two raw stages
-    {128, 128, 2, 1.25},   // 1: split once, two plane sets, three raw stages
-    {128, 128, 2, 0.95},   // 2: split in registers by every wave that reads a fragment
-    {64, 128, 4, 0.75},    // 3: split once, 64 x 128
-    {128, 64, 4, 0.75},    // 4: split once, 128 x 64
+    {128, 128, 2, 0.60, 0.48},   // 0: five stages
+    {64, 64, 4, 0.25, 0.26},     // 1
+    {128, 128, 2, 0.57, 0.48},   // 2: three stages
+    {64, 128, 3, 0.35, 0.33},    // 3
+    {128, 64, 4, 0.39, 0.33},    // 4
 };
 constexpr int kGroupedVariants = (int)(sizeof(kGroupedK) / sizeof(kGroupedK[0]));
 int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
@@ -965,21 +545,28 @@ int64_t split_grouped_workspace_bytes(const moa_gemm_desc *const *members, int c
 
 int split_grouped_variant_count() { return kGroupedVariants; }
 
-// Static rule: the block with the fewest weighted slab steps over the
-// members (ties to the earlier variant in the list); variants 0 and 1 are
-// left to the autotuner (variant 2 measured 1-12% faster than variant 0 on
-// the batching workload and 10-15% on groups of 1024^3 and 2048^3 products,
-// the same on groups of small ones).
+// Static rule. Short k walks (below 32 slabs): the block among 128 x 128, 64 x
+// 128 and 128 x 64 with the fewest slab steps over the members, weighted by the
+// time of a step. Longer ones: the block for which the CUs' share of the steps
+// plus the longest walk of one block is shortest, 64 x 64 among them -- a group
+// that leaves CUs idle is as slow as its longest walk (32 products 100 x 4000 x
+// 100: 115 us with 128 x 128 blocks, 95 with 64 x 128, 81 with 64 x 64; 64
+// products 512^3, which fill the CUs: 85, 106 and 134). Ties to the earlier
+// variant in the list; variant 0 is left to the autotuner.
 int split_grouped_default_variant(const moa_gemm_desc *const *members, int count) {
+    int64_t longest = 0;
+    for (int k = 0; k < count; ++k) longest = std::max(longest, (members[k]->n + SLAB - 1) / SLAB);
     int best = 2;
     double best_cost = 0;
-    for (int v : {2, 3, 4}) {
+    for (int v : {2, 3, 4, 1}) {
+        if (v == 1 && longest < 32) continue;
         double cost = 0;
         for (int k = 0; k < count; ++k) {
             const moa_gemm_desc &d = *members[k];
             cost += (double)member_tiles(d, kGroupedK[v].bm, kGroupedK[v].bn) * (double)((d.n + SLAB - 1) / SLAB);
         }
-        cost *= kGroupedK[v].step_cost;
+        cost *= kGroupedK[v].step_us;
+        if (longest >= 32) cost = cost / kNumCUs + (double)longest * kGroupedK[v].alone_us;
         if (v == 2 || cost < best_cost) {
             best = v;
             best_cost = cost;
@@ -1064,24 +651,24 @@ hipError_t launch_persistent(void *ws, int count, const GroupedWork &work, hipSt
     const dim3 gr((unsigned)grid), bl(256);
     switch (v) {
     case 1:
-        hipLaunchKernelGGL((split_grouped_conv_kernel<128, 128, 3, 2, 2>), gr, bl, 0, st, dev_members, tile_owner,
-                           bounds, counter);
+        hipLaunchKernelGGL((split_grouped_kernel<64, 64, 32, 32, 4>), gr, bl, 0, st, dev_members, tile_owner, bounds,
+                           counter);
         break;
     case 2:
-        hipLaunchKernelGGL((split_grouped_kernel<128, 128, GW_M, GW_N, G_NST>), gr, bl, 0, st, dev_members,
-                           tile_owner, bounds, counter);
+        hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
+                           counter);
         break;
     case 3:
-        hipLaunchKernelGGL((split_grouped_conv_kernel<64, 128, 2, 1, 4>), gr, bl, 0, st, dev_members, tile_owner,
-                           bounds, counter);
+        hipLaunchKernelGGL((split_grouped_kernel<64, 128, 32, 64, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
+                           counter);
         break;
     case 4:
-        hipLaunchKernelGGL((split_grouped_conv_kernel<128, 64, 2, 1, 4>), gr, bl, 0, st, dev_members, tile_owner,
-                           bounds, counter);
+        hipLaunchKernelGGL((split_grouped_kernel<128, 64, 64, 32, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
+                           counter);
         break;
     default:
-        hipLaunchKernelGGL((split_grouped_conv_kernel<128, 128, 2, 1, 3>), gr, bl, 0, st, dev_members, tile_owner,
-                           bounds, counter);
+        hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 5>), gr, bl, 0, st, dev_members, tile_owner, bounds,
+                           counter);
         break;
     }
     return hipGetLastError();
