@@ -124,8 +124,8 @@ typedef enum moa_path {
  * least 512 k); MOA_FLAG_SPLIT_K(1) keeps such a product unsplit. The result
  * is deterministic and within the path's error bound, but its summation order
  * differs from the unsplit product's, so it is not bitwise equal to it.
- * Grouped launches and the serving loop run split members as single launches
- * (the same plan as alone, so the same result); prepared groups refuse them.
+ * Grouped launches and the serving loop give split members the chunks they have
+ * alone (the same plan, so the same result); prepared groups refuse them.
  * The partials (c m p FP32 values) are part of the workspace. Occupies flag
  * bits 16..23. */
 #define MOA_FLAG_SPLIT_K(c) (((uint32_t)(c) & 0xFFu) << 16)
@@ -211,12 +211,14 @@ moa_status moa_gemm_noalloc(const moa_gemm_desc *desc, void *stream);
  * many products at once). Row-major members on the split-BF16 path
  * (including F32 with MOA_PATH_AUTO) are contracted by ONE persistent launch
  * that walks a shared tile list and splits the FP32 operands into hi/lo BF16
- * on the way through LDS (no conditioning pass); scaled-FP8 members are
- * conditioned together and contracted by one persistent launch per term
- * count; members on the ONF and FP32 matrix-core paths, and members with a
- * column-major operand or a split k walk, run as single launches on the same
- * stream. No ordering among members. Each result is bitwise the result
- * moa_gemm gives for the same descriptor, whichever persistent kernel runs.
+ * on the way through LDS (no conditioning pass; a member that splits its k
+ * walk puts one item per chunk on the list, and its partials are summed
+ * behind the launch); scaled-FP8 members are conditioned together and
+ * contracted by one persistent launch per term count; members on the ONF and
+ * FP32 matrix-core paths, members with a column-major operand and scaled-FP8
+ * members with a split k walk run as single launches on the same stream. No
+ * ordering among members. Each result is bitwise the result moa_gemm gives for
+ * the same descriptor, whichever persistent kernel runs.
  * Descriptors are read on the host during the call; the array may be reused
  * when the call returns.
  * Errors: as moa_gemm, checked for every member before anything launches;

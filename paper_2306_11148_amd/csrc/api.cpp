@@ -89,7 +89,12 @@ moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixe
         return fail(MOA_ERR_NOMEM, "the product needs %lld bytes of scratch, the fixed scratch array holds %lld",
                     (long long)pl.workspace_bytes, (long long)fixed_bytes);
     void *ws = fixed_ws;
-    const bool cached = !fixed_ws && pl.path != MOA_PATH_ONF && pl.raw_block < 0;
+    // without conditioning only the split-k partials are used
+    if (pl.raw_block >= 0 && !fixed_ws) {
+        pl.workspace_bytes -= pl.split_k > 1 ? pl.partial_offset : pl.workspace_bytes;
+        pl.partial_offset = 0;
+    }
+    const bool cached = !fixed_ws && pl.path != MOA_PATH_ONF && pl.workspace_bytes > 0;
     if (cached && (s = scratch_alloc(&ws, pl.workspace_bytes, stream)) != MOA_OK) return s;
     hipError_t e = hipSuccess;
     switch (pl.path) {

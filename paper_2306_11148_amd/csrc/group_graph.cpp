@@ -84,17 +84,19 @@ moa_status moa_group_create(const moa_gemm_desc *descs, int64_t count, moa_group
             release(g);
             return hip_fail(e, "hipEventCreateWithFlags");
         }
-        GroupedWork work{0, 0, 0};
+        GroupedWork work{0, 0, 0, 0};
+        SplitGroup items;
         const int cnt = (int)split.size();
         if (cnt > 0) {
-            e = hipMalloc(&g->ws, (size_t)split_grouped_workspace_bytes(split.data(), cnt));
+            for (const moa_gemm_desc *d : split) split_group_add(items, *d, 1, nullptr);
+            e = hipMalloc(&g->ws, (size_t)split_grouped_workspace_bytes(items));
             if (e != hipSuccess) {
                 release(g);
                 return fail(MOA_ERR_NOMEM, "group workspace: %s", hipGetErrorString(e));
             }
-            std::vector<char> host((size_t)split_grouped_desc_bytes(split.data(), cnt));
-            work = split_grouped_layout(split.data(), cnt, g->ws, host.data(),
-                                        split_grouped_choose(split.data(), cnt, -1, nullptr));
+            std::vector<char> host((size_t)split_grouped_table_bytes(items));
+            work = split_grouped_layout(items, host.data(),
+                                        split_grouped_choose(split.data(), cnt, items, -1, nullptr));
             e = hipMemcpy(static_cast<char *>(g->ws) + 256, host.data(), host.size(), hipMemcpyHostToDevice);
             if (e != hipSuccess) {
                 release(g);
@@ -132,7 +134,7 @@ moa_status moa_group_create(const moa_gemm_desc *descs, int64_t count, moa_group
             }
         }
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess && cnt > 0) e = split_grouped_enqueue(g->ws, cnt, work, cs);
+        if (e == hipSuccess && cnt > 0) e = split_grouped_enqueue(g->ws, items, work, cs);
         for (int two = 0; two < 2 && e == hipSuccess; ++two)
             if (!fp8[two].empty()) e = fp8_grouped_enqueue(g->ws8[two], (int)fp8[two].size(), two != 0, work8[two], cs);
         moa_status rs = MOA_OK;

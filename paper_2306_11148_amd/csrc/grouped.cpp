@@ -1,10 +1,11 @@
 // moa_gemm_grouped: independent products in one launch sequence.
 //
 // Members on the split-BF16 path (the path of the batching workload) are
-// conditioned together and contracted by one persistent launch that walks a
-// shared tile list; scaled-FP8 members likewise, one sequence per term count.
-// Members on the ONF and FP32 matrix-core paths run as single launches, in
-// order, on the same stream. The member tables of the persistent launches
+// contracted by one persistent launch that walks a shared tile list (members
+// that split their k walk put one item per chunk on it, and one kernel adds
+// their partials afterwards); scaled-FP8 members are conditioned together and
+// contracted likewise, one sequence per term count. Members on the ONF and FP32
+// matrix-core paths run as single launches, in order, on the same stream. The member tables of the persistent launches
 // are written to pinned, coherent staging buffers, mapped into the device's
 // address space, that are recycled once the stream has consumed them; each
 // launch reads its table from there with a small kernel.
@@ -116,15 +117,11 @@ void *arena_take(ScratchArena *a, int64_t bytes) {
     return static_cast<char *>(a->base) + off;
 }
 
-// One persistent launch sequence over `list`: workspace from `arena` when
-// given, else from the scratch cache; member table through pinned staging.
-template <class Bytes, class Launch>
-moa_status run_list(const std::vector<const moa_gemm_desc *> &list, int64_t desc_bytes, Bytes ws_bytes,
-                    Launch launch, hipStream_t stream, ScratchArena *arena) {
-    if (list.empty()) return MOA_OK;
-    if (list.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
-    const int cnt = (int)list.size();
-    const int64_t need = ws_bytes(list.data(), cnt);
+// One persistent launch sequence: `need` bytes of workspace from `arena` when
+// given, else from the scratch cache; its table of `desc_bytes` bytes through
+// pinned staging.
+template <class Launch>
+moa_status run_persistent(int64_t desc_bytes, int64_t need, Launch launch, hipStream_t stream, ScratchArena *arena) {
     void *ws = nullptr;
     moa_status s = MOA_OK;
     if (arena) {
@@ -139,35 +136,59 @@ moa_status run_list(const std::vector<const moa_gemm_desc *> &list, int64_t desc
         if (!arena) scratch_free(ws, stream);
         return s;
     }
-    const hipError_t e = launch(list.data(), cnt, ws, st.ptr, st.dev);
+    const hipError_t e = launch(ws, st.ptr, st.dev);
     staging_release(st, stream);
     if (!arena) scratch_free(ws, stream);
     if (e != hipSuccess) return hip_fail(e, "grouped launch");
     return MOA_OK;
 }
 
-// The members that run as persistent launches (split-BF16; FP8 by term
-// count) and those that run singly, as run_grouped splits them.
+// The members that run in persistent launches (split-BF16, `chunked` those that
+// split their k walk into so many chunks; FP8 by term count) and those that run
+// singly, as run_grouped splits them.
 struct Partition {
     std::vector<const moa_gemm_desc *> single, split, fp8[2];
+    std::vector<std::pair<const moa_gemm_desc *, int>> chunked;
 };
 
-Partition partition(const moa_gemm_desc *descs, int64_t count, const char *split_k = nullptr) {
+Partition partition(const moa_gemm_desc *descs, int64_t count, const int *split_k = nullptr) {
     Partition pt;
     for (int64_t g = 0; g < count; ++g) {
         const moa_gemm_desc &d = descs[g];
         if (d.m == 0 || d.p == 0) continue;
         const moa_path path = resolve_path(d);
-        if (has_col_operand(d) || (split_k ? split_k[g] != 0 : plans_split_k(d)))   // the persistent launches take
-            pt.single.push_back(&d);                  // row-major, unsplit members
+        const int chunks = split_k ? split_k[g] : planned_split_k(d);
+        if (has_col_operand(d))         // the persistent launches take row-major members
+            pt.single.push_back(&d);
+        else if (path == MOA_PATH_SPLIT_BF16 && split_grouped_fits(d) && chunks > 1)
+            pt.chunked.push_back({&d, chunks});
         else if (path == MOA_PATH_SPLIT_BF16 && split_grouped_fits(d))
             pt.split.push_back(&d);
-        else if (path == MOA_PATH_FP8_SCALED)
+        else if (path == MOA_PATH_FP8_SCALED && chunks <= 1)
             pt.fp8[fp8_two_term(d) ? 1 : 0].push_back(&d);
         else
             pt.single.push_back(&d);
     }
     return pt;
+}
+
+// Bytes of the chunked members' partials, 256-byte aligned each.
+int64_t partial_bytes(const Partition &pt) {
+    int64_t b = 0;
+    for (const auto &c : pt.chunked) b += align256((int64_t)c.second * c.first->m * c.first->p * 4);
+    return b;
+}
+
+// The items of the split-BF16 launch, partials carved from `partials`.
+SplitGroup split_items(const Partition &pt, void *partials) {
+    SplitGroup g;
+    for (const moa_gemm_desc *d : pt.split) split_group_add(g, *d, 1, nullptr);
+    char *at = static_cast<char *>(partials);
+    for (const auto &c : pt.chunked) {
+        split_group_add(g, *c.first, c.second, reinterpret_cast<float *>(at));
+        if (at) at += align256((int64_t)c.second * c.first->m * c.first->p * 4);
+    }
+    return g;
 }
 
 }  // namespace
@@ -176,8 +197,8 @@ int64_t grouped_scratch_bytes(const moa_gemm_desc *descs, int64_t count) {
     const Partition pt = partition(descs, count);
     int64_t total = 0;
     for (const moa_gemm_desc *d : pt.single) total += align256(gemm_workspace_bytes(*d));
-    if (!pt.split.empty())
-        total += align256(split_grouped_workspace_bytes(pt.split.data(), (int)pt.split.size()));
+    if (!pt.split.empty() || !pt.chunked.empty())
+        total += align256(align256(split_grouped_workspace_bytes(split_items(pt, nullptr))) + partial_bytes(pt));
     for (int two = 0; two < 2; ++two)
         if (!pt.fp8[two].empty())
             total += align256(fp8_grouped_workspace_bytes(pt.fp8[two].data(), (int)pt.fp8[two].size(), two != 0));
@@ -185,10 +206,8 @@ int64_t grouped_scratch_bytes(const moa_gemm_desc *descs, int64_t count) {
 }
 
 moa_status run_grouped(const moa_gemm_desc *descs, int64_t count, hipStream_t stream, ScratchArena *arena,
-                       int split_variant, const char *split_k) {
+                       int split_variant, const int *split_k) {
     const Partition pt = partition(descs, count, split_k);
-    const int sv = pt.split.empty() ? 0 : split_grouped_choose(pt.split.data(), (int)pt.split.size(), split_variant,
-                                                               nullptr);
     for (const moa_gemm_desc *d : pt.single) {
         moa_status s;
         if (arena) {
@@ -202,20 +221,32 @@ moa_status run_grouped(const moa_gemm_desc *descs, int64_t count, hipStream_t st
         }
         if (s != MOA_OK) return s;
     }
-    moa_status s = run_list(
-        pt.split, split_grouped_desc_bytes(pt.split.data(), (int)pt.split.size()), split_grouped_workspace_bytes,
-        [&](const moa_gemm_desc *const *m, int c, void *ws, void *host, void *host_dev) {
-            return launch_split_grouped(m, c, sv, ws, host, host_dev, stream);
-        },
-        stream, arena);
-    for (int two = 0; two < 2 && s == MOA_OK; ++two)
-        s = run_list(
-            pt.fp8[two], fp8_grouped_desc_bytes((int)pt.fp8[two].size()),
-            [&](const moa_gemm_desc *const *m, int c) { return fp8_grouped_workspace_bytes(m, c, two != 0); },
-            [&](const moa_gemm_desc *const *m, int c, void *ws, void *host, void *host_dev) {
-                return launch_fp8_grouped(m, c, two != 0, ws, host, host_dev, stream);
+    moa_status s = MOA_OK;
+    if (!pt.split.empty() || !pt.chunked.empty()) {
+        SplitGroup g = split_items(pt, nullptr);
+        if (g.items.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
+        const int v = split_grouped_choose(pt.split.data(), (int)pt.split.size(), g, split_variant, nullptr);
+        const int64_t tables = align256(split_grouped_workspace_bytes(g));
+        s = run_persistent(
+            split_grouped_table_bytes(g), tables + partial_bytes(pt),
+            [&](void *ws, void *host, void *host_dev) {
+                if (!pt.chunked.empty()) g = split_items(pt, static_cast<char *>(ws) + tables);
+                return launch_split_grouped(g, v, ws, host, host_dev, stream);
             },
             stream, arena);
+    }
+    for (int two = 0; two < 2 && s == MOA_OK; ++two) {
+        const auto &list = pt.fp8[two];
+        if (list.empty()) continue;
+        if (list.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
+        const int c = (int)list.size();
+        s = run_persistent(
+            fp8_grouped_desc_bytes(c), fp8_grouped_workspace_bytes(list.data(), c, two != 0),
+            [&](void *ws, void *host, void *host_dev) {
+                return launch_fp8_grouped(list.data(), c, two != 0, ws, host, host_dev, stream);
+            },
+            stream, arena);
+    }
     return s;
 }
 
@@ -225,19 +256,19 @@ using namespace moa;
 
 namespace {
 
-// Validates every member and plans it once; `split_k` (optional) receives
-// whether each member's plan splits k.
-moa_status check_grouped_args(const moa_gemm_desc *descs, int64_t count, std::vector<char> *split_k = nullptr) {
+// Validates every member and plans it once; `split_k` (optional) receives each
+// member's chunk count.
+moa_status check_grouped_args(const moa_gemm_desc *descs, int64_t count, std::vector<int> *split_k = nullptr) {
     if (count < 0) return fail(MOA_ERR_INVALID, "negative count");
     if (count > 0 && !descs) return fail(MOA_ERR_INVALID, "null descriptor array");
-    if (split_k) split_k->assign((size_t)count, 0);
+    if (split_k) split_k->assign((size_t)count, 1);
     for (int64_t g = 0; g < count; ++g) {
         moa_status s = validate(descs[g], true);
         if (s != MOA_OK) return s;
         Plan pl;
         if (descs[g].m > 0 && descs[g].p > 0) {
             if ((s = make_plan(descs[g], &pl)) != MOA_OK) return s;
-            if (split_k) (*split_k)[(size_t)g] = pl.split_k > 1 ? 1 : 0;
+            if (split_k) (*split_k)[(size_t)g] = pl.split_k;
         }
     }
     return check_group_overlap(descs, count);
@@ -254,7 +285,7 @@ extern "C" moa_status moa_gemm_grouped_variant(const moa_gemm_desc *descs, int64
     try {
         if (variant < -1 || variant >= split_grouped_variant_count())
             return fail(MOA_ERR_INVALID, "grouped variant %d out of range", (int)variant);
-        std::vector<char> split_k;
+        std::vector<int> split_k;
         moa_status s = check_grouped_args(descs, count, &split_k);
         if (s != MOA_OK) return s;
         return run_grouped(descs, count, static_cast<hipStream_t>(stream), nullptr, variant, split_k.data());
@@ -266,15 +297,17 @@ extern "C" moa_status moa_gemm_grouped_variant(const moa_gemm_desc *descs, int64
 extern "C" moa_status moa_grouped_plan_query(const moa_gemm_desc *descs, int64_t count, int32_t *variant,
                                              int32_t *tuned, int64_t *persistent_members) {
     try {
-        std::vector<char> split_k;
+        std::vector<int> split_k;
         moa_status s = check_grouped_args(descs, count, &split_k);
         if (s != MOA_OK) return s;
         const Partition pt = partition(descs, count, split_k.data());
         bool t = false;
-        const int v = pt.split.empty() ? -1 : split_grouped_choose(pt.split.data(), (int)pt.split.size(), -1, &t);
+        const int64_t members = (int64_t)(pt.split.size() + pt.chunked.size());
+        const int v = members == 0 ? -1 : split_grouped_choose(pt.split.data(), (int)pt.split.size(),
+                                                               split_items(pt, nullptr), -1, &t);
         if (variant) *variant = v;
         if (tuned) *tuned = t ? 1 : 0;
-        if (persistent_members) *persistent_members = (int64_t)pt.split.size();
+        if (persistent_members) *persistent_members = members;
         return MOA_OK;
     } catch (...) {
         return fail(MOA_ERR_DEVICE, "internal error");
@@ -285,7 +318,7 @@ extern "C" moa_status moa_autotune_grouped(const moa_gemm_desc *descs, int64_t c
                                            int32_t *chosen, double *best_ms) {
     try {
         if (reps < 1) return fail(MOA_ERR_INVALID, "reps must be >= 1");
-        std::vector<char> split_k;
+        std::vector<int> split_k;
         moa_status s = check_grouped_args(descs, count, &split_k);
         if (s != MOA_OK) return s;
         const Partition pt = partition(descs, count, split_k.data());

@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <string>
+#include <vector>
 
 #include "moa.h"
 
@@ -85,11 +86,11 @@ inline int split_k_chunks(int requested, int64_t S) {
 moa_status validate(const moa_gemm_desc &d, bool need_ptrs);
 moa_path resolve_path(const moa_gemm_desc &d);
 moa_status make_plan(const moa_gemm_desc &d, Plan *out);
-// Whether the plan of `d` sums k in chunks over separate workgroups (asked
-// for or chosen by the planner).
-inline bool plans_split_k(const moa_gemm_desc &d) {
+// Chunks into which the plan of `d` cuts its k walk (asked for or chosen by the
+// planner; 1: none).
+inline int planned_split_k(const moa_gemm_desc &d) {
     Plan pl;
-    return d.m > 0 && d.p > 0 && make_plan(d, &pl) == MOA_OK && pl.split_k > 1;
+    return d.m > 0 && d.p > 0 && make_plan(d, &pl) == MOA_OK ? pl.split_k : 1;
 }
 
 // gfx950 constants used by the static rule and the planner.
@@ -153,40 +154,63 @@ int split_bf16_variant_count();
 int split_bf16_default_variant(int64_t m, int64_t p);   // the planner's default block
 int64_t split_bf16_workspace_bytes(int64_t m, int64_t n, int64_t p);
 int split_raw_block(const moa_gemm_desc &d);            // block without conditioning, -1: conditioned
-// Grouped split-BF16: all `members` in one persistent launch. `host_staging` is pinned memory of at least
-// split_grouped_desc_bytes(count) bytes that stays untouched until the
-// stream has passed this call.
-int64_t split_grouped_workspace_bytes(const moa_gemm_desc *const *members, int count);
+bool split_raw_splitk(const moa_gemm_desc &d);          // a split-k product without conditioning
+// Grouped split-BF16: all items in one persistent launch. An item is a product
+// or, for a member that splits its k walk, one chunk of it: a window of n of the
+// rows' ld elements, whose sum goes to the chunk's partial; a SplitSum adds a
+// member's partials in chunk order afterwards.
+struct SplitItem {
+    const float *A, *B;
+    float *C;
+    int64_t m, n, p, ld;
+    int32_t accumulate;
+};
+struct SplitSum {
+    const float *partials;
+    float *C;
+    int64_t mp;                         // elements
+    int32_t chunks, accumulate;
+    int64_t first_block;                // first block of the summing kernel (set by the layout)
+};
+struct SplitGroup {
+    std::vector<SplitItem> items;
+    std::vector<SplitSum> sums;
+};
+// Appends `d`: one item, or split_k chunks with their partials at `partials`.
+void split_group_add(SplitGroup &g, const moa_gemm_desc &d, int split_k, float *partials);
+// Workspace of the launch (tables and claim counters) and the bytes of its
+// host table. `host_staging` is pinned memory of at least
+// split_grouped_table_bytes bytes that stays untouched until the stream has
+// passed the call.
+int64_t split_grouped_workspace_bytes(const SplitGroup &g);
+int64_t split_grouped_table_bytes(const SplitGroup &g);
 // Whether a split-BF16 member fits the persistent launch's 32-bit offsets
 // (else it runs as a single launch).
 bool split_grouped_fits(const moa_gemm_desc &d);
-int64_t split_grouped_desc_bytes(const moa_gemm_desc *const *members, int count);
 // `host_staging_dev`: the staging buffer's address in the device's address
 // space (null: the table goes up by a copy instead of being read in place).
-hipError_t launch_split_grouped(const moa_gemm_desc *const *members, int count, int variant, void *workspace,
-                                void *host_staging, const void *host_staging_dev, hipStream_t stream);
+hipError_t launch_split_grouped(const SplitGroup &g, int variant, void *workspace, void *host_staging,
+                                const void *host_staging_dev, hipStream_t stream);
 // Persistent split-BF16 kernels of a grouped launch (blocks 128 x 128 with two
 // ring depths, 64 x 64, 64 x 128, 128 x 64), the static rule's choice, and the choice a
 // grouped launch makes: `forced` when >= 0, else the autotuner's record for
-// the members' class, else the static rule.
+// the class of the unsplit members, else the static rule over the items.
 int split_grouped_variant_count();
-int split_grouped_default_variant(const moa_gemm_desc *const *members, int count);
-int split_grouped_choose(const moa_gemm_desc *const *members, int count, int forced, bool *tuned);
+int split_grouped_default_variant(const SplitGroup &g);
+int split_grouped_choose(const moa_gemm_desc *const *members, int count, const SplitGroup &g, int forced, bool *tuned);
 int tuned_group_variant(const moa_gemm_desc *const *members, int count);
 void record_tuned_group_variant(const moa_gemm_desc *const *members, int count, int variant, double ms);
-// The two halves of launch_split_grouped: host layout (returns the sizes of
-// the contraction and conditioning work lists; the member array to upload is
-// in host_staging) and the device sequence, which allocates, copies and clears
+// The two halves of launch_split_grouped: host layout (the table to upload is in
+// host_staging) and the device sequence, which allocates, copies and clears
 // nothing (graph-capturable).
 struct GroupedWork {
-    int64_t tiles;                      // contraction tiles over all members
-    int64_t pack_items;                 // conditioning items over all members
+    int64_t tiles;                      // contraction tiles over all items
+    int64_t sum_blocks;                 // blocks of the summing kernel
     int variant;                        // persistent kernel
-    int64_t table_used;                 // bytes of the member table the launch reads (a prefix)
+    int64_t table_used;                 // bytes of the table the launch reads (a prefix)
 };
-GroupedWork split_grouped_layout(const moa_gemm_desc *const *members, int count, void *workspace,
-                                 void *host_staging, int variant);
-hipError_t split_grouped_enqueue(void *workspace, int count, const GroupedWork &work, hipStream_t stream);
+GroupedWork split_grouped_layout(const SplitGroup &g, void *host_staging, int variant);
+hipError_t split_grouped_enqueue(void *workspace, const SplitGroup &g, const GroupedWork &work, hipStream_t stream);
 
 hipError_t launch_fp8(const moa_gemm_desc &d, const Plan &plan, void *workspace,
                       hipStream_t stream);
@@ -231,9 +255,10 @@ moa_status run_gemm(const moa_gemm_desc &d, hipStream_t stream);
 // (MOA_ERR_NOMEM if the plan needs more), or the cached scratch when null.
 moa_status run_gemm_in(const moa_gemm_desc &d, hipStream_t stream, void *fixed_ws, int64_t fixed_bytes);
 
-// Grouped products (validated by the caller): split-BF16 members in one
-// persistent launch sequence, scaled-FP8 members in one per term count, the
-// others (and split-k or column-major members) one after another.
+// Grouped products (validated by the caller): split-BF16 members (split-k ones
+// chunk by chunk) in one persistent launch sequence, scaled-FP8 members in one
+// per term count, the others (and column-major or split-k FP8 members) one
+// after another.
 // A caller-owned block of device memory that a grouped launch carves its
 // scratch from (256-byte aligned pieces, in launch order) instead of the
 // scratch cache.
@@ -242,10 +267,10 @@ struct ScratchArena {
     int64_t size = 0;
     int64_t used = 0;
 };
-// `split_k` (optional): per member, whether its plan splits k (as the caller
+// `split_k` (optional): per member, its plan's chunk count (as the caller
 // already planned it), so that members are not planned twice.
 moa_status run_grouped(const moa_gemm_desc *descs, int64_t count, hipStream_t stream,
-                       ScratchArena *arena = nullptr, int split_variant = -1, const char *split_k = nullptr);
+                       ScratchArena *arena = nullptr, int split_variant = -1, const int *split_k = nullptr);
 // Bytes of scratch run_grouped takes from an arena for these members.
 int64_t grouped_scratch_bytes(const moa_gemm_desc *descs, int64_t count);
 // Scratch bytes of one product under its plan (0 for empty products).

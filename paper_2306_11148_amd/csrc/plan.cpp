@@ -75,7 +75,8 @@ void record_tuned_group_variant(const moa_gemm_desc *const *members, int count, 
     g_tuned[group_key(members, count)] = {variant, ms};
 }
 
-int split_grouped_choose(const moa_gemm_desc *const *members, int count, int forced, bool *tuned) {
+int split_grouped_choose(const moa_gemm_desc *const *members, int count, const SplitGroup &g, int forced,
+                         bool *tuned) {
     if (tuned) *tuned = false;
     if (forced >= 0) return forced;
     const int t = tuned_group_variant(members, count);
@@ -83,7 +84,7 @@ int split_grouped_choose(const moa_gemm_desc *const *members, int count, int for
         if (tuned) *tuned = true;
         return t;
     }
-    return split_grouped_default_variant(members, count);
+    return split_grouped_default_variant(g);
 }
 
 int tuned_variant(const moa_gemm_desc &d, moa_path path) {
@@ -268,7 +269,10 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
         // Products of few blocks run without conditioning unless a flag or the
         // autotuner names a record-ring block. The plan's other fields stay those
         // of the conditioned form (fixed scratch refuses the same products).
-        else if (forced < 0 && !pl.tuned && split_k_requested(d) == 0) pl.raw_block = split_raw_block(d);
+        if (forced < 0 && !pl.tuned) {
+            if (pl.split_k > 1) pl.raw_block = split_raw_splitk(d) ? 3 : -1;
+            else if (split_k_requested(d) == 0) pl.raw_block = split_raw_block(d);
+        }
         // 256 record rows of (n/16) 64-byte records must stay below 2^31 bytes
         // (32-bit buffer offsets of one tile).
         if ((d.n + 15) / 16 > 131071)

@@ -41,11 +41,12 @@ namespace raw {
 
 constexpr int SLAB = 16;
 
-// One product's operands.
+// One product's operands. ld: elements from row to row of a k-contiguous operand
+// (n for a whole product, more for a window of its k walk).
 struct Operands {
     const float *A, *B;
     float *C;
-    int64_t m, n, p;
+    int64_t m, n, p, ld;
     int accumulate;
 };
 
@@ -118,15 +119,16 @@ __device__ __forceinline__ void block(const Operands &d, int64_t i0, int64_t j0,
     // for every slab. Slabs past the last have empty ranges: their loads touch
     // no memory but keep the count of loads in flight.
     const int64_t a_live = m - i0 < BM ? m - i0 : BM, b_live = p - j0 < BN ? p - j0 : BN;
-    const char *a_src = reinterpret_cast<const char *>(d.A + (A_KC ? i0 * n : i0));
-    const char *b_src = reinterpret_cast<const char *>(d.B + (B_KC ? j0 * n : j0));
-    int64_t a_left = (A_KC ? a_live * n : n * m - i0) * 4, b_left = (B_KC ? b_live * n : n * p - j0) * 4;
+    const char *a_src = reinterpret_cast<const char *>(d.A + (A_KC ? i0 * d.ld : i0));
+    const char *b_src = reinterpret_cast<const char *>(d.B + (B_KC ? j0 * d.ld : j0));
+    int64_t a_left = (A_KC ? (a_live - 1) * d.ld + n : n * m - i0) * 4;
+    int64_t b_left = (B_KC ? (b_live - 1) * d.ld + n : n * p - j0) * 4;
     const int64_t a_step = (A_KC ? 1 : m) * SLAB * 4, b_step = (B_KC ? 1 : p) * SLAB * 4;
     int voff[LPW];
 #pragma unroll
-    for (int q = 0; q < LPA; ++q) voff[q] = OA::voffset(wave * LPA + q, lane, a_live, (A_KC ? n : m) * 4);
+    for (int q = 0; q < LPA; ++q) voff[q] = OA::voffset(wave * LPA + q, lane, a_live, (A_KC ? d.ld : m) * 4);
 #pragma unroll
-    for (int q = 0; q < LPB; ++q) voff[LPA + q] = OB::voffset(wave * LPB + q, lane, b_live, (B_KC ? n : p) * 4);
+    for (int q = 0; q < LPB; ++q) voff[LPA + q] = OB::voffset(wave * LPB + q, lane, b_live, (B_KC ? d.ld : p) * 4);
     int to_issue = S;
     auto clip = [](int64_t x) {                              // 0 .. 2^31 - 1, in 32-bit scalar steps
         const int hi = (int)(x >> 32);
@@ -334,6 +336,28 @@ __global__ __launch_bounds__(256, 2) void single_kernel(Operands d, int tiles_m,
     int tm, tn;
     ring::block_of(tiles_m, tiles_n, &tm, &tn);
     block<BM, BN, WM, WN, NST, A_KC, B_KC>(d, (int64_t)tm * BM, (int64_t)tn * BN, lds);
+}
+
+// Split-k (the sigma loop cut into runs of chunk_slabs slabs): workgroup w takes
+// chunk w / tiles of block w mod tiles (after the XCD remap, so the blocks of
+// one chunk share an L2) and writes its block sum to partials + chunk m p.
+template <int BM, int BN, int WM, int WN, int NST, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(256, 2) void splitk_kernel(Operands d, int tiles_m, int tiles_n, int chunk_slabs,
+                                                        float *partials) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[Cfg<BM, BN, WM, WN, NST>::LDS];
+    const int tiles = tiles_m * tiles_n;
+    const int id = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, (int)gridDim.x));
+    const int chunk = id / tiles;
+    int tm, tn;
+    tile_coords(id - chunk * tiles, tiles_m, tiles_n, 8, &tm, &tn);
+    const int64_t k0 = (int64_t)chunk * chunk_slabs * SLAB;
+    d.A += A_KC ? k0 : k0 * d.m;
+    d.B += B_KC ? k0 : k0 * d.p;
+    d.C = partials + (int64_t)chunk * d.m * d.p;
+    d.n = min((int64_t)chunk_slabs * SLAB, d.n - k0);
+    d.accumulate = 0;
+    block<BM, BN, WM, WN, NST, A_KC, B_KC>(d, (int64_t)__builtin_amdgcn_readfirstlane(tm) * BM,
+                                           (int64_t)__builtin_amdgcn_readfirstlane(tn) * BN, lds);
 }
 
 }  // namespace raw

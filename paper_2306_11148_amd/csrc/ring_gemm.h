@@ -364,23 +364,80 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void splitk_kernel(Oper
                                           partials + (int64_t)chunk * op.m * op.p);
 }
 
-// Deterministic reduction of the chunk partials: C = ((P_0 + P_1) + ...) + P_c-1,
-// then the descale (scaled modes) and the accumulate form, as the epilogue of
-// an unsplit product does.
-static __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partials, int chunks,
-                                                            int64_t m, int64_t p, float *__restrict__ C,
-                                                            const int32_t *__restrict__ row_exp,
-                                                            const int32_t *__restrict__ col_exp, int accumulate) {
-    const int64_t mp = m * p;
-    for (int64_t i = blockIdx.y; i < m; i += gridDim.y)
-        for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < p; j += (int64_t)gridDim.x * 256) {
-            const int64_t x = i * p + j;
-            float v = partials[x];
-            for (int q = 1; q < chunks; ++q) v += partials[(int64_t)q * mp + x];
-            if (row_exp) v = ldexpf(v, -(row_exp[i] + col_exp[j]));
-            if (accumulate) v += C[x];
-            C[x] = v;
+// W consecutive elements of C from their chunk partials (mp apart), in chunk
+// order: C = ((P_0 + P_1) + ...) + P_c-1, then the descale (scaled modes) and
+// the accumulate form, as the epilogue of an unsplit product does. Eight chunks'
+// loads are in flight together: the sum is a chain, the loads need not be.
+template <int W>
+__device__ __forceinline__ void splitk_sum(const float *__restrict__ partials, int chunks, int64_t mp, int64_t x,
+                                           float *__restrict__ C, int exponent, const int32_t *col_exp,
+                                           int accumulate) {
+    typedef float vec __attribute__((ext_vector_type(W == 1 ? 2 : W)));
+    float v[W];
+    auto load = [&](const float *src, float (&out)[W]) {
+        if constexpr (W == 1) {
+            out[0] = *src;
+        } else {
+            const vec y = *reinterpret_cast<const vec *>(src);
+#pragma unroll
+            for (int e = 0; e < W; ++e) out[e] = y[e];
         }
+    };
+    load(partials + x, v);
+#pragma unroll 8
+    for (int q = 1; q < chunks; ++q) {
+        float y[W];
+        load(partials + (int64_t)q * mp + x, y);
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[e] += y[e];
+    }
+    if (col_exp) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[e] = ldexpf(v[e], -(exponent + col_exp[e]));
+    }
+    if (accumulate) {
+        float old[W];
+        load(C + x, old);
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[e] += old[e];
+    }
+    if constexpr (W == 1) {
+        C[x] = v[0];
+    } else {
+        vec y;
+#pragma unroll
+        for (int e = 0; e < W; ++e) y[e] = v[e];
+        *reinterpret_cast<vec *>(C + x) = y;
+    }
+}
+
+// The whole m x p array, W elements per thread (W divides p).
+template <int W>
+static __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partials, int chunks,
+                                                                   int64_t m, int64_t p, float *__restrict__ C,
+                                                                   const int32_t *__restrict__ row_exp,
+                                                                   const int32_t *__restrict__ col_exp,
+                                                                   int accumulate) {
+    const int64_t mp = m * p;
+    for (int64_t x = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W; x < mp; x += (int64_t)gridDim.x * 256 * W) {
+        const int64_t i = row_exp ? x / p : 0;
+        splitk_sum<W>(partials, chunks, mp, x, C, row_exp ? row_exp[i] : 0, row_exp ? col_exp + (x - i * p) : nullptr,
+                      accumulate);
+    }
+}
+
+inline hipError_t launch_splitk_reduce(const float *partials, int chunks, int64_t m, int64_t p, float *C,
+                                       const int32_t *row_exp, const int32_t *col_exp, int accumulate,
+                                       hipStream_t st) {
+    const bool wide = p % 4 == 0 && (uintptr_t)C % 16 == 0 && (uintptr_t)partials % 16 == 0;
+    const dim3 grid((unsigned)std::min<int64_t>((m * p / (wide ? 4 : 1) + 255) / 256, 65536));
+    if (wide)
+        hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, st, partials, chunks, m, p, C, row_exp, col_exp,
+                           accumulate);
+    else
+        hipLaunchKernelGGL(splitk_reduce_kernel<1>, grid, dim3(256), 0, st, partials, chunks, m, p, C, row_exp, col_exp,
+                           accumulate);
+    return hipGetLastError();
 }
 
 // Host side of a split-k launch: chunk kernel, then the reduction.
@@ -392,10 +449,7 @@ hipError_t launch_splitk(const Operands &op, int chunks, float *partials, hipStr
     hipLaunchKernelGGL((splitk_kernel<BM, BN, WM, WN, NREC, Mode, NST>), dim3(tiles_m * tiles_n * chunks),
                        dim3(Cfg<BM, BN, WM, WN, NREC, NST>::THREADS), 0, st, op, tiles_m, tiles_n, chunk_slabs,
                        partials);
-    const dim3 grid((unsigned)std::min<int64_t>((op.p + 255) / 256, 64), (unsigned)std::min<int64_t>(op.m, 65535));
-    hipLaunchKernelGGL(splitk_reduce_kernel, grid, dim3(256), 0, st, partials, chunks, op.m, op.p, op.C, op.row_exp,
-                       op.col_exp, op.accumulate);
-    return hipGetLastError();
+    return launch_splitk_reduce(partials, chunks, op.m, op.p, op.C, op.row_exp, op.col_exp, op.accumulate, st);
 }
 
 // Host check of the direct loads of single-product launches over an m x p

@@ -243,11 +243,9 @@ ring::Operands split_operands(const uint8_t *Ap, const uint8_t *Bp, float *C, in
 // conditioning pass: every tile is a block of raw_gemm.h, so grouped and single
 // results are bitwise equal, whichever kernel and block shape run.
 struct GroupMember {
-    const float *A, *B;
-    float *C;
-    int64_t m, n, p, S;
-    int64_t first_tile;                 // first contraction work-list id of this member
-    int32_t tiles_n, accumulate;
+    SplitItem item;
+    int32_t tiles_n;
+    int64_t first_tile;                 // first contraction work-list id of this item
 };
 
 // Work-list claims, XCD by XCD. The tile list is cut into eight segments of
@@ -269,9 +267,10 @@ __device__ __forceinline__ int64_t claim_tile(unsigned long long *ctr, const int
 }
 
 template <int BM, int BN, int WM, int WN, int NST>
-__device__ __forceinline__ void grouped_tile(const GroupMember &d, int64_t local, uint8_t *lds) {
-    const int64_t tm = local / d.tiles_n, tn = local - tm * d.tiles_n;
-    const raw::Operands op{d.A, d.B, d.C, d.m, d.n, d.p, d.accumulate};
+__device__ __forceinline__ void grouped_tile(const GroupMember &g, int64_t local, uint8_t *lds) {
+    const int64_t tm = local / g.tiles_n, tn = local - tm * g.tiles_n;
+    const SplitItem &d = g.item;
+    const raw::Operands op{d.A, d.B, d.C, d.m, d.n, d.p, d.ld, d.accumulate};
     raw::block<BM, BN, WM, WN, NST, true, false>(op, __builtin_amdgcn_readfirstlane((int)tm) * (int64_t)BM,
                                                  __builtin_amdgcn_readfirstlane((int)tn) * (int64_t)BN, lds);
 }
@@ -296,6 +295,26 @@ __global__ __launch_bounds__(256, 2) void split_grouped_kernel(const GroupMember
         if (tile < 0) break;
         const int k = __builtin_amdgcn_readfirstlane(tile_owner[tile]);
         grouped_tile<BM, BN, WM, WN, NST>(g[k], tile - g[k].first_tile, lds);
+    }
+}
+
+// Sums of the split members' chunk partials: block b works on the last member
+// whose first_block is at most b, 1024 elements per block.
+constexpr int SUM_BLOCK = 1024;
+__global__ __launch_bounds__(256) void split_sums_kernel(const SplitSum *__restrict__ sums, int count) {
+    int k = 0;
+    while (k + 1 < count && sums[k + 1].first_block <= (int64_t)blockIdx.x) ++k;
+    const SplitSum d = sums[__builtin_amdgcn_readfirstlane(k)];
+    const int64_t x0 = ((int64_t)blockIdx.x - d.first_block) * SUM_BLOCK;
+    if (d.mp % 4 == 0 && (uintptr_t)d.C % 16 == 0) {
+        const int64_t x = x0 + threadIdx.x * 4;
+        if (x < d.mp) ring::splitk_sum<4>(d.partials, d.chunks, d.mp, x, d.C, 0, nullptr, d.accumulate);
+    } else {
+#pragma unroll
+        for (int e = 0; e < SUM_BLOCK / 256; ++e) {
+            const int64_t x = x0 + e * 256 + threadIdx.x;
+            if (x < d.mp) ring::splitk_sum<1>(d.partials, d.chunks, d.mp, x, d.C, 0, nullptr, d.accumulate);
+        }
     }
 }
 
@@ -345,7 +364,7 @@ constexpr RawBlock kRaw[] = {{64, 64, 130, 150}, {64, 128, 130, 240}, {128, 64, 
 template <int BM, int BN, int WM, int WN, int NST>
 hipError_t launch_raw(const moa_gemm_desc &d, hipStream_t st) {
     const raw::Operands op{static_cast<const float *>(d.A), static_cast<const float *>(d.B), static_cast<float *>(d.C),
-                           d.m, d.n, d.p, d.accumulate};
+                           d.m, d.n, d.p, d.n, d.accumulate};
     const int tiles_m = (int)((d.m + BM - 1) / BM), tiles_n = (int)((d.p + BN - 1) / BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n)), bl(256);
     const bool a_kc = !(d.flags & MOA_FLAG_A_COL), b_kc = (d.flags & MOA_FLAG_B_COL) != 0;
@@ -361,6 +380,32 @@ hipError_t launch_raw(const moa_gemm_desc &d, hipStream_t st) {
 }
 
 }  // namespace
+
+// Split-k without conditioning: 128 x 128 blocks, chunks summed in order.
+hipError_t launch_raw_splitk(const moa_gemm_desc &d, int chunks, float *partials, hipStream_t st) {
+    const raw::Operands op{static_cast<const float *>(d.A), static_cast<const float *>(d.B), static_cast<float *>(d.C),
+                           d.m, d.n, d.p, d.n, 0};
+    const int tiles_m = (int)((d.m + 127) / 128), tiles_n = (int)((d.p + 127) / 128);
+    const int S = (int)((d.n + SLAB - 1) / SLAB), per = (S + chunks - 1) / chunks;
+    const dim3 grid((unsigned)(tiles_m * tiles_n * chunks)), bl(256);
+    const bool a_kc = !(d.flags & MOA_FLAG_A_COL), b_kc = (d.flags & MOA_FLAG_B_COL) != 0;
+    if (a_kc && b_kc)
+        hipLaunchKernelGGL((raw::splitk_kernel<128, 128, 64, 64, 3, true, true>), grid, bl, 0, st, op, tiles_m, tiles_n,
+                           per, partials);
+    else if (a_kc)
+        hipLaunchKernelGGL((raw::splitk_kernel<128, 128, 64, 64, 3, true, false>), grid, bl, 0, st, op, tiles_m, tiles_n,
+                           per, partials);
+    else if (b_kc)
+        hipLaunchKernelGGL((raw::splitk_kernel<128, 128, 64, 64, 3, false, true>), grid, bl, 0, st, op, tiles_m, tiles_n,
+                           per, partials);
+    else
+        hipLaunchKernelGGL((raw::splitk_kernel<128, 128, 64, 64, 3, false, false>), grid, bl, 0, st, op, tiles_m, tiles_n,
+                           per, partials);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return ring::launch_splitk_reduce(partials, chunks, d.m, d.p, static_cast<float *>(d.C), nullptr, nullptr,
+                                      d.accumulate, st);
+}
 
 // The block a product takes without conditioning, -1 for the conditioned path:
 // the one whose busiest CU is done first, for products of at most three 128 x
@@ -387,6 +432,15 @@ int split_raw_block(const moa_gemm_desc &d) {
         }
     }
     return best;
+}
+
+// Split-k products: likewise, at most three 128 x 128 blocks per CU (512 x 32768
+// x 512 in 32 chunks: 73 us without, 119 with conditioning).
+bool split_raw_splitk(const moa_gemm_desc &d) {
+    const int64_t lim = 0x7FFFFFFF / 4;
+    const int64_t a = (d.flags & MOA_FLAG_A_COL) ? (raw::SLAB + 1) * d.m : (int64_t)129 * d.n;
+    const int64_t b = (d.flags & MOA_FLAG_B_COL) ? (int64_t)129 * d.n : (raw::SLAB + 1) * d.p;
+    return ((d.m + 127) / 128) * ((d.p + 127) / 128) <= 3 * kNumCUs && a < lim && b < lim && 9 * d.p < lim;
 }
 
 int split_bf16_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }
@@ -460,6 +514,9 @@ hipError_t launch_split_pack(const moa_gemm_desc &d, void *ws, hipStream_t st) {
 hipError_t launch_split_bf16(const moa_gemm_desc &d, const Plan &plan, void *ws, hipStream_t st) {
     if (plan.raw_block >= 0) {
         TraceScope ts(MOA_K_SPLIT_BF16, st);
+        if (plan.split_k > 1)
+            return launch_raw_splitk(d, plan.split_k,
+                                     reinterpret_cast<float *>(static_cast<char *>(ws) + plan.partial_offset), st);
         switch (plan.raw_block) {
         case 0: return launch_raw<64, 64, 32, 32, 4>(d, st);
         case 1: return launch_raw<64, 128, 32, 64, 3>(d, st);
@@ -511,22 +568,24 @@ constexpr GroupedKernel kGroupedK[] = {
 constexpr int kGroupedVariants = (int)(sizeof(kGroupedK) / sizeof(kGroupedK[0]));
 int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 
-int64_t member_tiles(const moa_gemm_desc &d, int bm, int bn) {
-    return ((d.m + bm - 1) / bm) * ((d.p + bn - 1) / bn);
-}
+int64_t item_tiles(const SplitItem &d, int bm, int bn) { return ((d.m + bm - 1) / bm) * ((d.p + bn - 1) / bn); }
+int64_t item_slabs(const SplitItem &d) { return (d.n + SLAB - 1) / SLAB; }
 
-// Contraction tiles of a member list under any variant (64 x 64 blocks: at
-// least as many as every block of the table), for sizing the tables.
-GroupedWork grouped_counts(const moa_gemm_desc *const *members, int count) {
-    GroupedWork w{0, 0, 0};
-    for (int k = 0; k < count; ++k) w.tiles += member_tiles(*members[k], 64, 64);
-    return w;
+// The table: items, then the nine segment bounds of the XCD claims (int64, 256
+// bytes), the sums of the split members, and the tile -> item table (int32),
+// sized for 64 x 64 blocks (at least as many tiles as every block of the list):
+// the part a launch uses is one prefix.
+struct TableAt { int64_t bounds, sums, owner, bytes; };
+TableAt table_at(const SplitGroup &g) {
+    TableAt t;
+    t.bounds = align256((int64_t)(g.items.size() * sizeof(GroupMember)));
+    t.sums = t.bounds + 256;
+    t.owner = t.sums + align256((int64_t)(g.sums.size() * sizeof(SplitSum)));
+    int64_t tiles = 0;
+    for (const SplitItem &d : g.items) tiles += item_tiles(d, 64, 64);
+    t.bytes = t.owner + align256(4 * tiles);
+    return t;
 }
-// Member table, then the nine segment bounds of the XCD claims (int64, 256
-// bytes), then the tile -> member table (int32): the part a launch uses is
-// one prefix of the table.
-int64_t members_bytes(int count) { return align256((int64_t)count * (int64_t)sizeof(GroupMember)); }
-int64_t table_bytes(int count, const GroupedWork &w) { return members_bytes(count) + 256 + align256(4 * w.tiles); }
 }  // namespace
 
 // The raw ring addresses a tile's rows of A with 32-bit offsets (128 rows of
@@ -535,36 +594,50 @@ bool split_grouped_fits(const moa_gemm_desc &d) {
     return ((int64_t)GB_M + 1) * d.n * 4 < 0x7FFFFFFF && ((int64_t)SLAB + 1) * d.p * 4 < 0x7FFFFFFF;
 }
 
-int64_t split_grouped_desc_bytes(const moa_gemm_desc *const *members, int count) {
-    return table_bytes(count, grouped_counts(members, count));
+void split_group_add(SplitGroup &g, const moa_gemm_desc &d, int split_k, float *partials) {
+    SplitItem it{static_cast<const float *>(d.A), static_cast<const float *>(d.B), static_cast<float *>(d.C),
+                 d.m, d.n, d.p, d.n, d.accumulate};
+    if (split_k <= 1) {
+        g.items.push_back(it);
+        return;
+    }
+    const int64_t S = (d.n + SLAB - 1) / SLAB, window = (S + split_k - 1) / split_k * SLAB;
+    for (int c = 0; c < split_k; ++c) {
+        const int64_t k0 = c * window;
+        it.A = static_cast<const float *>(d.A) + k0;
+        it.B = static_cast<const float *>(d.B) + k0 * d.p;
+        it.C = partials ? partials + (int64_t)c * d.m * d.p : nullptr;
+        it.n = std::min(window, d.n - k0);
+        it.accumulate = 0;
+        g.items.push_back(it);
+    }
+    g.sums.push_back({partials, static_cast<float *>(d.C), d.m * d.p, split_k, d.accumulate, 0});
 }
 
-int64_t split_grouped_workspace_bytes(const moa_gemm_desc *const *members, int count) {
-    return 256 + split_grouped_desc_bytes(members, count);
-}
+int64_t split_grouped_table_bytes(const SplitGroup &g) { return table_at(g).bytes; }
+
+int64_t split_grouped_workspace_bytes(const SplitGroup &g) { return 256 + split_grouped_table_bytes(g); }
 
 int split_grouped_variant_count() { return kGroupedVariants; }
 
 // Static rule. Short k walks (below 32 slabs): the block among 128 x 128, 64 x
-// 128 and 128 x 64 with the fewest slab steps over the members, weighted by the
+// 128 and 128 x 64 with the fewest slab steps over the items, weighted by the
 // time of a step. Longer ones: the block for which the CUs' share of the steps
 // plus the longest walk of one block is shortest, 64 x 64 among them -- a group
 // that leaves CUs idle is as slow as its longest walk (32 products 100 x 4000 x
 // 100: 115 us with 128 x 128 blocks, 95 with 64 x 128, 81 with 64 x 64; 64
 // products 512^3, which fill the CUs: 85, 106 and 134). Ties to the earlier
 // variant in the list; variant 0 is left to the autotuner.
-int split_grouped_default_variant(const moa_gemm_desc *const *members, int count) {
+int split_grouped_default_variant(const SplitGroup &g) {
     int64_t longest = 0;
-    for (int k = 0; k < count; ++k) longest = std::max(longest, (members[k]->n + SLAB - 1) / SLAB);
+    for (const SplitItem &d : g.items) longest = std::max(longest, item_slabs(d));
     int best = 2;
     double best_cost = 0;
     for (int v : {2, 3, 4, 1}) {
         if (v == 1 && longest < 32) continue;
         double cost = 0;
-        for (int k = 0; k < count; ++k) {
-            const moa_gemm_desc &d = *members[k];
-            cost += (double)member_tiles(d, kGroupedK[v].bm, kGroupedK[v].bn) * (double)((d.n + SLAB - 1) / SLAB);
-        }
+        for (const SplitItem &d : g.items)
+            cost += (double)item_tiles(d, kGroupedK[v].bm, kGroupedK[v].bn) * (double)item_slabs(d);
         cost *= kGroupedK[v].step_us;
         if (longest >= 32) cost = cost / kNumCUs + (double)longest * kGroupedK[v].alone_us;
         if (v == 2 || cost < best_cost) {
@@ -575,18 +648,16 @@ int split_grouped_default_variant(const moa_gemm_desc *const *members, int count
     return best;
 }
 
-// Lays out the members in `host_staging` for grouped kernel `variant`;
-// returns the tile count. Members are dealt, heaviest first (tiles x slab
-// steps), to the lightest of eight XCD segments; inside a segment they run
-// longest k walk first, so each segment's tail holds its cheapest tiles. The
-// device member array is at ws + 256, the claim counters at ws.
-GroupedWork split_grouped_layout(const moa_gemm_desc *const *members, int count, void *ws,
-                                 void *host_staging, int variant) {
-    (void)ws;
+// Lays out the items in `host_staging` for grouped kernel `variant`. Items are
+// dealt, heaviest first (tiles x slab steps), to the lightest of eight XCD
+// segments; inside a segment they run longest k walk first, so each segment's
+// tail holds its cheapest tiles. On the device the claim counters are at the
+// workspace's start and the table 256 bytes behind it.
+GroupedWork split_grouped_layout(const SplitGroup &g, void *host_staging, int variant) {
     const GroupedKernel gk = kGroupedK[variant];
+    const int count = (int)g.items.size();
     auto cost = [&](int k) {
-        const moa_gemm_desc &d = *members[k];
-        return (double)member_tiles(d, gk.bm, gk.bn) * (double)((d.n + SLAB - 1) / SLAB);
+        return (double)item_tiles(g.items[k], gk.bm, gk.bn) * (double)item_slabs(g.items[k]);
     };
     std::vector<int> heavy(count);
     for (int k = 0; k < count; ++k) heavy[k] = k;
@@ -604,73 +675,80 @@ GroupedWork split_grouped_layout(const moa_gemm_desc *const *members, int count,
     for (int k = 0; k < count; ++k) order[k] = k;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         if (seg_of[a] != seg_of[b]) return seg_of[a] < seg_of[b];
-        return members[a]->n > members[b]->n;
+        return g.items[a].n > g.items[b].n;
     });
+    const TableAt at = table_at(g);
     char *base = static_cast<char *>(host_staging);
     GroupMember *h = reinterpret_cast<GroupMember *>(base);
-    int32_t *tile_owner = reinterpret_cast<int32_t *>(base + members_bytes(count) + 256);
+    int32_t *tile_owner = reinterpret_cast<int32_t *>(base + at.owner);
     int64_t tiles = 0;
     int64_t bounds[9];
     int next_seg = 0;
     for (int q = 0; q < count; ++q) {
-        const moa_gemm_desc &d = *members[order[q]];
+        const SplitItem &d = g.items[order[q]];
         while (next_seg <= seg_of[order[q]]) bounds[next_seg++] = tiles;
-        GroupMember g{};
-        g.A = static_cast<const float *>(d.A);
-        g.B = static_cast<const float *>(d.B);
-        g.C = static_cast<float *>(d.C);
-        g.m = d.m; g.n = d.n; g.p = d.p;
-        g.S = (d.n + SLAB - 1) / SLAB;
-        g.first_tile = tiles;
-        g.tiles_n = (int32_t)((d.p + gk.bn - 1) / gk.bn);
-        g.accumulate = d.accumulate;
-        const int64_t mt = ((d.m + gk.bm - 1) / gk.bm) * g.tiles_n;
+        GroupMember m{};
+        m.item = d;
+        m.first_tile = tiles;
+        m.tiles_n = (int32_t)((d.p + gk.bn - 1) / gk.bn);
+        const int64_t mt = item_tiles(d, gk.bm, gk.bn);
         for (int64_t t = 0; t < mt; ++t) tile_owner[tiles + t] = q;
         tiles += mt;
-        h[q] = g;
+        h[q] = m;
     }
     while (next_seg <= 8) bounds[next_seg++] = tiles;
-    std::memcpy(base + members_bytes(count), bounds, sizeof(bounds));
-    return {tiles, 0, variant, members_bytes(count) + 256 + 4 * tiles};
+    std::memcpy(base + at.bounds, bounds, sizeof(bounds));
+    SplitSum *sums = reinterpret_cast<SplitSum *>(base + at.sums);
+    int64_t blocks = 0;
+    for (size_t k = 0; k < g.sums.size(); ++k) {
+        sums[k] = g.sums[k];
+        sums[k].first_block = blocks;
+        blocks += (g.sums[k].mp + SUM_BLOCK - 1) / SUM_BLOCK;
+    }
+    return {tiles, blocks, variant, at.owner + 4 * tiles};
 }
 
 namespace {
-// The persistent contraction of a grouped launch whose member table and
-// cleared claim counters are in place.
-hipError_t launch_persistent(void *ws, int count, const GroupedWork &work, hipStream_t st) {
-    const int64_t tiles = work.tiles;
+// The persistent contraction of a grouped launch whose table and cleared claim
+// counters are in place, and the sums of its split members.
+hipError_t launch_persistent(void *ws, const SplitGroup &g, const GroupedWork &work, hipStream_t st) {
+    const TableAt at = table_at(g);
     char *base = static_cast<char *>(ws);
     unsigned long long *counter = reinterpret_cast<unsigned long long *>(base);
     const GroupMember *dev_members = reinterpret_cast<const GroupMember *>(base + 256);
-    const int64_t *bounds = reinterpret_cast<const int64_t *>(base + 256 + members_bytes(count));
-    const int32_t *tile_owner = reinterpret_cast<const int32_t *>(base + 256 + members_bytes(count) + 256);
+    const int64_t *bounds = reinterpret_cast<const int64_t *>(base + 256 + at.bounds);
+    const int32_t *tile_owner = reinterpret_cast<const int32_t *>(base + 256 + at.owner);
     const int v = work.variant;
-    const int64_t grid = std::min<int64_t>(tiles, (int64_t)kGroupedK[v].occ * kNumCUs);   // resident blocks
+    const int64_t grid = std::min<int64_t>(work.tiles, (int64_t)kGroupedK[v].occ * kNumCUs);   // resident blocks
     TraceScope ts(MOA_K_SPLIT_GROUPED, st);
-    if (grid <= 0) return hipGetLastError();
-    const dim3 gr((unsigned)grid), bl(256);
-    switch (v) {
-    case 1:
-        hipLaunchKernelGGL((split_grouped_kernel<64, 64, 32, 32, 4>), gr, bl, 0, st, dev_members, tile_owner, bounds,
-                           counter);
-        break;
-    case 2:
-        hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
-                           counter);
-        break;
-    case 3:
-        hipLaunchKernelGGL((split_grouped_kernel<64, 128, 32, 64, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
-                           counter);
-        break;
-    case 4:
-        hipLaunchKernelGGL((split_grouped_kernel<128, 64, 64, 32, 3>), gr, bl, 0, st, dev_members, tile_owner, bounds,
-                           counter);
-        break;
-    default:
-        hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 5>), gr, bl, 0, st, dev_members, tile_owner, bounds,
-                           counter);
-        break;
+    if (grid > 0) {
+        const dim3 gr((unsigned)grid), bl(256);
+        switch (v) {
+        case 1:
+            hipLaunchKernelGGL((split_grouped_kernel<64, 64, 32, 32, 4>), gr, bl, 0, st, dev_members, tile_owner,
+                               bounds, counter);
+            break;
+        case 2:
+            hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 3>), gr, bl, 0, st, dev_members, tile_owner,
+                               bounds, counter);
+            break;
+        case 3:
+            hipLaunchKernelGGL((split_grouped_kernel<64, 128, 32, 64, 3>), gr, bl, 0, st, dev_members, tile_owner,
+                               bounds, counter);
+            break;
+        case 4:
+            hipLaunchKernelGGL((split_grouped_kernel<128, 64, 64, 32, 3>), gr, bl, 0, st, dev_members, tile_owner,
+                               bounds, counter);
+            break;
+        default:
+            hipLaunchKernelGGL((split_grouped_kernel<128, 128, 64, 64, 5>), gr, bl, 0, st, dev_members, tile_owner,
+                               bounds, counter);
+            break;
+        }
     }
+    if (work.sum_blocks > 0)
+        hipLaunchKernelGGL(split_sums_kernel, dim3((unsigned)work.sum_blocks), dim3(256), 0, st,
+                           reinterpret_cast<const SplitSum *>(base + 256 + at.sums), (int)g.sums.size());
     return hipGetLastError();
 }
 
@@ -686,31 +764,30 @@ __global__ __launch_bounds__(256) void stage_table_kernel(const uint4 *__restric
 }
 }  // namespace
 
-// The device part of a grouped launch whose member table is already on the
-// device: clear the claim counters, run the persistent contraction. Contains
-// no allocation, copy or memset, so it can be captured in a graph and
-// replayed.
-hipError_t split_grouped_enqueue(void *ws, int count, const GroupedWork &work, hipStream_t st) {
+// The device part of a grouped launch whose table is already on the device:
+// clear the claim counters, run the persistent contraction. Contains no
+// allocation, copy or memset, so it can be captured in a graph and replayed.
+hipError_t split_grouped_enqueue(void *ws, const SplitGroup &g, const GroupedWork &work, hipStream_t st) {
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, st, static_cast<unsigned long long *>(ws));
-    return launch_persistent(ws, count, work, st);
+    return launch_persistent(ws, g, work, st);
 }
 
-hipError_t launch_split_grouped(const moa_gemm_desc *const *members, int count, int variant, void *ws,
-                                void *host_staging, const void *host_staging_dev, hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    const GroupedWork work = split_grouped_layout(members, count, ws, host_staging, variant);
+hipError_t launch_split_grouped(const SplitGroup &g, int variant, void *ws, void *host_staging,
+                                const void *host_staging_dev, hipStream_t st) {
+    if (g.items.empty()) return hipSuccess;
+    const GroupedWork work = split_grouped_layout(g, host_staging, variant);
     char *base = static_cast<char *>(ws);
     if (!host_staging_dev) {
         hipError_t e = hipMemcpyAsync(base + 256, host_staging, (size_t)work.table_used, hipMemcpyHostToDevice, st);
         if (e != hipSuccess) return e;
-        return split_grouped_enqueue(ws, count, work, st);
+        return split_grouped_enqueue(ws, g, work, st);
     }
     const int64_t n16 = (work.table_used + 15) / 16;
     const int64_t blocks = std::min<int64_t>((n16 + 255) / 256, 64);
     hipLaunchKernelGGL(stage_table_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
                        static_cast<const uint4 *>(host_staging_dev), reinterpret_cast<uint4 *>(base + 256), n16,
                        reinterpret_cast<unsigned long long *>(base));
-    return launch_persistent(ws, count, work, st);
+    return launch_persistent(ws, g, work, st);
 }
 
 hipError_t launch_split_only(const float *X, int64_t count, uint16_t *hi, uint16_t *lo,

@@ -71,3 +71,44 @@ def test_every_block_of_the_rule(shape):
     rows = [0, m // 2, m - 1]
     R = O.gemm_f64(A[rows].cpu().numpy().astype(np.float64), B.cpu().numpy().astype(np.float64))
     assert O.rel_err(got[rows].cpu().numpy(), R) <= 1e-5
+
+
+@pytest.mark.parametrize("shape,chunks", [((1, 33, 1), 3), ((130, 1000, 67), 2), ((129, 4096, 257), 0), ((64, 20000, 64), 0),
+                                          ((300, 5003, 132), 7)])
+def test_split_k_layouts(shape, chunks):
+    """Chunks of the k walk, asked for or planned: the same partials and sums as the record ring's."""
+    m, n, p = shape
+    g = torch.Generator(device=DEV).manual_seed(n)
+    for a_col, b_col, c_col, acc in itertools.product((False, True), repeat=4):
+        A, B, C0 = operand(g, m, n, a_col), operand(g, n, p, b_col), operand(g, m, p, c_col)
+        out = []
+        for flags in (0, moa.MOA_FLAG_VARIANT(0)):
+            C = torch.empty_strided(C0.shape, C0.stride(), device=DEV)
+            C.copy_(C0 if acc else torch.full_like(C0, float("nan")))
+            moa.moa_gemm(A, B, C, path="split_bf16", accumulate=acc, flags=flags | moa.MOA_FLAG_SPLIT_K(chunks))
+            out.append(C)
+        assert torch.equal(out[0], out[1]), f"a_col {a_col}, b_col {b_col}, c_col {c_col}, accumulate {acc}"
+
+
+def test_grouped_split_k_members_share_the_launch():
+    """Members that split k (planned, asked for, ragged, accumulating), unsplit ones and an FP8 one that splits:
+    each bitwise as alone, whichever persistent kernel runs, twice in a row on the same scratch."""
+    members = [(96, 6000, 130, "split_bf16", 0, False), (300, 700, 200, "split_bf16", 0, False),
+               (65, 5003, 33, "split_bf16", moa.MOA_FLAG_SPLIT_K(9), True), (3, 4099, 7, "split_bf16", 0, True),
+               (128, 40, 64, "split_bf16", moa.MOA_FLAG_SPLIT_K(2), False), (96, 4500, 70, "fp8", 0, False)]
+    g = torch.Generator(device=DEV).manual_seed(2)
+    ops, descs = [], []
+    for m, n, p, path, flags, acc in members:
+        A, B, C0 = operand(g, m, n, False), operand(g, n, p, False), operand(g, m, p, False)
+        R = C0.clone()
+        moa.moa_gemm(A, B, R, path=path, accumulate=acc, flags=flags)
+        C = torch.empty_like(C0)
+        ops.append((A, B, C, C0, R))
+        descs.append(moa.make_desc(A, B, C, path=path, accumulate=acc, flags=flags))
+    assert moa.moa_grouped_plan_query(descs)["persistent_members"] == 5
+    for variant in (-1, *range(moa.MOA_GROUPED_VARIANTS), -1):
+        for _, _, C, C0, _ in ops:
+            C.copy_(C0)
+        moa.moa_gemm_grouped_variant(descs, variant)
+        for k, (_, _, C, _, R) in enumerate(ops):
+            assert torch.equal(C, R), f"variant {variant}, member {k}"
