@@ -13,12 +13,14 @@
 // The factor 2^-4 is the E8M0 block scale of the residual operand of the
 // scaled matrix-core step, so all three sums share one FP32 accumulator.
 //
-// Conditioning (HBM-bound): row exponents of A (one wave per row), column
-// amax of B (atomic max on the bit patterns of |x|, which order like
-// unsigned ints), then quantisation straight into record tiles (layout in
-// ring_gemm.h): record (r, s) holds the 64 codes of k = 64s .. 64s+63 of row r
-// of A, or of column r of B (B is transposed on the way). The two-term path
-// keeps the residual codes in a second record array per operand. The
+// Conditioning (HBM-bound), straight into record tiles (layout in ring_gemm.h):
+// record (r, s) holds the 64 codes of k = 64s .. 64s+63 of row r of A, or of
+// column r of B. Rows of up to 8192 values are conditioned in one pass, a wave
+// per row that holds the row in registers: amax, exponent, codes (longer rows:
+// exponents first, then codes). Columns take two: column amax (atomic max on
+// the bit patterns of |x|, which order like unsigned ints), then the codes,
+// transposed on the way. The two-term path keeps the residual codes in a second
+// record array per operand. The
 // contraction is the record-tile ring of ring_gemm.h with
 // v_mfma_scale_f32_32x32x64_f8f6f4 steps.
 #include <algorithm>
@@ -84,57 +86,132 @@ __global__ void fill_u32_kernel(uint32_t *x, int64_t count) {
     if (t < count) x[t] = 0u;
 }
 
-// One wave: e_i of row i of A from amax |A[i, :]| (all 64 lanes take part).
-__device__ __forceinline__ void row_exp_wave(const float *__restrict__ A, int64_t i, int64_t n, int vec,
-                                             int lane, int32_t *__restrict__ e) {
-    const float *row = A + i * n;
-    float mx = 0.0f;
-    if (vec) {
-        const float4 *r4 = reinterpret_cast<const float4 *>(row);
-#pragma unroll 8
-        for (int64_t k = lane; k < n / 4; k += 64) {
-            const float4 v = r4[k];
-            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-        }
-    } else {
-        for (int64_t k = lane; k < n; k += 64) mx = fmaxf(mx, fabsf(row[k]));
-    }
+__device__ __forceinline__ float amax4(const f32x4_t v) {
+    return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+__device__ __forceinline__ float wave_max(float mx) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) e[i] = pow2_exponent(mx);
+    return mx;
+}
+// Four values of a row from k on, zero past n.
+__device__ __forceinline__ f32x4_t row4(const float *__restrict__ row, int64_t k, int64_t n) {
+    if (k + 4 <= n) return load4(row + k);
+    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (k + t < n) v[t] = row[k + t];
+    return v;
 }
 
-// One wave per row of A.
-__global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ A, int64_t m, int64_t n,
-                                                      int vec, int32_t *__restrict__ e) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i < m) row_exp_wave(A, i, n, vec, threadIdx.x & 63, e);
-}
-
-// Column amax of B: one thread per column over a band of COL_BAND rows.
-constexpr int COL_BAND = 256;
-__device__ __forceinline__ void col_amax_thread(const float *__restrict__ B, int64_t n, int64_t p, int64_t j,
-                                                int64_t k0, uint32_t *__restrict__ amax) {
+// e_i of every row of A, one workgroup per row.
+__global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ A, int64_t n,
+                                                      int32_t *__restrict__ e) {
+    __shared__ float part[4];
+    const float *row = A + (int64_t)blockIdx.x * n;
     float mx = 0.0f;
-    const int64_t k1 = min(n, k0 + COL_BAND);
+#pragma unroll 8
+    for (int64_t k = (int64_t)threadIdx.x * 4; k < n; k += 1024) mx = fmaxf(mx, amax4(row4(row, k, n)));
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) e[blockIdx.x] = pow2_exponent(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
+}
+
+// Column amax of B: a workgroup takes 256 columns (four per lane) over a band
+// of COL_BAND rows, a quarter of the band per wave, and adds one atomic per
+// column. HBM-bound when its loads are 16 bytes and many are in flight; with one
+// column per lane and a launch to clear first it took 42 us at 4096 x 8192.
+constexpr int COL_BAND = 256;
+__device__ __forceinline__ void col_amax_block(const float *__restrict__ B, int64_t n, int64_t p, int64_t bx,
+                                               int64_t by, uint32_t *__restrict__ amax, float (*part)[256]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t j = bx * 256 + lane * 4;
+    const int64_t k0 = by * COL_BAND + wave * (COL_BAND / 4), k1 = min(n, k0 + COL_BAND / 4);
+    f32x4_t mx = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (j + 4 <= p) {
 #pragma unroll 16
-    for (int64_t k = k0; k < k1; ++k) mx = fmaxf(mx, fabsf(B[k * p + j]));
-    atomicMax(&amax[j], __float_as_uint(mx));
+        for (int64_t k = k0; k < k1; ++k) {
+            const f32x4_t v = load4(B + k * p + j);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mx[t] = fmaxf(mx[t], fabsf(v[t]));
+        }
+    } else {
+        for (int64_t k = k0; k < k1; ++k)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (j + t < p) mx[t] = fmaxf(mx[t], fabsf(B[k * p + j + t]));
+    }
+    __syncthreads();                               // earlier readers of `part` are done
+    *reinterpret_cast<f32x4_t *>(&part[wave][lane * 4]) = mx;
+    __syncthreads();
+    const int c = threadIdx.x;
+    const float m = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+    if (bx * 256 + c < p) atomicMax(&amax[bx * 256 + c], __float_as_uint(m));
 }
 
 __global__ __launch_bounds__(256) void col_amax_kernel(const float *__restrict__ B, int64_t n,
                                                        int64_t p, uint32_t *__restrict__ amax) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j < p) col_amax_thread(B, n, p, j, (int64_t)blockIdx.y * COL_BAND, amax);
+    __shared__ __attribute__((aligned(16))) float part[4][256];
+    col_amax_block(B, n, p, blockIdx.x, blockIdx.y, amax, part);
 }
 
 // --------------------------------------------------- record conditioning --
 
-// Rows of A -> records. Chunk q = 16 codes of one record (4 per record);
-// consecutive chunks fill one KiB record tile contiguously.
+// One wave: row i of A (rows past m up to the padded end: zeros) held in
+// registers, J x 256 values; exponent, then the codes as one dword per four
+// values, 16 lanes filling a record. n <= 256 J. One read of the operand and one
+// launch in place of two each; all of a lane's loads are in flight together, at
+// any 4-byte alignment (3001 x 2777 rows: exponents and codes were 15 + 13.5 us
+// with scalar loads for the odd length, the product of two such operands, one
+// term, 99 us and now 54).
+template <bool TWO, int J>
+__device__ __forceinline__ void condition_row(const float *__restrict__ A, int64_t i, int64_t m, int64_t n, int64_t S,
+                                              int lane, int32_t *__restrict__ e, uint8_t *__restrict__ qa,
+                                              uint8_t *__restrict__ la) {
+    f32x4_t x[J];
+    float mx = 0.0f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        x[j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (i < m && 256 * j < n) x[j] = row4(A + i * n, 256 * j + 4 * lane, n);
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) mx = fmaxf(mx, amax4(x[j]));
+    const int ei = pow2_exponent(wave_max(mx));
+    if (lane == 0 && i < m) e[i] = ei;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int64_t s = 4 * j + (lane >> 4);
+        if (s >= S) continue;
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = ldexpf(x[j][t], ei);
+        uint32_t hi, lo = 0u;
+        quant4(v, TWO, &hi, &lo);
+        const int64_t at = ring::rec_byte(i, s, S) + 4 * (lane & 15);
+        *reinterpret_cast<uint32_t *>(qa + at) = hi;
+        if (TWO) *reinterpret_cast<uint32_t *>(la + at) = lo;
+    }
+}
+
+// Four rows per workgroup; clears `count` words at `clear` on the way (the
+// column amax of the other operand).
+template <bool TWO, int J>
+__global__ __launch_bounds__(256) void rows_fp8_kernel(const float *__restrict__ A, int64_t m, int64_t n, int64_t S,
+                                                       int32_t *__restrict__ e, uint8_t *__restrict__ qa,
+                                                       uint8_t *__restrict__ la, uint32_t *__restrict__ clear,
+                                                       int64_t count) {
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < count; t += (int64_t)gridDim.x * 256) clear[t] = 0u;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i < padded_rows(m)) condition_row<TWO, J>(A, i, m, n, S, threadIdx.x & 63, e, qa, la);
+}
+
+// Rows of A -> records, exponents given. Chunk q = 16 codes of one record (4
+// per record); consecutive chunks fill one KiB record tile contiguously.
 template <bool TWO>
 __device__ __forceinline__ void pack_rows_fp8_chunk(const float *__restrict__ A, int64_t m, int64_t n,
-                                                    int64_t S, int vec, const int32_t *__restrict__ e,
+                                                    int64_t S, const int32_t *__restrict__ e,
                                                     uint8_t *__restrict__ qa, uint8_t *__restrict__ la,
                                                     int64_t q) {
     const int c = (int)(q & 3);
@@ -143,29 +220,17 @@ __device__ __forceinline__ void pack_rows_fp8_chunk(const float *__restrict__ A,
     const int64_t s = gs % S, g = gs / S;
     const int64_t r = g * GROUP + rr;
     const int64_t k = s * SLAB8 + c * 16;
-    float x[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) x[t] = 0.0f;
-    if (r < m) {
-        const float *src = A + r * n + k;
-        if (vec && k + 16 <= n) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float4 v = reinterpret_cast<const float4 *>(src)[u];
-                x[4 * u] = v.x; x[4 * u + 1] = v.y; x[4 * u + 2] = v.z; x[4 * u + 3] = v.w;
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < 16; ++t)
-                if (k + t < n) x[t] = src[t];
-        }
-        const int er = e[r];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) x[t] = ldexpf(x[t], er);
-    }
     uint32_t hi[4], lo[4] = {0u, 0u, 0u, 0u};
+    const int er = r < m ? e[r] : 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) quant4(x + 4 * u, TWO, &hi[u], &lo[u]);
+    for (int u = 0; u < 4; ++u) {
+        f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (r < m) x = row4(A + r * n, k + 4 * u, n);
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = ldexpf(x[t], er);
+        quant4(v, TWO, &hi[u], &lo[u]);
+    }
     const int64_t at = ring::rec_byte(r, s, S) + c * 16;
     *reinterpret_cast<uint4 *>(qa + at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     if (TWO) *reinterpret_cast<uint4 *>(la + at) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
@@ -173,13 +238,13 @@ __device__ __forceinline__ void pack_rows_fp8_chunk(const float *__restrict__ A,
 
 template <bool TWO>
 __global__ __launch_bounds__(256) void pack_rows_fp8_kernel(const float *__restrict__ A, int64_t m,
-                                                            int64_t n, int64_t S, int vec,
+                                                            int64_t n, int64_t S,
                                                             const int32_t *__restrict__ e,
                                                             uint8_t *__restrict__ qa,
                                                             uint8_t *__restrict__ la) {
     const int64_t chunks = padded_rows(m) * S * 4;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < chunks; q += (int64_t)gridDim.x * 256)
-        pack_rows_fp8_chunk<TWO>(A, m, n, S, vec, e, qa, la, q);
+        pack_rows_fp8_chunk<TWO>(A, m, n, S, e, qa, la, q);
 }
 
 // Columns of B -> records (transposed), 64 columns x one slab (64 k) per
@@ -210,7 +275,7 @@ __device__ __forceinline__ void write_col_exps(const uint32_t *__restrict__ amax
 // take part; the LDS tiles are free again when it returns.
 template <bool TWO>
 __device__ __forceinline__ void pack_cols_fp8_block(const float *__restrict__ B, int64_t n, int64_t p,
-                                                    int64_t S, int vec, const uint32_t *__restrict__ amax,
+                                                    int64_t S, const uint32_t *__restrict__ amax,
                                                     uint8_t *__restrict__ qb, uint8_t *__restrict__ lb,
                                                     int64_t bx, int64_t s, uint32_t *tq, uint32_t *tl) {
     const int t = threadIdx.x;
@@ -227,14 +292,9 @@ __device__ __forceinline__ void pack_cols_fp8_block(const float *__restrict__ B,
         float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if (k < n) {
             const float *row = B + k * p + j;
-            if (vec && j + 4 <= p) {
-                const float4 x = *reinterpret_cast<const float4 *>(row);
-                v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-            } else {
+            const f32x4_t x = row4(row, 0, p - j);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (j + u < p) v[u] = row[u];
-            }
+            for (int u = 0; u < 4; ++u) v[u] = x[u];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = ldexpf(v[u], fcol[u]);
@@ -261,7 +321,7 @@ __device__ __forceinline__ void pack_cols_fp8_block(const float *__restrict__ B,
 
 template <bool TWO>
 __global__ __launch_bounds__(256) void pack_cols_fp8_kernel(const float *__restrict__ B, int64_t n,
-                                                            int64_t p, int64_t S, int vec,
+                                                            int64_t p, int64_t S,
                                                             const uint32_t *__restrict__ amax,
                                                             int32_t *__restrict__ f_out,
                                                             uint8_t *__restrict__ qb,
@@ -270,7 +330,7 @@ __global__ __launch_bounds__(256) void pack_cols_fp8_kernel(const float *__restr
     __shared__ uint32_t tl[TWO ? 64 * TSTRIDE : 1];
     if (blockIdx.y == 0) write_col_exps(amax, p, blockIdx.x, f_out);
     for (int64_t s = blockIdx.y; s < S; s += gridDim.y)
-        pack_cols_fp8_block<TWO>(B, n, p, S, vec, amax, qb, lb, blockIdx.x, s, tq, tl);
+        pack_cols_fp8_block<TWO>(B, n, p, S, amax, qb, lb, blockIdx.x, s, tq, tl);
 }
 
 // ------------------------------------------- row-major codes (exposed API) --
@@ -393,10 +453,10 @@ template <bool TWO> struct Fp8Mode {
 
 // ------------------------------------------------ grouped (persistent) --
 // Independent FP8 products of one term count share one launch sequence:
-// clear (claim counter + every member's column amax), scales (row exponents
-// and column amax of every member), records (every member's rows and column
+// clear (claim counter + every member's column amax), rows (every member's rows,
+// exponents and records, and its column amax), columns (every member's column
 // blocks), contraction (persistent workgroups claim tiles of all members from
-// one counter). The scale and record steps each walk one work list over all
+// one counter). The row and column steps each walk one work list over all
 // members, so large and small members share the machine evenly. Every element
 // sees the operation sequence of the single-product path, so results are
 // bitwise those of moa_gemm.
@@ -408,14 +468,12 @@ struct Fp8Member {
     uint32_t *amaxB;                    // column amax (bit patterns)
     int64_t m, n, p, S;
     int64_t first_tile;                 // first contraction work-list id
-    int64_t scale_first;                // first scale work-list id
-    int64_t pack_first;                 // first record work-list id
+    int64_t row_first;                  // first row work-list id
+    int64_t col_first;                  // first column work-list id
     int32_t tiles_n, reserved;
-    int32_t row_items;                  // scale items: row_items (4 rows each), then
+    int32_t row_items;                  // row items: row_items (4 rows each), then
     int32_t col_amax_x;                 //   col_amax_x * ceil(n / COL_BAND) column bands
-    int32_t pack_row_items;             // record items: pack_row_items (256 chunks each), then
-    int32_t pack_col_x;                 //   pack_col_x * max(S, 1) 64-column blocks
-    int32_t vec_a, vec_b;
+    int32_t col_x;                      // column items: col_x * max(S, 1) 64-column blocks
 };
 
 template <int64_t Fp8Member::*F>
@@ -428,43 +486,62 @@ __device__ __forceinline__ int find_member(const Fp8Member *__restrict__ g, int 
     return lo;
 }
 
-__global__ __launch_bounds__(256) void grouped_scales_kernel(const Fp8Member *__restrict__ g, int count,
-                                                             int64_t total) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-        const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::scale_first>(g, count, item));
-        const Fp8Member &d = g[k];
-        const int64_t local = item - d.scale_first;
-        if (local < d.row_items) {
-            const int64_t i = local * 4 + wave;
-            if (i < d.m) row_exp_wave(d.A, i, d.n, d.vec_a, lane, d.e);
-        } else {
-            const int64_t b = local - d.row_items;
-            const int64_t j = (b % d.col_amax_x) * 256 + threadIdx.x;
-            if (j < d.p) col_amax_thread(d.B, d.n, d.p, j, (b / d.col_amax_x) * COL_BAND, d.amaxB);
-        }
+// A row of any length by one wave: in registers up to 4096 values (the kernel
+// keeps four workgroups a CU), else in two passes over memory.
+template <bool TWO>
+__device__ __forceinline__ void condition_any_row(const Fp8Member &d, int64_t i, int lane) {
+    if (d.n <= 1024) return condition_row<TWO, 4>(d.A, i, d.m, d.n, d.S, lane, d.e, d.qa, d.la);
+    if (d.n <= 4096) return condition_row<TWO, 16>(d.A, i, d.m, d.n, d.S, lane, d.e, d.qa, d.la);
+    const float *row = d.A + i * d.n;
+    float mx = 0.0f;
+    if (i < d.m)
+#pragma unroll 8
+        for (int64_t k = 4 * lane; k < d.n; k += 256) mx = fmaxf(mx, amax4(row4(row, k, d.n)));
+    const int ei = pow2_exponent(wave_max(mx));
+    if (lane == 0 && i < d.m) d.e[i] = ei;
+    for (int64_t k = 4 * lane; k < d.S * SLAB8; k += 256) {
+        f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (i < d.m) x = row4(row, k, d.n);
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = ldexpf(x[t], ei);
+        uint32_t hi, lo = 0u;
+        quant4(v, TWO, &hi, &lo);
+        const int64_t at = ring::rec_byte(i, k / SLAB8, d.S) + k % SLAB8;
+        *reinterpret_cast<uint32_t *>(d.qa + at) = hi;
+        if (TWO) *reinterpret_cast<uint32_t *>(d.la + at) = lo;
+    }
+}
+
+// One item per workgroup: in a loop over items the compiler spills the row.
+template <bool TWO>
+__global__ __launch_bounds__(256) void grouped_rows_kernel(const Fp8Member *__restrict__ g, int count, int64_t total) {
+    __shared__ __attribute__((aligned(16))) float part[4][256];
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (item >= total) return;
+    const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::row_first>(g, count, item));
+    const Fp8Member &d = g[k];
+    const int64_t local = item - d.row_first;
+    if (local < d.row_items) {
+        const int64_t i = local * 4 + (threadIdx.x >> 6);
+        if (i < padded_rows(d.m)) condition_any_row<TWO>(d, i, threadIdx.x & 63);
+    } else {
+        const int64_t b = local - d.row_items;
+        col_amax_block(d.B, d.n, d.p, b % d.col_amax_x, b / d.col_amax_x, d.amaxB, part);
     }
 }
 
 template <bool TWO>
-__global__ __launch_bounds__(256) void grouped_records_kernel(const Fp8Member *__restrict__ g, int count,
-                                                              int64_t total) {
+__global__ __launch_bounds__(256) void grouped_cols_kernel(const Fp8Member *__restrict__ g, int count, int64_t total) {
     __shared__ uint32_t tq[64 * TSTRIDE];
     __shared__ uint32_t tl[TWO ? 64 * TSTRIDE : 1];
     for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-        const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::pack_first>(g, count, item));
+        const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::col_first>(g, count, item));
         const Fp8Member &d = g[k];
-        const int64_t local = item - d.pack_first;
-        if (local < d.pack_row_items) {
-            const int64_t q = local * 256 + threadIdx.x;
-            if (q < padded_rows(d.m) * d.S * 4)
-                pack_rows_fp8_chunk<TWO>(d.A, d.m, d.n, d.S, d.vec_a, d.e, d.qa, d.la, q);
-        } else {
-            const int64_t b = local - d.pack_row_items;
-            const int64_t bx = b % d.pack_col_x, s = b / d.pack_col_x;
-            if (s == 0) write_col_exps(d.amaxB, d.p, bx, d.f);
-            if (s < d.S) pack_cols_fp8_block<TWO>(d.B, d.n, d.p, d.S, d.vec_b, d.amaxB, d.qb, d.lb, bx, s, tq, tl);
-        }
+        const int64_t b = item - d.col_first;
+        const int64_t bx = b % d.col_x, s = b / d.col_x;
+        if (s == 0) write_col_exps(d.amaxB, d.p, bx, d.f);
+        if (s < d.S) pack_cols_fp8_block<TWO>(d.B, d.n, d.p, d.S, d.amaxB, d.qb, d.lb, bx, s, tq, tl);
     }
 }
 
@@ -543,61 +620,73 @@ Fp8Workspace carve(void *ws, int64_t m, int64_t n, int64_t p, bool two) {
     return w;
 }
 
-// Exponents of A's rows and amax of B's columns (shared by both layouts).
+// Exponents of A's rows and amax of B's columns.
 void scales(const float *A, int64_t m, int64_t n, const float *B, int64_t p, int32_t *e, uint32_t *amaxB,
             hipStream_t st) {
     if (p > 0) hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((p + 255) / 256)), dim3(256), 0, st, amaxB, p);
-    const int vec = (n % 4 == 0) && ((uintptr_t)A % 16 == 0);
-    if (m > 0) hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, A, m, n, vec, e);
+    if (m > 0) hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)m), dim3(256), 0, st, A, n, e);
     if (p > 0 && n > 0)
         hipLaunchKernelGGL(col_amax_kernel, dim3((unsigned)((p + 255) / 256), (unsigned)((n + COL_BAND - 1) / COL_BAND)),
                            dim3(256), 0, st, B, n, p, amaxB);
 }
 
-// Exponents and records of one operand. A "row operand" is consumed row by
-// row (A's rows: exponents e); a "column operand" column by column (B's
-// columns: exponents f). `X` is row-major; `by_rows` says whether the wanted
-// vectors are its rows (X is rows x K) or its columns (X is K x rows).
-void operand_records(const float *X, int64_t rows, int64_t K, int64_t S, bool by_rows, bool two, uint32_t *amax,
-                     int32_t *exps, uint8_t *q, uint8_t *l, hipStream_t st) {
-    if (rows == 0) return;
-    if (by_rows) {
-        const int vec = (K % 4 == 0) && ((uintptr_t)X % 16 == 0);
-        hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, X, rows, K, vec, exps);
-        if (S > 0) {
-            int64_t blocks = (padded_rows(rows) * S * 4 + 255) / 256;
-            if (blocks > 65536) blocks = 65536;
-            if (two)
-                hipLaunchKernelGGL(pack_rows_fp8_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, X, rows, K,
-                                   S, vec, exps, q, l);
-            else
-                hipLaunchKernelGGL(pack_rows_fp8_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, X, rows, K,
-                                   S, vec, exps, q, l);
-        }
-        return;
+// Exponents and records of one operand whose wanted vectors are the rows of X
+// (rows x K): A's rows, or a column-major B's columns. Clears `count` words at
+// `clear` on the way. The smallest J that holds a row: registers (28, 42, 74 and
+// 138) set the waves per SIMD. Beyond 8192 values a row would leave one wave
+// per SIMD, and two passes with a workgroup per row do better.
+template <bool TWO>
+void row_records(const float *X, int64_t rows, int64_t K, int64_t S, int32_t *exps, uint8_t *q, uint8_t *l,
+                 uint32_t *clear, int64_t count, hipStream_t st) {
+    const dim3 grid((unsigned)((padded_rows(rows) + 3) / 4)), bl(256);
+    if (K <= 1024) {
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 4>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+    } else if (K <= 2048) {
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 8>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+    } else if (K <= 4096) {
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 16>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+    } else if (K <= 8192) {
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 32>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+    } else {
+        if (count > 0)
+            hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((count + 255) / 256)), bl, 0, st, clear, count);
+        hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)rows), bl, 0, st, X, K, exps);
+        const int64_t blocks = std::min<int64_t>((padded_rows(rows) * S * 4 + 255) / 256, 65536);
+        hipLaunchKernelGGL(pack_rows_fp8_kernel<TWO>, dim3((unsigned)blocks), bl, 0, st, X, rows, K, S, exps, q, l);
     }
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, amax, rows);
+}
+
+// The same where they are the columns of X (K x cols); `amax` holds zeros.
+template <bool TWO>
+void col_records(const float *X, int64_t cols, int64_t K, int64_t S, uint32_t *amax, int32_t *exps, uint8_t *q,
+                 uint8_t *l, hipStream_t st) {
     if (K > 0)
-        hipLaunchKernelGGL(col_amax_kernel, dim3((unsigned)((rows + 255) / 256), (unsigned)((K + COL_BAND - 1) / COL_BAND)),
-                           dim3(256), 0, st, X, K, rows, amax);
+        hipLaunchKernelGGL(col_amax_kernel, dim3((unsigned)((cols + 255) / 256), (unsigned)((K + COL_BAND - 1) / COL_BAND)),
+                           dim3(256), 0, st, X, K, cols, amax);
     // also when S == 0: the epilogue reads the exponents
-    const int vec = (rows % 4 == 0) && ((uintptr_t)X % 16 == 0);
-    const dim3 grid((unsigned)((rows + 63) / 64), (unsigned)(S < 1 ? 1 : S > 65535 ? 65535 : S));
-    if (two)
-        hipLaunchKernelGGL(pack_cols_fp8_kernel<true>, grid, dim3(256), 0, st, X, K, rows, S, vec, amax, exps, q, l);
-    else
-        hipLaunchKernelGGL(pack_cols_fp8_kernel<false>, grid, dim3(256), 0, st, X, K, rows, S, vec, amax, exps, q, l);
+    const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)(S < 1 ? 1 : S > 65535 ? 65535 : S));
+    hipLaunchKernelGGL(pack_cols_fp8_kernel<TWO>, grid, dim3(256), 0, st, X, K, cols, S, amax, exps, q, l);
 }
 
 // A column-major A (element (i, k) at i + k m) is a row-major n x m array
 // whose columns are A's rows; a column-major B is a row-major p x n array
-// whose rows are B's columns.
-hipError_t pack_records(const moa_gemm_desc &d, bool two, const Fp8Workspace &w, hipStream_t st) {
+// whose rows are B's columns. An operand taken by rows goes first and clears
+// the other's column amax; two taken by columns share one clear (their amax
+// arrays are neighbours in the workspace).
+template <bool TWO>
+hipError_t pack_records(const moa_gemm_desc &d, const Fp8Workspace &w, hipStream_t st) {
     const float *A = static_cast<const float *>(d.A);
     const float *B = static_cast<const float *>(d.B);
     const int64_t S = (d.n + SLAB8 - 1) / SLAB8;
-    operand_records(A, d.m, d.n, S, !(d.flags & MOA_FLAG_A_COL), two, w.amaxA, w.e, w.qA, w.lA, st);
-    operand_records(B, d.p, d.n, S, (d.flags & MOA_FLAG_B_COL) != 0, two, w.amaxB, w.f, w.qB, w.lB, st);
+    const bool a_rows = !(d.flags & MOA_FLAG_A_COL), b_rows = (d.flags & MOA_FLAG_B_COL) != 0;
+    if (!a_rows && !b_rows) {
+        const int64_t words = align256(4 * d.p) / 4 + d.m;
+        hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, w.amaxB, words);
+    }
+    if (a_rows) row_records<TWO>(A, d.m, d.n, S, w.e, w.qA, w.lA, w.amaxB, b_rows ? 0 : d.p, st);
+    if (b_rows) row_records<TWO>(B, d.p, d.n, S, w.f, w.qB, w.lB, w.amaxA, a_rows ? 0 : d.m, st);
+    if (!a_rows) col_records<TWO>(A, d.m, d.n, S, w.amaxA, w.e, w.qA, w.lA, st);
+    if (!b_rows) col_records<TWO>(B, d.p, d.n, S, w.amaxB, w.f, w.qB, w.lB, st);
     return hipGetLastError();
 }
 
@@ -630,7 +719,7 @@ hipError_t launch_fp8(const moa_gemm_desc &d, const Plan &plan, void *ws, hipStr
     hipError_t err;
     {
         TraceScope ts(MOA_K_FP8_QUANT, st);
-        err = pack_records(d, two, w, st);
+        err = two ? pack_records<true>(d, w, st) : pack_records<false>(d, w, st);
     }
     if (err != hipSuccess) return err;
     TraceScope ts(two ? MOA_K_FP8_2TERM : MOA_K_FP8, st);
@@ -725,39 +814,40 @@ Fp8GroupWork fp8_grouped_layout(const moa_gemm_desc *const *members, int count, 
         g.op.col_exp = g.f;
         g.op.m = d.m; g.op.p = d.p; g.op.S = g.S;
         g.op.accumulate = d.accumulate;
-        g.vec_a = (d.n % 4 == 0) && ((uintptr_t)d.A % 16 == 0);
-        g.vec_b = (d.p % 4 == 0) && ((uintptr_t)d.B % 16 == 0);
         g.tiles_n = (int32_t)((d.p + G_BN - 1) / G_BN);
         g.first_tile = w.tiles;
         w.tiles += ((d.m + G_BM - 1) / G_BM) * g.tiles_n;
-        g.row_items = (int32_t)((d.m + 3) / 4);
+        g.row_items = (int32_t)(padded_rows(d.m) / 4);
         g.col_amax_x = (int32_t)((d.p + 255) / 256);
-        g.scale_first = w.scale_items;
-        w.scale_items += g.row_items + (int64_t)g.col_amax_x * ((d.n + COL_BAND - 1) / COL_BAND);
-        g.pack_row_items = (int32_t)((padded_rows(d.m) * g.S * 4 + 255) / 256);
-        g.pack_col_x = (int32_t)((d.p + 63) / 64);
-        g.pack_first = w.pack_items;
-        w.pack_items += g.pack_row_items + (int64_t)g.pack_col_x * (g.S > 0 ? g.S : 1);
+        g.row_first = w.row_items;
+        w.row_items += g.row_items + (int64_t)g.col_amax_x * ((d.n + COL_BAND - 1) / COL_BAND);
+        g.col_x = (int32_t)((d.p + 63) / 64);
+        g.col_first = w.col_items;
+        w.col_items += (int64_t)g.col_x * (g.S > 0 ? g.S : 1);
         h[q] = g;
     }
     return w;
 }
 
-hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork &w, hipStream_t st) {
+hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork &w, bool cleared, hipStream_t st) {
     char *base = static_cast<char *>(ws);
     unsigned long long *counter = reinterpret_cast<unsigned long long *>(base);
     const Fp8Member *dev = reinterpret_cast<const Fp8Member *>(base + w.table_offset);
     {
         TraceScope ts(MOA_K_FP8_QUANT, st);
-        hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((w.clear_words + 255) / 256)), dim3(256), 0, st,
-                           reinterpret_cast<uint32_t *>(base), w.clear_words);
-        if (w.scale_items > 0)
-            hipLaunchKernelGGL(grouped_scales_kernel, dim3((unsigned)std::min<int64_t>(w.scale_items, 8 * kNumCUs)),
-                               dim3(256), 0, st, dev, count, w.scale_items);
-        if (w.pack_items > 0) {
-            const dim3 grid((unsigned)std::min<int64_t>(w.pack_items, 8 * kNumCUs));
-            if (two) hipLaunchKernelGGL(grouped_records_kernel<true>, grid, dim3(256), 0, st, dev, count, w.pack_items);
-            else hipLaunchKernelGGL(grouped_records_kernel<false>, grid, dim3(256), 0, st, dev, count, w.pack_items);
+        if (!cleared)
+            hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((w.clear_words + 255) / 256)), dim3(256), 0, st,
+                               reinterpret_cast<uint32_t *>(base), w.clear_words);
+        if (w.row_items > 0) {
+            const int64_t wide = std::min<int64_t>(w.row_items, 1 << 20);
+            const dim3 grid((unsigned)wide, (unsigned)((w.row_items + wide - 1) / wide));
+            if (two) hipLaunchKernelGGL(grouped_rows_kernel<true>, grid, dim3(256), 0, st, dev, count, w.row_items);
+            else hipLaunchKernelGGL(grouped_rows_kernel<false>, grid, dim3(256), 0, st, dev, count, w.row_items);
+        }
+        if (w.col_items > 0) {
+            const dim3 grid((unsigned)std::min<int64_t>(w.col_items, 8 * kNumCUs));
+            if (two) hipLaunchKernelGGL(grouped_cols_kernel<true>, grid, dim3(256), 0, st, dev, count, w.col_items);
+            else hipLaunchKernelGGL(grouped_cols_kernel<false>, grid, dim3(256), 0, st, dev, count, w.col_items);
         }
     }
     TraceScope ts(MOA_K_FP8_GROUPED, st);
@@ -781,12 +871,15 @@ hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork
 
 namespace {
 // The member table straight from pinned host memory mapped into the device's
-// address space (n16 16-byte words): a kernel in place of a copy-engine
-// transfer and its hand-offs to and from the compute queue.
+// address space (n16 16-byte words), and the clear of the claim counter and the
+// column amax: one kernel in place of a copy-engine transfer and its hand-offs
+// to and from the compute queue.
 __global__ __launch_bounds__(256) void table_from_host_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst,
-                                                              int64_t n16) {
+                                                              int64_t n16, uint32_t *__restrict__ clear,
+                                                              int64_t words) {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += stride) clear[i] = 0u;
 }
 }  // namespace
 
@@ -798,14 +891,15 @@ hipError_t launch_fp8_grouped(const moa_gemm_desc *const *members, int count, bo
     const int64_t bytes = fp8_grouped_desc_bytes(count);
     if (host_staging_dev) {
         const int64_t n16 = (bytes + 15) / 16;
-        hipLaunchKernelGGL(table_from_host_kernel, dim3((unsigned)std::min<int64_t>((n16 + 255) / 256, 64)),
-                           dim3(256), 0, st, static_cast<const uint4 *>(host_staging_dev),
-                           reinterpret_cast<uint4 *>(table), n16);
-    } else {
-        hipError_t e = hipMemcpyAsync(table, host_staging, (size_t)bytes, hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) return e;
+        const int64_t blocks = std::min<int64_t>((std::max(n16, w.clear_words) + 255) / 256, 64);
+        hipLaunchKernelGGL(table_from_host_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
+                           static_cast<const uint4 *>(host_staging_dev), reinterpret_cast<uint4 *>(table), n16,
+                           static_cast<uint32_t *>(ws), w.clear_words);
+        return fp8_grouped_enqueue(ws, count, two, w, true, st);
     }
-    return fp8_grouped_enqueue(ws, count, two, w, st);
+    hipError_t e = hipMemcpyAsync(table, host_staging, (size_t)bytes, hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return e;
+    return fp8_grouped_enqueue(ws, count, two, w, false, st);
 }
 
 hipError_t launch_quantise_fp8(const float *A, int64_t m, int64_t n, const float *B, int64_t p,

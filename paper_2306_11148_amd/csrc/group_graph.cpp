@@ -136,7 +136,7 @@ moa_status moa_group_create(const moa_gemm_desc *descs, int64_t count, moa_group
         e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess && cnt > 0) e = split_grouped_enqueue(g->ws, items, work, cs);
         for (int two = 0; two < 2 && e == hipSuccess; ++two)
-            if (!fp8[two].empty()) e = fp8_grouped_enqueue(g->ws8[two], (int)fp8[two].size(), two != 0, work8[two], cs);
+            if (!fp8[two].empty()) e = fp8_grouped_enqueue(g->ws8[two], (int)fp8[two].size(), two != 0, work8[two], false, cs);
         moa_status rs = MOA_OK;
         for (size_t k = 0; e == hipSuccess && rs == MOA_OK && k < single.size(); ++k)
             rs = run_gemm(single[k], cs);

@@ -223,8 +223,8 @@ int64_t fp8_workspace_bytes(int64_t m, int64_t n, int64_t p, bool two_term);
 // layout/enqueue split mirrors the split-BF16 one (graph-capturable enqueue).
 struct Fp8GroupWork {
     int64_t tiles;                      // contraction tiles over all members
-    int64_t scale_items;                // exponent / amax items
-    int64_t pack_items;                 // record items
+    int64_t row_items;                  // row and column-amax items
+    int64_t col_items;                  // column record items
     int64_t clear_words;                // 32-bit words cleared first (counter + column amax)
     int64_t table_offset;               // byte offset of the member table in the workspace
 };
@@ -232,7 +232,7 @@ int64_t fp8_grouped_workspace_bytes(const moa_gemm_desc *const *members, int cou
 int64_t fp8_grouped_desc_bytes(int count);
 Fp8GroupWork fp8_grouped_layout(const moa_gemm_desc *const *members, int count, bool two_term, void *workspace,
                                 void *host_staging);
-hipError_t fp8_grouped_enqueue(void *workspace, int count, bool two_term, const Fp8GroupWork &work,
+hipError_t fp8_grouped_enqueue(void *workspace, int count, bool two_term, const Fp8GroupWork &work, bool cleared,
                                hipStream_t stream);
 hipError_t launch_fp8_grouped(const moa_gemm_desc *const *members, int count, bool two_term, void *workspace,
                               void *host_staging, const void *host_staging_dev, hipStream_t stream);

@@ -13,6 +13,14 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef int i32x8_t __attribute__((ext_vector_type(8)));
 
+// Four consecutive FP32 values at any element alignment: global memory serves
+// 16-byte loads that are only 4-byte aligned.
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4_t load4(const float *p) {
+    const f32x4u_t v = *reinterpret_cast<const f32x4u_t *>(p);
+    return v;
+}
+
 // Workgroups are handed to the 8 XCDs round-robin (workgroup id mod 8). Give
 // each XCD one contiguous range of tile ids so that the tiles sharing rows of
 // A and columns of B run under the same L2. Bijective for any tile count.

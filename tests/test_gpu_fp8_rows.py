@@ -1,0 +1,57 @@
+"""FP8 conditioning: operands taken by rows and by columns give the same product, bit for bit.
+
+A row-major A (or a column-major B) is conditioned row by row, a wave holding the
+row in 4, 8, 16 or 32 registers of four values, longer rows in two passes; a
+column-major A (or a row-major B) by columns with its amax in atomics. Exponents
+and codes do not depend on the way they were made, so the comparison is bitwise
+(no tolerance), at both sides of every register count, at odd lengths and at
+addresses that are only 4-byte aligned; a group of two must equal the single calls.
+"""
+import itertools
+
+import pytest
+import torch
+
+from paper_2306_11148_amd import moa
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TERMS = {1: moa.MOA_FLAG_FP8_ONE_TERM, 2: moa.MOA_FLAG_FP8_TWO_TERM}
+
+
+def operand(x, col, offset):
+    """x in the given order, `offset` elements past a 256-byte boundary."""
+    rows, cols = x.shape
+    buf = torch.empty(rows * cols + offset, device=DEV)[offset:]
+    v = buf.view(cols, rows).t() if col else buf.view(rows, cols)
+    return v.copy_(x)
+
+
+def values(g, rows, cols):
+    """Normal values; rows and columns of differing magnitude, some of them zero."""
+    x = torch.randn(rows, cols, generator=g, device=DEV)
+    x *= torch.exp2(torch.randint(-20, 20, (rows, 1), generator=g, device=DEV).float())
+    x[rows // 2] = 0.0
+    x[:, cols // 3] = 0.0
+    return x
+
+
+@pytest.mark.parametrize("terms", [1, 2])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 255, 257, 1023, 1024, 1025, 2048, 2049, 4096, 4099, 8191, 8192, 8193, 9000])
+def test_rows_and_columns_agree(n, terms):
+    m, p = 67, 259
+    g = torch.Generator(device=DEV).manual_seed(n)
+    A, B = values(g, m, n), values(g, p, n).t()
+    ref, descs = None, []
+    for a_col, b_col in itertools.product((False, True), repeat=2):
+        C = torch.full((m, p), float("nan"), device=DEV)
+        moa.moa_gemm(operand(A, a_col, n % 4), operand(B, b_col, (n + 1) % 4), C, path="fp8", flags=TERMS[terms])
+        ref = C if ref is None else ref
+        assert torch.equal(C, ref), f"a_col {a_col}, b_col {b_col}"
+    assert torch.isfinite(ref).all()
+    a, b = operand(A, False, n % 4), operand(B, False, (n + 3) % 4)
+    out = [torch.full((m, p), float("nan"), device=DEV) for _ in range(2)]
+    descs = [moa.make_desc(a, b, c, path="fp8", flags=TERMS[terms]) for c in out]
+    moa.moa_gemm_grouped(descs)
+    for c in out:
+        assert torch.equal(c, ref)
