@@ -402,25 +402,27 @@ template <bool TWO> struct Fp8Mode {
         i32x8_t ah[FM], bh[FN], al[TWO ? FM : 1], bl[TWO ? FN : 1];
     };
 
-    static __device__ __forceinline__ i32x8_t frag(const uint8_t *buf, int row, int half) {
-        const i32x4_t x = ring::lds_chunk<i32x4_t>(buf, row, 2 * half);
-        const i32x4_t y = ring::lds_chunk<i32x4_t>(buf, row, 2 * half + 1);
+    static constexpr int TERMS = TWO ? 3 : 1;
+    static __device__ __forceinline__ int chunk(int half, int x) { return 2 * half + x; }
+    static __device__ __forceinline__ i32x8_t frag(const uint8_t *rows, const int (&at)[2]) {
+        const i32x4_t x = *reinterpret_cast<const i32x4_t *>(rows + at[0]);
+        const i32x4_t y = *reinterpret_cast<const i32x4_t *>(rows + at[1]);
         return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
     }
 
     // LDS rows: [A hi (BM)][A lo (BM)][B hi (BN)][B lo (BN)] (lo: two-term only)
     template <int BM, int BN, int FM, int FN>
-    static __device__ __forceinline__ void read(const uint8_t *buf, int a_row, int b_row, int half,
+    static __device__ __forceinline__ void read(const uint8_t *a_part, const uint8_t *b_part, const int (&at)[2],
                                                 Frags<FM, FN> &f) {
 #pragma unroll
         for (int a = 0; a < FM; ++a) {
-            f.ah[a] = frag(buf, a_row + a * 32, half);
-            if constexpr (TWO) f.al[a] = frag(buf, a_row + BM + a * 32, half);
+            if constexpr (TWO) f.al[a] = frag(a_part + (BM + a * 32) * ring::REC_BYTES, at);
+            f.ah[a] = frag(a_part + a * 32 * ring::REC_BYTES, at);
         }
 #pragma unroll
         for (int b = 0; b < FN; ++b) {
-            f.bh[b] = frag(buf, b_row + b * 32, half);
-            if constexpr (TWO) f.bl[b] = frag(buf, b_row + BN + b * 32, half);
+            f.bh[b] = frag(b_part + b * 32 * ring::REC_BYTES, at);
+            if constexpr (TWO) f.bl[b] = frag(b_part + (BN + b * 32) * ring::REC_BYTES, at);
         }
     }
 
@@ -553,7 +555,8 @@ constexpr Fp8Shape kOne[] = {{128, 128, 64, 64, 3}, {256, 256, 128, 64, 3}, {256
 // The rectangular two-term blocks (8 waves of 64 x 64, 144 KB ring) read a
 // third less LDS per matrix-core step than 128 x 128 with 64 x 32 waves; a
 // wave's 96 LDS rows may span two record arrays. 256 x 128 is the default
-// for large products (8192 x 4096 x 8192: 0.75 vs 0.83-0.89 ms).
+// for large products (8192 x 4096 x 8192: 777 us vs 880-950 us for 128 x 128;
+// 834 us with four waves of 128 x 64, one per SIMD).
 constexpr Fp8Shape kTwo[] = {{128, 128, 64, 64, 3}, {128, 128, 64, 32, 3}, {128, 128, 64, 32, 5},
                              {128, 128, 64, 32, 4}, {128, 256, 64, 64, 3}, {256, 128, 64, 64, 3}};
 constexpr int kOneCount = sizeof(kOne) / sizeof(kOne[0]);
@@ -573,13 +576,19 @@ template <bool TWO, int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void fp8_grouped_kernel(
     const Fp8Member *__restrict__ g, int count, int64_t total_tiles, unsigned long long *__restrict__ counter) {
     constexpr int NREC = TWO ? 2 : 1;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[ring::Cfg<BM, BN, WM, WN, NREC, NST>::LDS];
-    __shared__ int64_t s_tile;
+    using G = ring::Cfg<BM, BN, WM, WN, NREC, NST>;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
+    // the claimed tile id lives in the ring's last slot, whose first load is
+    // issued behind the tile's first barrier (in an array of its own it makes
+    // the compiler wait for the loads in flight before every read of the ring)
+    int64_t *s_tile = reinterpret_cast<int64_t *>(lds + (NST - 1) * G::STAGE);
     for (;;) {
-        __syncthreads();                // nobody still reads lds or s_tile
-        if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(counter, 1ull);
+        __syncthreads();                // nobody still reads the ring
+        if (threadIdx.x == 0) *s_tile = (int64_t)atomicAdd(counter, 1ull);
         __syncthreads();
-        const int64_t tile = s_tile;
+        const int64_t claimed = *s_tile;
+        const int64_t tile = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)claimed) |
+                                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(claimed >> 32)) << 32);
         if (tile >= total_tiles) break;
         const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::first_tile>(g, count, tile));
         const Fp8Member &d = g[k];

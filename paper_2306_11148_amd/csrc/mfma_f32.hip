@@ -283,18 +283,20 @@ struct F32Mode {
     static constexpr bool SCALED = false;
     template <int FM, int FN> struct Frags { float4 a[FM][2], b[FN][2]; };
 
+    static constexpr int TERMS = 8;
+    static __device__ __forceinline__ int chunk(int half, int x) { return 2 * half + x; }
+
     template <int BM, int BN, int FM, int FN>
-    static __device__ __forceinline__ void read(const uint8_t *buf, int a_row, int b_row, int half,
+    static __device__ __forceinline__ void read(const uint8_t *a_part, const uint8_t *b_part, const int (&at)[2],
                                                 Frags<FM, FN> &f) {
 #pragma unroll
-        for (int a = 0; a < FM; ++a) {
-            f.a[a][0] = ring::lds_chunk<float4>(buf, a_row + a * 32, 2 * half);
-            f.a[a][1] = ring::lds_chunk<float4>(buf, a_row + a * 32, 2 * half + 1);
-        }
+        for (int x = 0; x < 2; ++x) {
 #pragma unroll
-        for (int b = 0; b < FN; ++b) {
-            f.b[b][0] = ring::lds_chunk<float4>(buf, b_row + b * 32, 2 * half);
-            f.b[b][1] = ring::lds_chunk<float4>(buf, b_row + b * 32, 2 * half + 1);
+            for (int a = 0; a < FM; ++a)
+                f.a[a][x] = *reinterpret_cast<const float4 *>(a_part + a * 32 * ring::REC_BYTES + at[x]);
+#pragma unroll
+            for (int b = 0; b < FN; ++b)
+                f.b[b][x] = *reinterpret_cast<const float4 *>(b_part + b * 32 * ring::REC_BYTES + at[x]);
         }
     }
 

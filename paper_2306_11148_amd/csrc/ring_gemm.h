@@ -14,8 +14,9 @@
 // walks the S slabs; per slab the NREC*(BM+BN) records go straight from HBM
 // into LDS (buffer_load ... lds, no register staging) through a ring of
 // NSTAGE buffers, and the slab's block products are summed in registers (the
-// "addition loop" over blocks). The fragments of slab t+1 are read from LDS
-// while the matrix-core steps of slab t issue.
+// "addition loop" over blocks). The fragments of slab s are read from LDS
+// while the matrix-core steps of slab s - 1 issue and slab s + NSTAGE - 1 is
+// on its way.
 //
 // LDS holds one 64-byte row per record. gfx950's LDS serves a 16-byte read for
 // 16 lanes per cycle out of a 256-byte window (64 banks), i.e. four
@@ -60,7 +61,7 @@ constexpr int waitcnt_vm(int n) { return (n & 0xF) | (((n >> 4) & 3) << 14) | (0
 // Workgroup barrier without the release fence of __syncthreads(): that fence
 // would also wait for the direct loads still in flight for later slabs. Each
 // wave first waits (s_waitcnt) for its own loads of the slab it is about to
-// read; LDS reads are complete before their values are used. The "memory"
+// read and for its LDS reads of the slot about to be refilled. The "memory"
 // clobber keeps the compiler from moving LDS accesses across the barrier.
 __device__ __forceinline__ void ring_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
@@ -73,9 +74,9 @@ template <int BM, int BN, int WM, int WN, int NREC, int NST = NSTAGE> struct Cfg
     static constexpr int LDS = NST * STAGE;
     static constexpr int LPW = ROWS / 16 / NW;            // KiB direct loads per wave per slab
     static_assert(ROWS % (16 * NW) == 0, "whole loads per wave");
-    // a wave's rows lie in one array, or span two (then fewer rows than either array)
-    static constexpr bool ONE_ARRAY = BM % (16 * LPW) == 0 && BN % (16 * LPW) == 0;
-    static_assert(ONE_ARRAY || (16 * LPW <= BM && 16 * LPW <= BN), "a wave's rows span at most two arrays");
+    static_assert(NST >= 3 && (NST - 2) * LPW <= 63, "a slot being refilled, one being read, one landing; vmcnt");
+    // load q of a slab is the same record array for every wave
+    static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole loads per wave and array");
 };
 
 // Vector offset of a load that must touch no memory: beyond any resource
@@ -106,16 +107,6 @@ __host__ __device__ inline RowWindow row_window(int BM, int BN, int NREC, int ro
     w.tiles = (int)((left < span ? left : span) / GROUP);
     return w;
 }
-// The first of a wave's LPW loads whose rows lie in the next array (LPW when
-// they all lie in one).
-__host__ __device__ inline int q_split_of(int BM, int BN, int NREC, int LPW, bool one_array, int row_first) {
-    if (one_array) return LPW;
-    const int end0 = row_first < NREC * BM ? (row_first / BM + 1) * BM
-                                           : NREC * BM + ((row_first - NREC * BM) / BN + 1) * BN;
-    const int q = (end0 - row_first) / 16;
-    return q < LPW ? q : LPW;
-}
-
 // The conditioned operands of one product.
 struct Operands {
     const uint8_t *a0, *a1;               // record arrays of A (a1 only when NREC == 2)
@@ -127,18 +118,20 @@ struct Operands {
     int accumulate;
 };
 
-// Fragment read of 16 bytes from LDS: logical chunk `chunk` of row `row`.
-template <class V>
-__device__ __forceinline__ V lds_chunk(const uint8_t *buf, int row, int chunk) {
-    static_assert(sizeof(V) == 16, "one 16-byte chunk");
-    return *reinterpret_cast<const V *>(buf + row * REC_BYTES + ((chunk ^ ((row >> 2) & 3)) << 4));
+// Byte offset of logical chunk `chunk` of row `row` (of any 32-row group: 32
+// rows further on the chunks lie alike).
+__device__ __forceinline__ int chunk_at(int row, int chunk) {
+    return row * REC_BYTES + ((chunk ^ ((row >> 2) & 3)) << 4);
 }
 
 // One BM x BN block of C at (i0, j0). Mode supplies
 //   template <int FM, int FN> struct Frags         fragments of one slab
+//   static int chunk(half, x)                      the two 16-byte chunks of a record that a lane reads
 //   template <int BM, int BN, int FM, int FN>
-//   static void read(buf, a_row, b_row, half, Frags &)   LDS -> registers
+//   static void read(a, b, at, Frags &)            LDS -> registers: chunk x of row r of the wave's part of A is
+//                                                  at a + at[x] + r * REC_BYTES, of its part of B at b + ...
 //   template <int FM, int FN> static void mma(const Frags &, acc)
+//   static constexpr int TERMS                     matrix-core steps per pair of fragments
 //   static constexpr bool SCALED                   apply row/col exponents
 // and the LDS rows of a slab are [A array 0 (BM)] .. [A array NREC-1]
 // [B array 0 (BN)] .. [B array NREC-1].
@@ -150,8 +143,9 @@ __device__ __forceinline__ V lds_chunk(const uint8_t *buf, int row, int chunk) {
 template <int BM, int BN, int WM, int WN, int NREC, class Mode, int NSTAGE = ring::NSTAGE>
 __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0, uint8_t *lds, int s_begin = 0,
                                      int s_end = -1, float *partial = nullptr) {
+#ifdef __HIP_DEVICE_COMPILE__           // the host pass would check the 16-byte direct loads against its own target
     using G = Cfg<BM, BN, WM, WN, NREC, NSTAGE>;
-    constexpr int WAVES_N = G::WAVES_N, FM = G::FM, FN = G::FN;
+    constexpr int WAVES_N = G::WAVES_N, NW = G::NW, FM = G::FM, FN = G::FN;
     constexpr int STAGE = G::STAGE, LPW = G::LPW;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -161,31 +155,19 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     const int L = (s_end < 0 ? S : s_end) - s_begin;   // slabs this block walks
 
     // LDS rows of a slab: [A array 0 (BM)] .. [A array NREC-1] [B array 0 (BN)] ..
-    // Wave w loads rows 16*LPW*w .. +16*LPW-1: inside one array, or (when the
-    // block's arrays are not multiples of a wave's share) across the end of
-    // one array into the next, from loads q_split onwards.
+    // Load q of wave w: rows 16 (NW q + w) .. +15, so which array a load reads
+    // is known at compile time, and its buffer resource (over the block's row
+    // tiles of that array) is one of 2 NREC, uniform over the workgroup.
     static_assert(NREC == 1 || NREC == 2, "one or two record arrays per operand");
     const int64_t tile_row = S * GROUP * REC_BYTES;       // bytes per row tile (16 rows, all slabs)
-    const int row_first = wave * LPW * 16;
-    // A buffer resource over the block's row tiles of the array holding a
-    // window's rows. (with two arrays the select of the base becomes a
-    // variable index into `op`: keep `op` in kernel-argument or global memory,
-    // never in a local variable, or it is placed in scratch memory)
-    auto resource = [&](const RowWindow &w) {
-        const uint8_t *base = w.a ? (NREC == 1 || w.arr == 0 ? op.a0 : op.a1) : (NREC == 1 || w.arr == 0 ? op.b0 : op.b1);
-        return __builtin_amdgcn_make_buffer_rsrc((void *)(base + w.first_tile * tile_row), (short)0,
-                                                 (int)(w.tiles * tile_row), 0x00020000);
-    };
-    const RowWindow w0 = row_window(BM, BN, NREC, row_first, i0, j0, op.m, op.p);
-    const __amdgpu_buffer_rsrc_t rsrc0 = resource(w0);
-    const int q_split = q_split_of(BM, BN, NREC, LPW, G::ONE_ARRAY, row_first);
-    RowWindow w1 = w0;
-    __amdgpu_buffer_rsrc_t rsrc1 = rsrc0;
-    if constexpr (!G::ONE_ARRAY) {
-        if (q_split < LPW) {
-            w1 = row_window(BM, BN, NREC, row_first + 16 * q_split, i0, j0, op.m, op.p);
-            rsrc1 = resource(w1);
-        }
+    const int64_t m = op.m, p = op.p;
+    RowWindow win[LPW];
+    const uint8_t *src[LPW];
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+        win[q] = row_window(BM, BN, NREC, NW * q * 16, i0, j0, m, p);
+        const uint8_t *base = win[q].a ? (win[q].arr == 0 ? op.a0 : op.a1) : (win[q].arr == 0 ? op.b0 : op.b1);
+        src[q] = base + win[q].first_tile * tile_row;
     }
     // lane L lands at row 16Q + L/4, physical chunk L%4, and fetches logical
     // chunk (L%4) ^ ((row/4) mod 4) = (L%4) ^ (L/16). Rows of the last
@@ -197,24 +179,29 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     // sum does not wrap); its LDS rows feed only outputs past m or p, which
     // are never stored.
     const int voff = (lane >> 2) * REC_BYTES + (((lane & 3) ^ (lane >> 4)) << 4);
-    auto issue = [&](int s) {            // s counts from s_begin
-        uint8_t *buf = lds + (s % NSTAGE) * STAGE + row_first * REC_BYTES;
+    // The next slab into buf. Slabs past the last have empty ranges: their loads
+    // touch no memory but keep the count of loads in flight.
+    int next_slab = 0;                   // counts from s_begin
+    auto issue_next = [&](uint8_t *buf) {
+        const bool past = next_slab >= L;
+        const int slab_at = (s0 + next_slab) * GROUP * REC_BYTES;
 #pragma unroll
         for (int q = 0; q < LPW; ++q) {
-            const bool first = G::ONE_ARRAY || q < q_split;
-            const int tile_in = first ? w0.row_in / GROUP + q : w1.row_in / GROUP + (q - q_split);
-            const bool live = tile_in < (first ? w0.tiles : w1.tiles);
+            const int tile_in = win[q].row_in / GROUP + wave;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                first ? rsrc0 : rsrc1, (lds_void_t *)(buf + q * 16 * REC_BYTES), 16,
-                live ? voff : kDeadVoffset, (int)(tile_in * tile_row) + (s0 + s) * GROUP * REC_BYTES, 0, 0);
+                __builtin_amdgcn_make_buffer_rsrc((void *)src[q], (short)0, past ? 0 : (int)(win[q].tiles * tile_row),
+                                                  0x00020000),
+                (lds_void_t *)(buf + (NW * q + wave) * 16 * REC_BYTES), 16,
+                tile_in < win[q].tiles ? voff : kDeadVoffset, (int)(tile_in * tile_row) + slab_at, 0, 0);
         }
+        ++next_slab;
     };
 
     const int frow = lane & 31, fhalf = lane >> 5;
+    const int at[2] = {chunk_at(frow, Mode::chunk(fhalf, 0)), chunk_at(frow, Mode::chunk(fhalf, 1))};
     typename Mode::template Frags<FM, FN> f0, f1;
-    auto read = [&](int s, typename Mode::template Frags<FM, FN> &f) {
-        const uint8_t *buf = lds + (s % NSTAGE) * STAGE;
-        Mode::template read<BM, BN, FM, FN>(buf, wm * WM + frow, NREC * BM + wn * WN + frow, fhalf, f);
+    auto read = [&](const uint8_t *buf, typename Mode::template Frags<FM, FN> &f) {
+        Mode::template read<BM, BN, FM, FN>(buf + wm * WM * REC_BYTES, buf + (NREC * BM + wn * WN) * REC_BYTES, at, f);
     };
 
     f32x16_t acc[FM][FN];
@@ -223,48 +210,69 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
 #pragma unroll
         for (int b = 0; b < FN; ++b) acc[a][b] = f32x16_t{};
 
-    // Wait until at most `stages` slabs of this wave's loads are in flight.
-    auto wait_loads = [&](int stages) {
-        switch (stages <= 0 ? 0 : stages >= 3 ? 3 : stages) {
-        case 0: __builtin_amdgcn_s_waitcnt(waitcnt_vm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(waitcnt_vm(LPW)); break;
-        case 2: __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * LPW)); break;
-        default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * LPW)); break;
+    // The next slab landed in every wave; every wave has read the one before it.
+    // The scheduling barriers keep a step's work between its barriers: left to
+    // itself the compiler moved matrix-core steps (which touch no memory) past
+    // the next barrier, so that the wait for the loads came right after their
+    // issue with nothing in between. With the steps kept apart, one more slab in
+    // flight and no branch in the loop the FP8 product 8192 x 4096 x 8192 takes
+    // 777 us (two terms; was 849), 3001 x 2777 x 1999 (one term) 49.6 (54), and the
+    // split-BF16 product of order 8192, whose steps had stayed in place, 2402 (2430).
+    auto arrive = [] {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * LPW) & ~(0xF << 8));
+        ring_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // One step, slab s landed: refill the slot of slab s - 1 (dma), read slab s
+    // (nxt), multiply slab s - 1, interleaved. The two slots are disjoint LDS,
+    // passed as restrict pointers so that the reads need not wait for the
+    // loads, which are meant to stay in flight.
+    auto step = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ nxt,
+                    const typename Mode::template Frags<FM, FN> &cur, typename Mode::template Frags<FM, FN> &next) {
+        constexpr int MMAS = Mode::TERMS * FM * FN, READS = 2 * NREC * (FM + FN);
+        issue_next(dma);
+        read(nxt, next);
+        Mode::template mma<FM, FN>(cur, acc);
+#pragma unroll
+        for (int i = 0; i < MMAS; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                  // matrix core
+            __builtin_amdgcn_sched_group_barrier(0x100, (READS + MMAS - 1) / MMAS, 0);
         }
     };
-    static_assert(NSTAGE >= 3 && NSTAGE <= 5, "wait_loads covers up to 3 slabs in flight");
-    static_assert(3 * LPW <= 63, "vmcnt counts up to 63 operations");
-
-    // One step (slab t + 1 exists): make slab t+1 visible (its loads landed
-    // in every wave), refill the buffer slab t-1 used with slab t+NSTAGE-1,
-    // read slab t+1's fragments, then issue slab t's products. The read is
-    // unconditional so that the two fragment sets keep fixed registers.
-    auto step = [&](int t, const typename Mode::template Frags<FM, FN> &cur,
-                    typename Mode::template Frags<FM, FN> &next) {
-        // issued so far: slabs up to t + NSTAGE - 2; t + 1 must have landed
-        wait_loads(min(NSTAGE - 3, L - t - 2));
-        ring_barrier();
-        if (t + NSTAGE - 1 < L) issue(t + NSTAGE - 1);
-        read(t + 1, next);
-        Mode::template mma<FM, FN>(cur, acc);
+    auto fill = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ nxt) {
+        issue_next(dma);
+        read(nxt, f0);
     };
 
     if (L > 0) {
-        for (int q = 0; q < NSTAGE - 1; ++q)
-            if (q < L) issue(q);
-        wait_loads(min(NSTAGE - 2, L - 1));            // slab 0 has landed
-        ring_barrier();
-        read(0, f0);
-        int t = 0;
-        for (; t + 2 < L; t += 2) {
-            step(t, f0, f1);
-            step(t + 1, f1, f0);
+        for (int q = 0; q < NSTAGE - 1; ++q) issue_next(lds + q * STAGE);
+        int rd = 0, wr = NSTAGE - 1;                         // slots of slabs s and s - 1
+        auto next_slot = [&] {
+            wr = rd;
+            rd = rd + 1 == NSTAGE ? 0 : rd + 1;
+        };
+        // An odd number of slabs starts with one of zeros, so that the loop runs
+        // whole pairs (its products add +0 to accumulators that are +0).
+        if (L & 1) {
+            f0 = {};
+        } else {
+            arrive();
+            fill(lds + wr * STAGE, lds + rd * STAGE);
+            next_slot();
         }
-        if (t + 1 < L) {                               // two slabs left
-            step(t, f0, f1);
-            f0 = f1;
+        for (int pairs = (L + 1) / 2 - 1; pairs > 0; --pairs) {
+            arrive();
+            step(lds + wr * STAGE, lds + rd * STAGE, f0, f1);
+            next_slot();
+            arrive();
+            step(lds + wr * STAGE, lds + rd * STAGE, f1, f0);
+            next_slot();
         }
-        Mode::template mma<FM, FN>(f0, acc);           // the last slab
+        arrive();
+        step(lds + wr * STAGE, lds + rd * STAGE, f0, f1);
+        Mode::template mma<FM, FN>(f1, acc);                 // the last slab
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));           // no load may land in LDS later
     }
 
     // Epilogue: register r of lane l holds C[8(r/4) + 4(l/32) + r%4][l%32] of
@@ -313,6 +321,7 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
         epilogue(std::true_type{});
     else
         epilogue(std::false_type{});
+#endif
 }
 
 // Tile-id -> block mapping of a single-product launch (XCD-aware bands).
@@ -467,26 +476,22 @@ inline int64_t check_loads(int BM, int BN, int WM, int WN, int NREC, int64_t m, 
     const int NW = (BM / WM) * (BN / WN);
     const int ROWS = NREC * (BM + BN);
     const int LPW = ROWS / 16 / NW;
-    const bool one_array = BM % (16 * LPW) == 0 && BN % (16 * LPW) == 0;
     const int64_t tile_row = S * GROUP * REC_BYTES;
     const int64_t lim31 = (int64_t(1) << 31) - 1;
     int64_t bad = 0, count = 0;
-    if (ROWS % (16 * NW) != 0 || S <= 0) return 1;
+    if (BM % (16 * NW) != 0 || BN % (16 * NW) != 0 || S <= 0) return 1;
     for (int64_t i0 = 0; i0 < m; i0 += BM)
         for (int64_t j0 = 0; j0 < p; j0 += BN)
-            for (int wave = 0; wave < NW; ++wave) {
-                const int row_first = wave * LPW * 16;
-                const RowWindow w0 = row_window(BM, BN, NREC, row_first, i0, j0, m, p);
-                const int q_split = q_split_of(BM, BN, NREC, LPW, one_array, row_first);
-                const RowWindow w1 = q_split < LPW ? row_window(BM, BN, NREC, row_first + 16 * q_split, i0, j0, m, p) : w0;
+            for (int wave = 0; wave < NW; ++wave)
                 for (int q = 0; q < LPW; ++q) {
                     ++count;
-                    const bool first = one_array || q < q_split;
-                    const RowWindow &w = first ? w0 : w1;
-                    const int tile_in = first ? w0.row_in / GROUP + q : w1.row_in / GROUP + (q - q_split);
-                    // the load's rows in LDS must be the rows this window names
-                    const RowWindow here = row_window(BM, BN, NREC, row_first + 16 * q, i0, j0, m, p);
-                    if (here.a != w.a || here.arr != w.arr || here.row_in != tile_in * GROUP) ++bad;
+                    const RowWindow w = row_window(BM, BN, NREC, (NW * q + wave) * 16, i0, j0, m, p);
+                    const int tile_in = w.row_in / GROUP;
+                    // every wave's load q reads the array of wave 0's, from the same first tile
+                    const RowWindow w0 = row_window(BM, BN, NREC, NW * q * 16, i0, j0, m, p);
+                    if (w0.a != w.a || w0.arr != w.arr || w0.first_tile != w.first_tile || w0.tiles != w.tiles ||
+                        w0.row_in + 16 * wave != w.row_in)
+                        ++bad;
                     const int64_t padded_tiles = padded_rows(w.a ? m : p) / GROUP;
                     const int64_t num_records = (int64_t)w.tiles * tile_row;
                     if (w.tiles < 1 || num_records > lim31) ++bad;
@@ -499,7 +504,6 @@ inline int64_t check_loads(int BM, int BN, int WM, int WN, int NREC, int64_t m, 
                         ++bad;                                // dead but inside the operand
                     }
                 }
-            }
     if (loads) *loads = count;
     return bad;
 }

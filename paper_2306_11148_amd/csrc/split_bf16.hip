@@ -186,18 +186,24 @@ struct SplitMode {
     static constexpr bool SCALED = false;
     template <int FM, int FN> struct Frags { bf16x8_t ah[FM], al[FM], bh[FN], bl[FN]; };
 
+    static constexpr int TERMS = 3;
+    static __device__ __forceinline__ int chunk(int half, int x) { return 2 * x + half; }
+    static __device__ __forceinline__ bf16x8_t frag(const uint8_t *rows, int at) {
+        return *reinterpret_cast<const bf16x8_t *>(rows + at);
+    }
+
     template <int BM, int BN, int FM, int FN>
-    static __device__ __forceinline__ void read(const uint8_t *buf, int a_row, int b_row, int half,
+    static __device__ __forceinline__ void read(const uint8_t *a_part, const uint8_t *b_part, const int (&at)[2],
                                                 Frags<FM, FN> &f) {
 #pragma unroll
         for (int a = 0; a < FM; ++a) {
-            f.ah[a] = ring::lds_chunk<bf16x8_t>(buf, a_row + a * 32, half);
-            f.al[a] = ring::lds_chunk<bf16x8_t>(buf, a_row + a * 32, 2 + half);
+            f.ah[a] = frag(a_part + a * 32 * ring::REC_BYTES, at[0]);
+            f.al[a] = frag(a_part + a * 32 * ring::REC_BYTES, at[1]);
         }
 #pragma unroll
         for (int b = 0; b < FN; ++b) {
-            f.bh[b] = ring::lds_chunk<bf16x8_t>(buf, b_row + b * 32, half);
-            f.bl[b] = ring::lds_chunk<bf16x8_t>(buf, b_row + b * 32, 2 + half);
+            f.bh[b] = frag(b_part + b * 32 * ring::REC_BYTES, at[0]);
+            f.bl[b] = frag(b_part + b * 32 * ring::REC_BYTES, at[1]);
         }
     }
 
