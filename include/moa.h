@@ -214,9 +214,9 @@ moa_status moa_gemm_noalloc(const moa_gemm_desc *desc, void *stream);
  * on the way through LDS (no conditioning pass; a member that splits its k
  * walk puts one item per chunk on the list, and its partials are summed
  * behind the launch); scaled-FP8 members are conditioned together and
- * contracted by one persistent launch per term count; members on the ONF and
- * FP32 matrix-core paths, members with a column-major operand and scaled-FP8
- * members with a split k walk run as single launches on the same stream. No
+ * contracted by one persistent launch per term count (split k walks likewise);
+ * members on the ONF and FP32 matrix-core paths and members with a
+ * column-major operand run as single launches on the same stream. No
  * ordering among members. Each result is bitwise the result moa_gemm gives for
  * the same descriptor, whichever persistent kernel runs.
  * Descriptors are read on the host during the call; the array may be reused

@@ -472,7 +472,10 @@ struct Fp8Member {
     int64_t first_tile;                 // first contraction work-list id
     int64_t row_first;                  // first row work-list id
     int64_t col_first;                  // first column work-list id
-    int32_t tiles_n, reserved;
+    float *partials;                    // split k walk: chunk q's sums at partials + q m p
+    int64_t sum_first;                  // first block of the summing kernel
+    int32_t tiles_n, tiles;             // blocks of a row of C, and of C
+    int32_t chunks, chunk_slabs;        // contraction items: `tiles` per chunk of the k walk
     int32_t row_items;                  // row items: row_items (4 rows each), then
     int32_t col_amax_x;                 //   col_amax_x * ceil(n / COL_BAND) column bands
     int32_t col_x;                      // column items: col_x * max(S, 1) 64-column blocks
@@ -553,9 +556,8 @@ constexpr Fp8Shape kOne[] = {{128, 128, 64, 64, 3}, {256, 256, 128, 64, 3}, {256
 // Deeper rings pay off here: a slab carries 64 k, so a step is short next
 // to the latency of its loads.
 // The rectangular two-term blocks (8 waves of 64 x 64, 144 KB ring) read a
-// third less LDS per matrix-core step than 128 x 128 with 64 x 32 waves; a
-// wave's 96 LDS rows may span two record arrays. 256 x 128 is the default
-// for large products (8192 x 4096 x 8192: 777 us vs 880-950 us for 128 x 128;
+// third less LDS per matrix-core step than 128 x 128 with 64 x 32 waves.
+// 256 x 128 is the default for large products (8192 x 4096 x 8192: 777 us vs 880-950 us for 128 x 128;
 // 834 us with four waves of 128 x 64, one per SIMD).
 constexpr Fp8Shape kTwo[] = {{128, 128, 64, 64, 3}, {128, 128, 64, 32, 3}, {128, 128, 64, 32, 5},
                              {128, 128, 64, 32, 4}, {128, 256, 64, 64, 3}, {256, 128, 64, 64, 3}};
@@ -583,6 +585,9 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void fp8_grouped_kernel
     // the compiler wait for the loads in flight before every read of the ring)
     int64_t *s_tile = reinterpret_cast<int64_t *>(lds + (NST - 1) * G::STAGE);
     for (;;) {
+        // the last tile's loads and stores of C are done (or the compiler waits
+        // for them behind the next tile's first loads, and so for those too)
+        __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0));
         __syncthreads();                // nobody still reads the ring
         if (threadIdx.x == 0) *s_tile = (int64_t)atomicAdd(counter, 1ull);
         __syncthreads();
@@ -592,10 +597,41 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void fp8_grouped_kernel
         if (tile >= total_tiles) break;
         const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::first_tile>(g, count, tile));
         const Fp8Member &d = g[k];
-        const int64_t local = tile - d.first_tile;
-        const int64_t tm = local / d.tiles_n, tn = local - tm * d.tiles_n;
-        ring::tile<BM, BN, WM, WN, NREC, Fp8Mode<TWO>, NST>(d.op, __builtin_amdgcn_readfirstlane((int)tm) * (int64_t)BM,
-                                                            __builtin_amdgcn_readfirstlane((int)tn) * (int64_t)BN, lds);
+        const int local = (int)(tile - d.first_tile);        // chunks x tiles: below 2^31
+        const int chunk = local / d.tiles, at = local - chunk * d.tiles;
+        const int tm = at / d.tiles_n, tn = at - tm * d.tiles_n;
+        const int s_begin = __builtin_amdgcn_readfirstlane(chunk * d.chunk_slabs);
+        const int s_end = __builtin_amdgcn_readfirstlane(min((int)d.S, s_begin + d.chunk_slabs));
+        float *partial = d.chunks > 1 ? d.partials + (int64_t)__builtin_amdgcn_readfirstlane(chunk) * d.m * d.p : nullptr;
+        ring::tile<BM, BN, WM, WN, NREC, Fp8Mode<TWO>, NST>(d.op, __builtin_amdgcn_readfirstlane(tm) * (int64_t)BM,
+                                                            __builtin_amdgcn_readfirstlane(tn) * (int64_t)BN, lds,
+                                                            s_begin, s_end, partial);
+    }
+}
+
+// C of the members with a split k walk from their chunks' partials, in chunk
+// order and descaled as ring::splitk_reduce_kernel does, 1024 elements per block.
+constexpr int SUM_BLOCK = 1024;
+__global__ __launch_bounds__(256) void fp8_sums_kernel(const Fp8Member *__restrict__ g, int count) {
+    // sum_first counts the blocks of the members before: the last member that
+    // starts at or before this block owns it (an unsplit one takes no blocks)
+    const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::sum_first>(g, count, (int64_t)blockIdx.x));
+    const Fp8Member &d = g[k];
+    const int64_t mp = d.m * d.p, x0 = ((int64_t)blockIdx.x - d.sum_first) * SUM_BLOCK;
+    if (d.p % 4 == 0 && (uintptr_t)d.op.C % 16 == 0) {
+        const int64_t x = x0 + threadIdx.x * 4;
+        if (x < mp) {
+            const int64_t i = x / d.p;
+            ring::splitk_sum<4>(d.partials, d.chunks, mp, x, d.op.C, d.e[i], d.f + (x - i * d.p), d.op.accumulate);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < SUM_BLOCK / 256; ++e) {
+            const int64_t x = x0 + e * 256 + threadIdx.x;
+            if (x >= mp) continue;
+            const int64_t i = x / d.p;
+            ring::splitk_sum<1>(d.partials, d.chunks, mp, x, d.op.C, d.e[i], d.f + (x - i * d.p), d.op.accumulate);
+        }
     }
 }
 
@@ -767,38 +803,45 @@ hipError_t launch_fp8(const moa_gemm_desc &d, const Plan &plan, void *ws, hipStr
 int64_t fp8_grouped_desc_bytes(int count) { return (int64_t)count * (int64_t)sizeof(Fp8Member); }
 
 namespace {
-int64_t member_bytes(const moa_gemm_desc &d, bool two) {
+int64_t partial_bytes(const Fp8Product &x) {
+    return x.split_k > 1 ? align256((int64_t)x.split_k * x.d->m * x.d->p * 4) : 0;
+}
+int64_t member_bytes(const Fp8Product &x, bool two) {
+    const moa_gemm_desc &d = *x.d;
     const int64_t S = (d.n + SLAB8 - 1) / SLAB8;
     const int64_t rec = align256(ring::array_bytes(d.m, S)) + align256(ring::array_bytes(d.p, S));
-    return align256(4 * d.m) + align256(4 * d.p) + (two ? 2 : 1) * rec;
+    return align256(4 * d.m) + align256(4 * d.p) + (two ? 2 : 1) * rec + partial_bytes(x);
 }
-int64_t header_bytes(const moa_gemm_desc *const *members, int count) {
+int64_t header_bytes(const Fp8Product *members, int count) {
     int64_t cols = 0;
-    for (int k = 0; k < count; ++k) cols += members[k]->p;
+    for (int k = 0; k < count; ++k) cols += members[k].d->p;
     return align256(8 + 4 * cols);     // claim counter, then every member's column amax
 }
 }  // namespace
 
-int64_t fp8_grouped_workspace_bytes(const moa_gemm_desc *const *members, int count, bool two) {
+int64_t fp8_grouped_workspace_bytes(const Fp8Product *members, int count, bool two) {
     int64_t b = header_bytes(members, count) + align256(fp8_grouped_desc_bytes(count));
-    for (int k = 0; k < count; ++k) b += member_bytes(*members[k], two);
+    for (int k = 0; k < count; ++k) b += member_bytes(members[k], two);
     return b;
 }
 
 // Workspace: [counter u64 | amax of every member][member table][per member:
-// e, f, record arrays]. Members are listed longest k walk first.
-Fp8GroupWork fp8_grouped_layout(const moa_gemm_desc *const *members, int count, bool two, void *ws,
+// e, f, record arrays, partials]. Members are listed longest k walk (of a
+// chunk) first.
+Fp8GroupWork fp8_grouped_layout(const Fp8Product *members, int count, bool two, void *ws,
                                 void *host_staging) {
     std::vector<int> order(count);
     for (int k = 0; k < count; ++k) order[k] = k;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return members[a]->n > members[b]->n; });
+    auto walk = [&](int k) { return members[k].d->n / std::max(members[k].split_k, 1); };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return walk(a) > walk(b); });
     char *base = static_cast<char *>(ws);
     uint32_t *amax = reinterpret_cast<uint32_t *>(base + 8);
     char *cur = base + header_bytes(members, count) + align256(fp8_grouped_desc_bytes(count));
     Fp8Member *h = static_cast<Fp8Member *>(host_staging);
-    Fp8GroupWork w{0, 0, 0, 2, header_bytes(members, count)};
+    Fp8GroupWork w{0, 0, 0, 0, 2, header_bytes(members, count)};
     for (int q = 0; q < count; ++q) {
-        const moa_gemm_desc &d = *members[order[q]];
+        const Fp8Product &x = members[order[q]];
+        const moa_gemm_desc &d = *x.d;
         Fp8Member g;
         g.A = static_cast<const float *>(d.A);
         g.B = static_cast<const float *>(d.B);
@@ -824,8 +867,22 @@ Fp8GroupWork fp8_grouped_layout(const moa_gemm_desc *const *members, int count, 
         g.op.m = d.m; g.op.p = d.p; g.op.S = g.S;
         g.op.accumulate = d.accumulate;
         g.tiles_n = (int32_t)((d.p + G_BN - 1) / G_BN);
+        g.tiles = (int32_t)((d.m + G_BM - 1) / G_BM) * g.tiles_n;
+        g.chunks = 1;
+        g.chunk_slabs = (int32_t)g.S;
+        g.partials = nullptr;
+        g.sum_first = w.sum_items;
+        if (x.split_k > 1 && g.S > 1) {                    // as ring::launch_splitk cuts them
+            g.chunk_slabs = (int32_t)((g.S + x.split_k - 1) / x.split_k);
+            g.chunks = (int32_t)((g.S + g.chunk_slabs - 1) / g.chunk_slabs);
+        }
+        if (g.chunks > 1) {
+            g.partials = reinterpret_cast<float *>(cur);
+            cur += partial_bytes(x);
+            w.sum_items += (d.m * d.p + SUM_BLOCK - 1) / SUM_BLOCK;
+        }
         g.first_tile = w.tiles;
-        w.tiles += ((d.m + G_BM - 1) / G_BM) * g.tiles_n;
+        w.tiles += (int64_t)g.chunks * g.tiles;
         g.row_items = (int32_t)(padded_rows(d.m) / 4);
         g.col_amax_x = (int32_t)((d.p + 255) / 256);
         g.row_first = w.row_items;
@@ -875,6 +932,8 @@ hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork
                                counter);
         }
     }
+    if (w.sum_items > 0)
+        hipLaunchKernelGGL(fp8_sums_kernel, dim3((unsigned)w.sum_items), dim3(256), 0, st, dev, count);
     return hipGetLastError();
 }
 
@@ -892,7 +951,7 @@ __global__ __launch_bounds__(256) void table_from_host_kernel(const uint4 *__res
 }
 }  // namespace
 
-hipError_t launch_fp8_grouped(const moa_gemm_desc *const *members, int count, bool two, void *ws,
+hipError_t launch_fp8_grouped(const Fp8Product *members, int count, bool two, void *ws,
                               void *host_staging, const void *host_staging_dev, hipStream_t st) {
     if (count <= 0) return hipSuccess;
     const Fp8GroupWork w = fp8_grouped_layout(members, count, two, ws, host_staging);

@@ -48,7 +48,8 @@ moa_status moa_group_create(const moa_gemm_desc *descs, int64_t count, moa_group
         if (!out) return fail(MOA_ERR_INVALID, "null output");
         *out = nullptr;
         if (count < 0 || (count > 0 && !descs)) return fail(MOA_ERR_INVALID, "bad descriptor array");
-        std::vector<const moa_gemm_desc *> split, fp8[2];
+        std::vector<const moa_gemm_desc *> split;
+        std::vector<Fp8Product> fp8[2];
         std::vector<moa_gemm_desc> single, f32m;
         std::vector<Plan> f32p;
         int64_t f32_bytes = 0;
@@ -65,7 +66,7 @@ moa_status moa_group_create(const moa_gemm_desc *descs, int64_t count, moa_group
             if (pl.path == MOA_PATH_SPLIT_BF16 && !split_grouped_fits(d))
                 return fail(MOA_ERR_UNSUPPORTED, "member %lld is too large for the persistent launch", (long long)k);
             if (pl.path == MOA_PATH_SPLIT_BF16) split.push_back(&d);
-            else if (pl.path == MOA_PATH_FP8_SCALED) fp8[fp8_two_term(d) ? 1 : 0].push_back(&d);
+            else if (pl.path == MOA_PATH_FP8_SCALED) fp8[fp8_two_term(d) ? 1 : 0].push_back({&d, 1});
             else if (pl.workspace_bytes == 0) single.push_back(d);
             else if (pl.path == MOA_PATH_MFMA_F32) {
                 f32m.push_back(d);

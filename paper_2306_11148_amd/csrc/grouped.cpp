@@ -5,10 +5,11 @@
 // that split their k walk put one item per chunk on it, and one kernel adds
 // their partials afterwards); scaled-FP8 members are conditioned together and
 // contracted likewise, one sequence per term count. Members on the ONF and FP32
-// matrix-core paths run as single launches, in order, on the same stream. The member tables of the persistent launches
-// are written to pinned, coherent staging buffers, mapped into the device's
-// address space, that are recycled once the stream has consumed them; each
-// launch reads its table from there with a small kernel.
+// matrix-core paths run as single launches, in order, on the same stream. The
+// member tables of the persistent launches are written to pinned, coherent
+// staging buffers, mapped into the device's address space, that are recycled
+// once the stream has consumed them; each launch reads its table from there
+// with a small kernel.
 #include <algorithm>
 #include <mutex>
 #include <vector>
@@ -147,7 +148,8 @@ moa_status run_persistent(int64_t desc_bytes, int64_t need, Launch launch, hipSt
 // split their k walk into so many chunks; FP8 by term count) and those that run
 // singly, as run_grouped splits them.
 struct Partition {
-    std::vector<const moa_gemm_desc *> single, split, fp8[2];
+    std::vector<const moa_gemm_desc *> single, split;
+    std::vector<Fp8Product> fp8[2];
     std::vector<std::pair<const moa_gemm_desc *, int>> chunked;
 };
 
@@ -164,8 +166,8 @@ Partition partition(const moa_gemm_desc *descs, int64_t count, const int *split_
             pt.chunked.push_back({&d, chunks});
         else if (path == MOA_PATH_SPLIT_BF16 && split_grouped_fits(d))
             pt.split.push_back(&d);
-        else if (path == MOA_PATH_FP8_SCALED && chunks <= 1)
-            pt.fp8[fp8_two_term(d) ? 1 : 0].push_back(&d);
+        else if (path == MOA_PATH_FP8_SCALED)
+            pt.fp8[fp8_two_term(d) ? 1 : 0].push_back({&d, chunks});
         else
             pt.single.push_back(&d);
     }

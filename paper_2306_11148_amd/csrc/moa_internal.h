@@ -218,23 +218,30 @@ void fp8_shape(bool two_term, int variant, Plan *p);
 int fp8_variant_count(bool two_term);
 int64_t fp8_workspace_bytes(int64_t m, int64_t n, int64_t p, bool two_term);
 
-// Grouped FP8 (members of one term count, validated by the caller): one
-// conditioning pass over all members and one persistent contraction. The
-// layout/enqueue split mirrors the split-BF16 one (graph-capturable enqueue).
+// Grouped FP8 (members of one term count, validated by the caller, each with
+// the chunks its k walk is split into): one conditioning pass over all members,
+// one persistent contraction, and where members are split one kernel that adds
+// their chunks' partials. The layout/enqueue split mirrors the split-BF16 one
+// (graph-capturable enqueue).
+struct Fp8Product {
+    const moa_gemm_desc *d;
+    int split_k;
+};
 struct Fp8GroupWork {
     int64_t tiles;                      // contraction tiles over all members
     int64_t row_items;                  // row and column-amax items
     int64_t col_items;                  // column record items
+    int64_t sum_items;                  // blocks of the summing kernel
     int64_t clear_words;                // 32-bit words cleared first (counter + column amax)
     int64_t table_offset;               // byte offset of the member table in the workspace
 };
-int64_t fp8_grouped_workspace_bytes(const moa_gemm_desc *const *members, int count, bool two_term);
+int64_t fp8_grouped_workspace_bytes(const Fp8Product *members, int count, bool two_term);
 int64_t fp8_grouped_desc_bytes(int count);
-Fp8GroupWork fp8_grouped_layout(const moa_gemm_desc *const *members, int count, bool two_term, void *workspace,
+Fp8GroupWork fp8_grouped_layout(const Fp8Product *members, int count, bool two_term, void *workspace,
                                 void *host_staging);
 hipError_t fp8_grouped_enqueue(void *workspace, int count, bool two_term, const Fp8GroupWork &work, bool cleared,
                                hipStream_t stream);
-hipError_t launch_fp8_grouped(const moa_gemm_desc *const *members, int count, bool two_term, void *workspace,
+hipError_t launch_fp8_grouped(const Fp8Product *members, int count, bool two_term, void *workspace,
                               void *host_staging, const void *host_staging_dev, hipStream_t stream);
 
 hipError_t launch_split_only(const float *X, int64_t count, uint16_t *hi, uint16_t *lo,

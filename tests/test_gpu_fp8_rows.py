@@ -55,3 +55,26 @@ def test_rows_and_columns_agree(n, terms):
     moa.moa_gemm_grouped(descs)
     for c in out:
         assert torch.equal(c, ref)
+
+
+@pytest.mark.parametrize("terms", [1, 2])
+def test_grouped_members_that_split_k(terms):
+    """Members with a split k walk (planned, asked for, more chunks than slabs divide into) beside unsplit ones:
+    each bitwise as alone, overwriting and accumulating, p a multiple of four and not, twice in a row."""
+    members = [(96, 6000, 132, 0, False), (200, 300, 70, 0, True), (65, 5003, 33, 9, True), (130, 64 * 7, 260, 5, False),
+               (3, 4099, 7, 0, True), (64, 65, 64, 2, False), (33, 40, 129, 0, False), (1, 9000, 1, 64, True)]
+    g = torch.Generator(device=DEV).manual_seed(terms)
+    ops, descs = [], []
+    for m, n, p, chunks, acc in members:
+        flags = TERMS[terms] | (moa.MOA_FLAG_SPLIT_K(chunks) if chunks else 0)
+        A, B, C0 = values(g, m, n), values(g, n, p), torch.randn(m, p, generator=g, device=DEV)
+        R, C = C0.clone(), torch.empty_like(C0)
+        moa.moa_gemm(A, B, R, path="fp8", accumulate=acc, flags=flags)
+        ops.append((C, C0, R, A, B))
+        descs.append(moa.make_desc(A, B, C, path="fp8", accumulate=acc, flags=flags))
+    for _ in range(2):
+        for C, C0, *_ in ops:
+            C.copy_(C0)
+        moa.moa_gemm_grouped(descs)
+        for k, (C, _, R, *_) in enumerate(ops):
+            assert torch.equal(C, R), f"member {k}"
