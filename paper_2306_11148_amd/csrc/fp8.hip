@@ -94,16 +94,6 @@ __device__ __forceinline__ float wave_max(float mx) {
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     return mx;
 }
-// Four values of a row from k on, zero past n.
-__device__ __forceinline__ f32x4_t row4(const float *__restrict__ row, int64_t k, int64_t n) {
-    if (k + 4 <= n) return load4(row + k);
-    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        if (k + t < n) v[t] = row[k + t];
-    return v;
-}
-
 // e_i of every row of A, one workgroup per row.
 __global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ A, int64_t n,
                                                       int32_t *__restrict__ e) {
@@ -119,29 +109,32 @@ __global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ 
 }
 
 // Column amax of B: a workgroup takes 256 columns (four per lane) over a band
-// of COL_BAND rows, a quarter of the band per wave, and adds one atomic per
-// column. HBM-bound when its loads are 16 bytes and many are in flight; with one
-// column per lane and a launch to clear first it took 42 us at 4096 x 8192.
-constexpr int COL_BAND = 256;
+// of COL_BAND rows, a quarter of the band per wave, all its loads in flight at
+// once, and adds one atomic per column. HBM-bound for large operands (4096 x
+// 8192: 34 us); a small one takes the latency of one round of loads (1000 x
+// 1000: 4.1 us; with 64 rows per wave 14.9, with one column per lane 9.5).
+constexpr int COL_BAND = 64;
 __device__ __forceinline__ void col_amax_block(const float *__restrict__ B, int64_t n, int64_t p, int64_t bx,
                                                int64_t by, uint32_t *__restrict__ amax, float (*part)[256]) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int R = COL_BAND / 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t j = bx * 256 + lane * 4;
-    const int64_t k0 = by * COL_BAND + wave * (COL_BAND / 4), k1 = min(n, k0 + COL_BAND / 4);
-    f32x4_t mx = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (j + 4 <= p) {
-#pragma unroll 16
-        for (int64_t k = k0; k < k1; ++k) {
-            const f32x4_t v = load4(B + k * p + j);
+    const int64_t k0 = by * COL_BAND + wave * R;
+    f32x4_t x[R], mx = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (k0 + R <= n && j + 4 <= p) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) mx[t] = fmaxf(mx[t], fabsf(v[t]));
-        }
+        for (int r = 0; r < R; ++r) x[r] = load4(B + (k0 + r) * p + j);
     } else {
-        for (int64_t k = k0; k < k1; ++k)
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (j + t < p) mx[t] = fmaxf(mx[t], fabsf(B[k * p + j + t]));
+        for (int r = 0; r < R; ++r) {
+            x[r] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            if (k0 + r < n) x[r] = row4(B + (k0 + r) * p, j, p);
+        }
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mx[t] = fmaxf(mx[t], fabsf(x[r][t]));
     __syncthreads();                               // earlier readers of `part` are done
     *reinterpret_cast<f32x4_t *>(&part[wave][lane * 4]) = mx;
     __syncthreads();
@@ -575,7 +568,7 @@ hipError_t launch_shape(const ring::Operands &op, hipStream_t st) {
 }
 
 template <bool TWO, int BM, int BN, int WM, int WN, int NST>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void fp8_grouped_kernel(
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, TWO ? 1 : 2) void fp8_grouped_kernel(
     const Fp8Member *__restrict__ g, int count, int64_t total_tiles, unsigned long long *__restrict__ counter) {
     constexpr int NREC = TWO ? 2 : 1;
     using G = ring::Cfg<BM, BN, WM, WN, NREC, NST>;

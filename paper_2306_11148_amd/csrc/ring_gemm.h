@@ -215,9 +215,10 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     // itself the compiler moved matrix-core steps (which touch no memory) past
     // the next barrier, so that the wait for the loads came right after their
     // issue with nothing in between. With the steps kept apart, one more slab in
-    // flight and no branch in the loop the FP8 product 8192 x 4096 x 8192 takes
-    // 777 us (two terms; was 849), 3001 x 2777 x 1999 (one term) 49.6 (54), and the
-    // split-BF16 product of order 8192, whose steps had stayed in place, 2402 (2430).
+    // flight, no branch in the loop and the loads spread over the step like the
+    // reads, the FP8 product 8192 x 4096 x 8192 takes 770 us (two terms; was 849)
+    // and the split-BF16 product of order 8192, whose steps had stayed in place,
+    // 2364 (2430; 2416 with all of a step's loads at its start).
     auto arrive = [] {
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * LPW) & ~(0xF << 8));
@@ -238,11 +239,13 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
         for (int i = 0; i < MMAS; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                  // matrix core
             __builtin_amdgcn_sched_group_barrier(0x100, (READS + MMAS - 1) / MMAS, 0);
+            __builtin_amdgcn_sched_group_barrier(0x20, (LPW + MMAS - 1) / MMAS, 0);
         }
     };
-    auto fill = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ nxt) {
+    auto fill = [&](uint8_t *__restrict__ dma, const uint8_t *__restrict__ nxt,
+                    typename Mode::template Frags<FM, FN> &next) {
         issue_next(dma);
-        read(nxt, f0);
+        read(nxt, next);
     };
 
     if (L > 0) {
@@ -252,25 +255,33 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
             wr = rd;
             rd = rd + 1 == NSTAGE ? 0 : rd + 1;
         };
-        // An odd number of slabs starts with one of zeros, so that the loop runs
-        // whole pairs (its products add +0 to accumulators that are +0).
+        // The loop runs whole pairs, from a slab in f0 to one in f0; the last slab
+        // ends in f1, so an odd number of slabs starts there.
+        arrive();
         if (L & 1) {
-            f0 = {};
+            fill(lds + wr * STAGE, lds + rd * STAGE, f1);
+            next_slot();
+            if (L > 1) {
+                arrive();
+                step(lds + wr * STAGE, lds + rd * STAGE, f1, f0);
+                next_slot();
+            }
         } else {
-            arrive();
-            fill(lds + wr * STAGE, lds + rd * STAGE);
+            fill(lds + wr * STAGE, lds + rd * STAGE, f0);
             next_slot();
         }
-        for (int pairs = (L + 1) / 2 - 1; pairs > 0; --pairs) {
+        if (L > 1) {
+            for (int pairs = L / 2 - 1; pairs > 0; --pairs) {
+                arrive();
+                step(lds + wr * STAGE, lds + rd * STAGE, f0, f1);
+                next_slot();
+                arrive();
+                step(lds + wr * STAGE, lds + rd * STAGE, f1, f0);
+                next_slot();
+            }
             arrive();
             step(lds + wr * STAGE, lds + rd * STAGE, f0, f1);
-            next_slot();
-            arrive();
-            step(lds + wr * STAGE, lds + rd * STAGE, f1, f0);
-            next_slot();
         }
-        arrive();
-        step(lds + wr * STAGE, lds + rd * STAGE, f0, f1);
         Mode::template mma<FM, FN>(f1, acc);                 // the last slab
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));           // no load may land in LDS later
     }

@@ -20,6 +20,15 @@ __device__ __forceinline__ f32x4_t load4(const float *p) {
     const f32x4u_t v = *reinterpret_cast<const f32x4u_t *>(p);
     return v;
 }
+// Four values of a row from k on, zero past n.
+__device__ __forceinline__ f32x4_t row4(const float *__restrict__ row, int64_t k, int64_t n) {
+    if (k + 4 <= n) return load4(row + k);
+    f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (k + t < n) v[t] = row[k + t];
+    return v;
+}
 
 // Workgroups are handed to the 8 XCDs round-robin (workgroup id mod 8). Give
 // each XCD one contiguous range of tile ids so that the tiles sharing rows of
