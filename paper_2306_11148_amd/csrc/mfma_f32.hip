@@ -202,29 +202,19 @@ static_assert(SLAB32 * 4 == ring::REC_BYTES, "one record holds one slab of one r
 // Rows of X (rows x K, row-major) -> records; chunk q = 8 values, half a record.
 // Consecutive chunks fill one KiB record tile contiguously.
 __global__ __launch_bounds__(256) void f32_rows_kernel(const float *__restrict__ X, int64_t rows, int64_t K,
-                                                       int64_t S, int vec, uint8_t *__restrict__ P) {
+                                                       int64_t S, uint8_t *__restrict__ P) {
     const int64_t chunks = padded_rows(rows) * S * 2;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < chunks; q += (int64_t)gridDim.x * 256) {
         const int c = (int)(q & 1);
         const int64_t rr = (q >> 1) % GROUP, gs = (q >> 1) / GROUP;
         const int64_t s = gs % S, r = (gs / S) * GROUP + rr;
         const int64_t k = s * SLAB32 + c * 8;
-        float4 x0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), x1 = x0;
+        f32x4_t x0 = {0.0f, 0.0f, 0.0f, 0.0f}, x1 = x0;
         if (r < rows) {
-            if (vec && k + 8 <= K) {
-                const float4 *src = reinterpret_cast<const float4 *>(X + r * K + k);
-                x0 = src[0];
-                x1 = src[1];
-            } else {
-                float *e0 = reinterpret_cast<float *>(&x0), *e1 = reinterpret_cast<float *>(&x1);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (k + e < K) e0[e] = X[r * K + k + e];
-                    if (k + 4 + e < K) e1[e] = X[r * K + k + 4 + e];
-                }
-            }
+            x0 = row4(X + r * K, k, K);
+            x1 = row4(X + r * K, k + 4, K);
         }
-        float4 *dst = reinterpret_cast<float4 *>(P + ring::rec_byte(r, s, S) + c * 32);
+        f32x4_t *dst = reinterpret_cast<f32x4_t *>(P + ring::rec_byte(r, s, S) + c * 32);
         dst[0] = x0;
         dst[1] = x1;
     }
@@ -235,7 +225,7 @@ __global__ __launch_bounds__(256) void f32_rows_kernel(const float *__restrict__
 // so that a wave's 16-byte stores fill half of every record of two row tiles.
 // Columns past `cols` get zero records. All 256 threads take part.
 __global__ __launch_bounds__(256) void f32_cols_kernel(const float *__restrict__ X, int64_t K, int64_t cols,
-                                                       int64_t S, int vec, uint8_t *__restrict__ P) {
+                                                       int64_t S, uint8_t *__restrict__ P) {
     __shared__ __attribute__((aligned(16))) float tile[4 * SLAB32][64 + 4];
     const int t = threadIdx.x;
     const int64_t bx = blockIdx.x;
@@ -246,18 +236,9 @@ __global__ __launch_bounds__(256) void f32_cols_kernel(const float *__restrict__
         for (int i = 0; i < 4; ++i) {
             const int kk = (t >> 4) + 16 * i;
             const int64_t k = by * 4 * SLAB32 + kk;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (k < K) {
-                if (vec && j + 4 <= cols) {
-                    v = *reinterpret_cast<const float4 *>(X + k * cols + j);
-                } else {
-                    float *e = reinterpret_cast<float *>(&v);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        if (j + q < cols) e[q] = X[k * cols + j + q];
-                }
-            }
-            *reinterpret_cast<float4 *>(&tile[kk][(t & 15) * 4]) = v;
+            f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (k < K) v = row4(X + k * cols, j, cols);
+            *reinterpret_cast<f32x4_t *>(&tile[kk][(t & 15) * 4]) = v;
         }
         __syncthreads();
 #pragma unroll
@@ -385,15 +366,13 @@ hipError_t launch_mfma_f32(const moa_gemm_desc &d, const Plan &plan, void *ws, h
             // A's rows; a column-major B is a row-major p x n array whose rows
             // are B's columns.
             auto rows = [&](const float *X, int64_t r, uint8_t *P) {
-                const int vec = (d.n % 8 == 0) && ((uintptr_t)X % 16 == 0);
                 const int64_t rb = std::min<int64_t>((padded_rows(r) * S * 2 + 255) / 256, 65536);
-                hipLaunchKernelGGL(f32_rows_kernel, dim3((unsigned)rb), dim3(256), 0, st, X, r, d.n, S, vec, P);
+                hipLaunchKernelGGL(f32_rows_kernel, dim3((unsigned)rb), dim3(256), 0, st, X, r, d.n, S, P);
             };
             auto cols = [&](const float *X, int64_t c, uint8_t *P) {
-                const int vec = (c % 4 == 0) && ((uintptr_t)X % 16 == 0);
                 const int64_t by = std::min<int64_t>((S + 3) / 4, 65535);
                 hipLaunchKernelGGL(f32_cols_kernel, dim3((unsigned)((c + 63) / 64), (unsigned)by), dim3(256), 0, st,
-                                   X, d.n, c, S, vec, P);
+                                   X, d.n, c, S, P);
             };
             if (d.flags & MOA_FLAG_A_COL) cols(A, d.m, Ap); else rows(A, d.m, Ap);
             if (d.flags & MOA_FLAG_B_COL) rows(B, d.p, Bp); else cols(B, d.p, Bp);

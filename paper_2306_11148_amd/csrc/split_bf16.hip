@@ -44,8 +44,7 @@ static_assert(REC_BYTES == 2 * SLAB * 2, "one record holds hi and lo of one slab
 // Rows of X (rows x K, row-major) -> records: chunk q = 8 k values of one
 // record (2 chunks per record).
 __device__ __forceinline__ void pack_rows_chunk(const float *__restrict__ X, int64_t rows, int64_t K,
-                                                int64_t S, int vec, uint8_t *__restrict__ P,
-                                                int64_t q) {
+                                                int64_t S, uint8_t *__restrict__ P, int64_t q) {
     // q -> (row tile g, slab s, row rr in the tile, chunk c): consecutive
     // threads fill one KiB tile contiguously
     const int c = (int)(q & 1);
@@ -54,62 +53,44 @@ __device__ __forceinline__ void pack_rows_chunk(const float *__restrict__ X, int
     const int64_t s = gs % S, g = gs / S;
     const int64_t r = g * GROUP + rr;
     const int64_t k = s * SLAB + c * 8;
-    float x[8];
-    if (r >= rows) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = 0.0f;
-    } else if (vec && k + 8 <= K) {
-        const float4 *src = reinterpret_cast<const float4 *>(X + r * K + k);
-        const float4 a = src[0], b = src[1];
-        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = (k + e < K) ? X[r * K + k + e] : 0.0f;
+    f32x4_t x[2] = {};
+    if (r < rows) {
+        x[0] = row4(X + r * K, k, K);
+        x[1] = row4(X + r * K, k + 4, K);
     }
     uint4 hi, lo;
-    split_pair(x[0], x[1], &hi.x, &lo.x);
-    split_pair(x[2], x[3], &hi.y, &lo.y);
-    split_pair(x[4], x[5], &hi.z, &lo.z);
-    split_pair(x[6], x[7], &hi.w, &lo.w);
+    split_pair(x[0][0], x[0][1], &hi.x, &lo.x);
+    split_pair(x[0][2], x[0][3], &hi.y, &lo.y);
+    split_pair(x[1][0], x[1][1], &hi.z, &lo.z);
+    split_pair(x[1][2], x[1][3], &hi.w, &lo.w);
     uint8_t *rec = P + ring::rec_byte(r, s, S);
     *reinterpret_cast<uint4 *>(rec + c * 16) = hi;          // hi: bytes 0 .. 31
     *reinterpret_cast<uint4 *>(rec + 32 + c * 16) = lo;     // lo: bytes 32 .. 63
 }
 
 __global__ __launch_bounds__(256) void pack_rows_kernel(const float *__restrict__ X, int64_t rows,
-                                                        int64_t K, int64_t S, int vec,
-                                                        uint8_t *__restrict__ P) {
+                                                        int64_t K, int64_t S, uint8_t *__restrict__ P) {
     const int64_t chunks = padded_rows(rows) * S * 2;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < chunks; q += (int64_t)gridDim.x * 256)
-        pack_rows_chunk(X, rows, K, S, vec, P, q);
+        pack_rows_chunk(X, rows, K, S, P, q);
 }
 
 // Columns of X (K x cols, row-major) -> records (transposed), 64 columns x
 // 64 k (4 slabs) per block through LDS: reads of X rows are contiguous
 // float4s and each thread writes two half records. Columns past
 // `cols` get zero records. All 256 threads must take part.
-struct ColBlockRegs { float4 v[4]; };
+struct ColBlockRegs { f32x4_t v[4]; };
 
 __device__ __forceinline__ void pack_cols_load(const float *__restrict__ X, int64_t K, int64_t cols,
-                                               int64_t bx, int64_t by, int vec, ColBlockRegs &r) {
+                                               int64_t bx, int64_t by, ColBlockRegs &r) {
     const int t = threadIdx.x;
     const int jq = (t & 15) * 4;                 // four columns 4 (t%16) .. +3
     const int64_t j = bx * 64 + jq;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int64_t k = by * 4 * SLAB + (t >> 4) + 16 * i;
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (k < K) {
-            if (vec && j + 4 <= cols) {
-                v = *reinterpret_cast<const float4 *>(X + k * cols + j);
-            } else {
-                float *e = reinterpret_cast<float *>(&v);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (j + q < cols) e[q] = X[k * cols + j + q];
-            }
-        }
+        f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k < K) v = row4(X + k * cols, j, cols);
         r.v[i] = v;
     }
 }
@@ -126,7 +107,7 @@ __device__ __forceinline__ void pack_cols_emit(const ColBlockRegs &r, int64_t co
     const int t = threadIdx.x;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        *reinterpret_cast<float4 *>(&tile[(t >> 4) + 16 * i][(t & 15) * 4]) = r.v[i];
+        *reinterpret_cast<f32x4_t *>(&tile[(t >> 4) + 16 * i][(t & 15) * 4]) = r.v[i];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -148,30 +129,21 @@ __device__ __forceinline__ void pack_cols_emit(const ColBlockRegs &r, int64_t co
     __syncthreads();                             // tile free for the next block
 }
 
-__device__ __forceinline__ void pack_cols_block(const float *__restrict__ X, int64_t K, int64_t cols,
-                                                int64_t S, uint8_t *__restrict__ P, int64_t bx,
-                                                int64_t by, float (*tile)[64 + 4], int vec) {
-    ColBlockRegs r;
-    pack_cols_load(X, K, cols, bx, by, vec, r);
-    pack_cols_emit(r, cols, S, P, bx, by, tile);
-}
-
 // Each workgroup walks up to COL_BLOCKS consecutive 64-k blocks of one
 // 64-column strip, loading block b+1 while it writes block b.
 constexpr int COL_BLOCKS = 4;
 
 __global__ __launch_bounds__(256) void pack_cols_kernel(const float *__restrict__ X, int64_t K,
-                                                        int64_t cols, int64_t S, int vec,
-                                                        uint8_t *__restrict__ P) {
+                                                        int64_t cols, int64_t S, uint8_t *__restrict__ P) {
     __shared__ __attribute__((aligned(16))) float tile[4 * SLAB][64 + 4];
     const int64_t by_count = (S + 3) / 4;
     const int64_t bx = blockIdx.x;
     for (int64_t by0 = (int64_t)blockIdx.y * COL_BLOCKS; by0 < by_count; by0 += (int64_t)gridDim.y * COL_BLOCKS) {
         const int64_t by_end = min(by0 + COL_BLOCKS, by_count);
         ColBlockRegs cur, next;
-        pack_cols_load(X, K, cols, bx, by0, vec, cur);
+        pack_cols_load(X, K, cols, bx, by0, cur);
         for (int64_t by = by0; by < by_end; ++by) {
-            if (by + 1 < by_end) pack_cols_load(X, K, cols, bx, by + 1, vec, next);
+            if (by + 1 < by_end) pack_cols_load(X, K, cols, bx, by + 1, next);
             pack_cols_emit(cur, cols, S, P, bx, by, tile);
             cur = next;
         }
@@ -414,12 +386,13 @@ hipError_t launch_raw_splitk(const moa_gemm_desc &d, int chunks, float *partials
 }
 
 // The block a product takes without conditioning, -1 for the conditioned path:
-// the one whose busiest CU is done first, for products of at most three 128 x
-// 128 blocks per CU. Beyond that the record ring's larger blocks gain more than
-// the two conditioning launches cost (us, without / with conditioning: 192 x
-// 320 x 160 8 / 26, 512^3 11 / 29, 1024^3 21 / 46, 1531 x 2029 x 1237 48 / 84,
-// 2048^3 65 / 80, 3072^3 230 / 230, 4096^3 434 / 355). Operands whose offsets
-// inside a block exceed 32 bits stay on the conditioned path.
+// the one whose busiest CU is done first, unless the record ring, whose step is
+// shorter, makes up for its conditioning (two launches, each operand read and
+// written once at 4.6 TB/s); beyond three 128 x 128 blocks per CU the ring's
+// larger blocks always do (us, without / with conditioning: 192 x 320 x 160 8 /
+// 26, 1024^3 21 / 38, 2048^3 64 / 68, 3072 x 1024 x 3072 79 / 82, 2560^3 124 /
+// 112, 2048 x 8192 x 2048 239 / 223, 3072^3 227 / 192, 4096^3 434 / 343). Operands
+// whose offsets inside a block exceed 32 bits stay on the conditioned path.
 int split_raw_block(const moa_gemm_desc &d) {
     if (((d.m + 127) / 128) * ((d.p + 127) / 128) > 3 * kNumCUs) return -1;
     int best = -1;
@@ -437,7 +410,11 @@ int split_raw_block(const moa_gemm_desc &d) {
             best_ns = ns;
         }
     }
-    return best;
+    // the ring's 128 x 128 blocks: fitted like kRaw
+    const double slabs = (double)((d.n + SLAB - 1) / SLAB);
+    const double rounds = (double)((((d.m + 127) / 128) * ((d.p + 127) / 128) + kNumCUs - 1) / kNumCUs);
+    const double records = 20000 + 8.0 * (double)d.n * (double)(d.m + d.p) / 4600 + slabs * (80 + 235 * rounds);
+    return slabs * best_ns <= records ? best : -1;
 }
 
 // Split-k products: likewise, at most three 128 x 128 blocks per CU (512 x 32768
@@ -486,17 +463,15 @@ void split_bf16_shape(int v, Plan *p) {
 namespace {
 // Records of the `rows` rows of a row-major rows x K array.
 void rows_records(const float *X, int64_t rows, int64_t K, int64_t S, uint8_t *P, hipStream_t st) {
-    const int vec = (K % 8 == 0) && ((uintptr_t)X % 16 == 0);
     int64_t blocks = (padded_rows(rows) * S * 2 + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, X, rows, K, S, vec, P);
+    hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, X, rows, K, S, P);
 }
 // Records of the `cols` columns of a row-major K x cols array.
 void cols_records(const float *X, int64_t K, int64_t cols, int64_t S, uint8_t *P, hipStream_t st) {
-    const int vec = (cols % 4 == 0) && ((uintptr_t)X % 16 == 0);
     const int64_t by = ((S + 3) / 4 + COL_BLOCKS - 1) / COL_BLOCKS;
     hipLaunchKernelGGL(pack_cols_kernel, dim3((unsigned)((cols + 63) / 64), (unsigned)(by < 65535 ? by : 65535)),
-                       dim3(256), 0, st, X, K, cols, S, vec, P);
+                       dim3(256), 0, st, X, K, cols, S, P);
 }
 }  // namespace
 
