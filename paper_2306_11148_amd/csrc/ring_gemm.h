@@ -287,51 +287,98 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     }
 
     // Epilogue: register r of lane l holds C[8(r/4) + 4(l/32) + r%4][l%32] of
-    // each 32x32 block; 32 lanes write one 128-byte run of a row of C. C is
-    // addressed as global memory: a generic (flat) access could alias LDS and
-    // would have to wait for the direct loads still in flight.
-    global_f32 *C = (global_f32 *)op.C;
-    const global_i32 *row_exp = (const global_i32 *)op.row_exp;
-    const global_i32 *col_exp = (const global_i32 *)op.col_exp;
-    // The accumulate form reads a block's 16 values of C before any store, so
-    // the loads are in flight together; the other forms have no trace of it.
+    // each 32x32 block; 32 lanes write one 128-byte run of a row of C. All loads
+    // (exponents; the accumulate form's values of C, a block at a time) come
+    // before the stores that need them: a load between two stores waits for
+    // both (with the row's exponent loaded before each store the FP8 product
+    // 3001 x 2777 x 1999, one term, took 50 us, now 45). Buffer
+    // resources end at row m, and columns past p get an offset beyond every
+    // range, so no access needs a branch; one resource per 8 rows of C keeps
+    // the offsets below 2^31 up to p = 2^26.
+    float *dst = partial ? partial : op.C;
+    const bool descale = Mode::SCALED && !partial;
+    const int64_t iw = i0 + wm * WM, jw = j0 + wn * WN;      // the wave's part of C
+    auto rsrc_of = [](const void *base, int64_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, bytes > 0 ? (int)bytes : 0, 0x00020000);
+    };
     auto epilogue = [&](auto acc_form) {
         constexpr bool ACC = decltype(acc_form)::value;
+        const int pb = (int)(p * 4);
+        const int vrow = (lane >> 5) * 4 * pb;
+        int fj[FN];
+        if constexpr (Mode::SCALED) {
+            const __amdgpu_buffer_rsrc_t cols = rsrc_of(op.col_exp + jw, descale ? (p - jw < WN ? p - jw : WN) * 4 : 0);
+#pragma unroll
+            for (int b = 0; b < FN; ++b)
+                fj[b] = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, (b * 32 + (lane & 31)) * 4, 0, 0);
+        }
+#pragma unroll
+        for (int a = 0; a < FM; ++a) {
+            const int64_t ia = iw + a * 32;
+            i32x4_t ei[4];                                   // rows 8 g + 4 (lane / 32) .. + 3
+            if constexpr (Mode::SCALED) {
+                // whole quads: the exponents' array is padded to 256 bytes
+                const int64_t quads = m - ia < 32 ? (m - ia + 3) / 4 : 8;
+                const __amdgpu_buffer_rsrc_t rows = rsrc_of(op.row_exp + ia, descale ? quads * 16 : 0);
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    ei[g] = __builtin_bit_cast(i32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rows, (8 * g + 4 * (lane >> 5)) * 4, 0, 0));
+            }
+#pragma unroll
+            for (int b = 0; b < FN; ++b) {
+                const int64_t j = jw + b * 32 + (lane & 31);
+                const int vj = j < p ? (b * 32 + (lane & 31)) * 4 + vrow : kDeadVoffset;
+                auto c_rows = [&](int g) {                   // rows ia + 8 g .. + 7, from column jw on
+                    const int64_t i = ia + 8 * g, rows = m - i < 8 ? m - i : 8;
+                    return rsrc_of(dst + i * p + jw, rows > 0 ? rows * pb - jw * 4 : 0);
+                };
+                float old[16];
+                if constexpr (ACC) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        old[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                               c_rows(r >> 2), vj + (r & 3) * pb, 0, 0));
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float v = acc[a][b][r];
+                    if constexpr (Mode::SCALED) v = ldexpf(v, -(ei[r >> 2][r & 3] + fj[b]));
+                    if constexpr (ACC) v += old[r];
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), c_rows(r >> 2),
+                                                          vj + (r & 3) * pb, 0, 0);
+                }
+            }
+        }
+    };
+    // p beyond 2^26: 64-bit addresses. C is addressed as global memory: a generic
+    // (flat) access could alias LDS.
+    auto wide_epilogue = [&] {
+        global_f32 *C = (global_f32 *)dst;
+        const global_i32 *row_exp = (const global_i32 *)op.row_exp;
+        const global_i32 *col_exp = (const global_i32 *)op.col_exp;
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
             for (int b = 0; b < FN; ++b) {
-                const int64_t j = j0 + wn * WN + b * 32 + (lane & 31);
-                if (j >= op.p) continue;
-                const int fj = Mode::SCALED && !partial ? col_exp[j] : 0;
-                float old[16];
-                if constexpr (ACC) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int64_t i = i0 + wm * WM + a * 32 + mfma32_row(r, lane);
-                        if (i < op.m) old[r] = C[i * op.p + j];
-                    }
-                }
+                const int64_t j = jw + b * 32 + (lane & 31);
+                if (j >= p) continue;
+                const int fj = descale ? col_exp[j] : 0;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const int64_t i = i0 + wm * WM + a * 32 + mfma32_row(r, lane);
-                    if (i < op.m) {
+                    const int64_t i = iw + a * 32 + mfma32_row(r, lane);
+                    if (i < m) {
                         float v = acc[a][b][r];
-                        if (partial) {
-                            ((global_f32 *)partial)[i * op.p + j] = v;
-                            continue;
-                        }
-                        if constexpr (Mode::SCALED) v = ldexpf(v, -(row_exp[i] + fj));
-                        if constexpr (ACC) v += old[r];
-                        C[i * op.p + j] = v;
+                        if (descale) v = ldexpf(v, -(row_exp[i] + fj));
+                        if (op.accumulate && !partial) v += C[i * p + j];
+                        C[i * p + j] = v;
                     }
                 }
             }
     };
-    if (op.accumulate && !partial)
-        epilogue(std::true_type{});
-    else
-        epilogue(std::false_type{});
+    if (p >= (int64_t(1) << 26)) wide_epilogue();
+    else if (op.accumulate && !partial) epilogue(std::true_type{});
+    else epilogue(std::false_type{});
 #endif
 }
 

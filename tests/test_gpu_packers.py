@@ -33,3 +33,20 @@ def test_rows_and_columns_agree(path, shape):
         assert torch.equal(C, ref), f"a_col {a_col}, b_col {b_col}, offset {offset}"
     bound = 2e-5 * (A.double().abs() @ B.double().abs())       # both paths hold 1e-5 normwise
     assert ((ref.double() - A.double() @ B.double()).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("path", ["split_bf16", "fp8"])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_rows_of_c_beyond_buffer_offsets(path, accumulate):
+    """p at and past 2^26, where C is written with 64-bit addresses: the same bits as a narrow slice of the product."""
+    for p in ((1 << 26) - 1, (1 << 26) + 5):
+        m, n, w = 9, 3, 300
+        g = torch.Generator(device=DEV).manual_seed(p)
+        A, B = torch.randn(m, n, generator=g, device=DEV), torch.randn(n, p, generator=g, device=DEV)
+        C = torch.ones(m, p, device=DEV)
+        moa.moa_gemm(A, B, C, path=path, accumulate=accumulate, flags=moa.MOA_FLAG_VARIANT(0))
+        for at in (0, p // 2, p - w):
+            R = torch.ones(m, w, device=DEV)
+            moa.moa_gemm(A, B[:, at:at + w].contiguous(), R, path=path, accumulate=accumulate,
+                         flags=moa.MOA_FLAG_VARIANT(0))
+            assert torch.equal(C[:, at:at + w], R), f"p {p}, columns from {at}"
