@@ -43,7 +43,6 @@ static_assert(REC_BYTES == SLAB8, "one record holds one slab of codes");
 constexpr int kScaleOne = 0x7f;          // 2^0 (0 would mean 2^-127)
 constexpr int kScaleLo = 0x7f - 4;       // 2^-4: residual codes carry a factor 2^4
 
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int pow2_exponent(float amax) {
     if (!(amax > 0.0f)) return 0;
@@ -188,16 +187,25 @@ __device__ __forceinline__ void condition_row(const float *__restrict__ A, int64
     }
 }
 
-// Four rows per workgroup; clears `count` words at `clear` on the way (the
-// column amax of the other operand).
+// The rows of one operand and where they go. `blocks`: workgroups of four rows.
+struct RowsJob {
+    const float *X;
+    int64_t rows, blocks;
+    int32_t *e;
+    uint8_t *q, *l;
+};
+
+// Four rows of n values per workgroup: the rows of one job, then those of a
+// second one (no blocks: none). Clears `count` words at `clear` on the way (the
+// column amax of an operand taken by columns).
 template <bool TWO, int J>
-__global__ __launch_bounds__(256) void rows_fp8_kernel(const float *__restrict__ A, int64_t m, int64_t n, int64_t S,
-                                                       int32_t *__restrict__ e, uint8_t *__restrict__ qa,
-                                                       uint8_t *__restrict__ la, uint32_t *__restrict__ clear,
-                                                       int64_t count) {
+__global__ __launch_bounds__(256) void rows_fp8_kernel(RowsJob first, RowsJob second, int64_t n, int64_t S,
+                                                       uint32_t *__restrict__ clear, int64_t count) {
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < count; t += (int64_t)gridDim.x * 256) clear[t] = 0u;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i < padded_rows(m)) condition_row<TWO, J>(A, i, m, n, S, threadIdx.x & 63, e, qa, la);
+    const bool of_first = blockIdx.x < first.blocks;
+    const RowsJob d = of_first ? first : second;
+    const int64_t i = ((int64_t)blockIdx.x - (of_first ? 0 : first.blocks)) * 4 + (threadIdx.x >> 6);
+    if (i < padded_rows(d.rows)) condition_row<TWO, J>(d.X, i, d.rows, n, S, threadIdx.x & 63, d.e, d.q, d.l);
 }
 
 // Rows of A -> records, exponents given. Chunk q = 16 codes of one record (4
@@ -668,29 +676,38 @@ void scales(const float *A, int64_t m, int64_t n, const float *B, int64_t p, int
                            dim3(256), 0, st, B, n, p, amaxB);
 }
 
-// Exponents and records of one operand whose wanted vectors are the rows of X
-// (rows x K): A's rows, or a column-major B's columns. Clears `count` words at
-// `clear` on the way. The smallest J that holds a row: registers (28, 42, 74 and
-// 138) set the waves per SIMD. Beyond 8192 values a row would leave one wave
-// per SIMD, and two passes with a workgroup per row do better.
+RowsJob rows_job(const float *X, int64_t rows, int32_t *e, uint8_t *q, uint8_t *l) {
+    return {X, rows, padded_rows(rows) / 4, e, q, l};
+}
+
+// Exponents and records of operands whose wanted vectors are the rows (of K
+// values) of an array: A's rows, a column-major B's columns, or both in one
+// launch. Clears `count` words at `clear` on the way. The smallest J that holds
+// a row: registers (28, 42, 74 and 138) set the waves per SIMD. Beyond 8192
+// values a row would take over 256 registers, one wave per SIMD: two passes
+// there, a workgroup per row.
 template <bool TWO>
-void row_records(const float *X, int64_t rows, int64_t K, int64_t S, int32_t *exps, uint8_t *q, uint8_t *l,
-                 uint32_t *clear, int64_t count, hipStream_t st) {
-    const dim3 grid((unsigned)((padded_rows(rows) + 3) / 4)), bl(256);
+void row_records(const RowsJob &a, const RowsJob &b, int64_t K, int64_t S, uint32_t *clear, int64_t count,
+                 hipStream_t st) {
+    const dim3 grid((unsigned)(a.blocks + b.blocks)), bl(256);
     if (K <= 1024) {
-        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 4>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 4>), grid, bl, 0, st, a, b, K, S, clear, count);
     } else if (K <= 2048) {
-        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 8>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 8>), grid, bl, 0, st, a, b, K, S, clear, count);
     } else if (K <= 4096) {
-        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 16>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 16>), grid, bl, 0, st, a, b, K, S, clear, count);
     } else if (K <= 8192) {
-        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 32>), grid, bl, 0, st, X, rows, K, S, exps, q, l, clear, count);
+        hipLaunchKernelGGL((rows_fp8_kernel<TWO, 32>), grid, bl, 0, st, a, b, K, S, clear, count);
     } else {
         if (count > 0)
             hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((count + 255) / 256)), bl, 0, st, clear, count);
-        hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)rows), bl, 0, st, X, K, exps);
-        const int64_t blocks = std::min<int64_t>((padded_rows(rows) * S * 4 + 255) / 256, 65536);
-        hipLaunchKernelGGL(pack_rows_fp8_kernel<TWO>, dim3((unsigned)blocks), bl, 0, st, X, rows, K, S, exps, q, l);
+        for (const RowsJob *d : {&a, &b}) {
+            if (d->blocks == 0) continue;
+            hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)d->rows), bl, 0, st, d->X, K, d->e);
+            const int64_t blocks = std::min<int64_t>((padded_rows(d->rows) * S * 4 + 255) / 256, 65536);
+            hipLaunchKernelGGL(pack_rows_fp8_kernel<TWO>, dim3((unsigned)blocks), bl, 0, st, d->X, d->rows, K, S, d->e,
+                               d->q, d->l);
+        }
     }
 }
 
@@ -721,8 +738,10 @@ hipError_t pack_records(const moa_gemm_desc &d, const Fp8Workspace &w, hipStream
         const int64_t words = align256(4 * d.p) / 4 + d.m;
         hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, w.amaxB, words);
     }
-    if (a_rows) row_records<TWO>(A, d.m, d.n, S, w.e, w.qA, w.lA, w.amaxB, b_rows ? 0 : d.p, st);
-    if (b_rows) row_records<TWO>(B, d.p, d.n, S, w.f, w.qB, w.lB, w.amaxA, a_rows ? 0 : d.m, st);
+    const RowsJob a = rows_job(A, d.m, w.e, w.qA, w.lA), b = rows_job(B, d.p, w.f, w.qB, w.lB), none{};
+    if (a_rows && b_rows) row_records<TWO>(a, b, d.n, S, nullptr, 0, st);
+    else if (a_rows) row_records<TWO>(a, none, d.n, S, w.amaxB, d.p, st);
+    else if (b_rows) row_records<TWO>(b, none, d.n, S, w.amaxA, d.m, st);
     if (!a_rows) col_records<TWO>(A, d.m, d.n, S, w.amaxA, w.e, w.qA, w.lA, st);
     if (!b_rows) col_records<TWO>(B, d.p, d.n, S, w.amaxB, w.f, w.qB, w.lB, st);
     return hipGetLastError();
