@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void col_amax_kernel(const float *__restrict__
 // launch in place of two each; all of a lane's loads are in flight together, at
 // any 4-byte alignment (3001 x 2777 rows: exponents and codes were 15 + 13.5 us
 // with scalar loads for the odd length, the product of two such operands, one
-// term, 99 us and now 54).
+// term, 99 us and now 41).
 template <bool TWO, int J>
 __device__ __forceinline__ void condition_row(const float *__restrict__ A, int64_t i, int64_t m, int64_t n, int64_t S,
                                               int lane, int32_t *__restrict__ e, uint8_t *__restrict__ qa,
@@ -558,8 +558,8 @@ constexpr Fp8Shape kOne[] = {{128, 128, 64, 64, 3}, {256, 256, 128, 64, 3}, {256
 // to the latency of its loads.
 // The rectangular two-term blocks (8 waves of 64 x 64, 144 KB ring) read a
 // third less LDS per matrix-core step than 128 x 128 with 64 x 32 waves.
-// 256 x 128 is the default for large products (8192 x 4096 x 8192: 777 us vs 880-950 us for 128 x 128;
-// 834 us with four waves of 128 x 64, one per SIMD).
+// (8192 x 4096 x 8192: 714 us, 128 x 256, and 732, 256 x 128, against 840-858; four
+// waves of 128 x 64, one per SIMD, were slower, 834 when eight took 777).
 constexpr Fp8Shape kTwo[] = {{128, 128, 64, 64, 3}, {128, 128, 64, 32, 3}, {128, 128, 64, 32, 5},
                              {128, 128, 64, 32, 4}, {128, 256, 64, 64, 3}, {256, 128, 64, 64, 3}};
 constexpr int kOneCount = sizeof(kOne) / sizeof(kOne[0]);

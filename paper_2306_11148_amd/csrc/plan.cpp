@@ -290,17 +290,32 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
         } else if ((v = tuned_variant(d, pl.path)) >= 0) {
             pl.tuned = true;
         } else {
-            v = 0;
-            for (int c = nv - 1; c >= 0; --c) {
+            auto rounds = [&](int c) {
                 Plan t;
                 fp8_shape(two, c, &t);
-                if (tiles_for(d.m, d.p, t.tile_m, t.tile_n) >= kNumCUs) { v = c; break; }
-            }
-            if (!two) {
-                // one term: when the 256 x 256 blocks fill more than one round of
-                // the CUs but leave the last round less than 40% full, the
-                // 128 x 128 blocks (three per CU) finish sooner (measured N = 6144:
-                // 0.24 vs 0.27 ms, 7168: 0.40 vs 0.42 ms)
+                return (tiles_for(d.m, d.p, t.tile_m, t.tile_n) + kNumCUs - 1) / kNumCUs;
+            };
+            if (two) {
+                // 128 x 128, with eight waves once it fills the CUs; the
+                // rectangular blocks (128 x 256, else 256 x 128) take 1.75 of its
+                // time each and are the choice where their rounds of the CUs come
+                // out shorter (us, 128 x 128 / 128 x 256 / 256 x 128: 2048^3 48 / 57 /
+                // 56, 2560^3 78 / 71 / 71, 3072^3 120 / 129 / 129, 3001 x 2777 x 1999
+                // 87 / 79 / 79, 8192 x 4096 x 8192 858 / 714 / 732)
+                const int64_t square = rounds(3), flat = rounds(4), tall = rounds(5);
+                v = tiles_for(d.m, d.p, 128, 128) >= kNumCUs ? 3 : 0;
+                if (7 * std::min(flat, tall) <= 4 * square) v = flat <= tall ? 4 : 5;
+            } else {
+                v = 0;
+                for (int c = nv - 1; c >= 0; --c) {
+                    Plan t;
+                    fp8_shape(two, c, &t);
+                    if (tiles_for(d.m, d.p, t.tile_m, t.tile_n) >= kNumCUs) { v = c; break; }
+                }
+                // when the 256 x 256 blocks fill more than one round of the CUs
+                // but leave the last round less than 40% full, the 128 x 128
+                // blocks (three per CU) finish sooner (measured N = 6144: 0.24 vs
+                // 0.27 ms, 7168: 0.40 vs 0.42 ms)
                 Plan t;
                 fp8_shape(two, v, &t);
                 const int64_t big = tiles_for(d.m, d.p, t.tile_m, t.tile_n), tail = big % kNumCUs;

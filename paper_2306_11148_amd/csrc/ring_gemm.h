@@ -216,9 +216,9 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     // the next barrier, so that the wait for the loads came right after their
     // issue with nothing in between. With the steps kept apart, one more slab in
     // flight, no branch in the loop and the loads spread over the step like the
-    // reads, the FP8 product 8192 x 4096 x 8192 takes 770 us (two terms; was 849)
-    // and the split-BF16 product of order 8192, whose steps had stayed in place,
-    // 2364 (2430; 2416 with all of a step's loads at its start).
+    // reads, the FP8 product 8192 x 4096 x 8192 went from 849 to 762 us (two
+    // terms) and the split-BF16 product of order 8192, whose steps had stayed in
+    // place, from 2430 to 2350 (2416 with all of a step's loads at its start).
     auto arrive = [] {
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(waitcnt_vm((NSTAGE - 2) * LPW) & ~(0xF << 8));
