@@ -93,18 +93,23 @@ __device__ __forceinline__ float wave_max(float mx) {
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     return mx;
 }
-// e_i of every row of A, one workgroup per row.
-__global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ A, int64_t n,
+// e_i of every row of A, one workgroup per row (at most ROW_BLOCKS: a launch
+// holds fewer than 2^32 threads).
+constexpr int64_t ROW_BLOCKS = 1 << 20;
+__global__ __launch_bounds__(256) void row_exp_kernel(const float *__restrict__ A, int64_t m, int64_t n,
                                                       int32_t *__restrict__ e) {
     __shared__ float part[4];
-    const float *row = A + (int64_t)blockIdx.x * n;
-    float mx = 0.0f;
+    for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
+        const float *row = A + i * n;
+        float mx = 0.0f;
 #pragma unroll 8
-    for (int64_t k = (int64_t)threadIdx.x * 4; k < n; k += 1024) mx = fmaxf(mx, amax4(row4(row, k, n)));
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) e[blockIdx.x] = pow2_exponent(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
+        for (int64_t k = (int64_t)threadIdx.x * 4; k < n; k += 1024) mx = fmaxf(mx, amax4(row4(row, k, n)));
+        mx = wave_max(mx);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
+        __syncthreads();
+        if (threadIdx.x == 0) e[i] = pow2_exponent(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
+        __syncthreads();                           // part free for the next row
+    }
 }
 
 // Column amax of B: a workgroup takes 256 columns (four per lane) over a band
@@ -145,7 +150,7 @@ __device__ __forceinline__ void col_amax_block(const float *__restrict__ B, int6
 __global__ __launch_bounds__(256) void col_amax_kernel(const float *__restrict__ B, int64_t n,
                                                        int64_t p, uint32_t *__restrict__ amax) {
     __shared__ __attribute__((aligned(16))) float part[4][256];
-    col_amax_block(B, n, p, blockIdx.x, blockIdx.y, amax, part);
+    for (int64_t by = blockIdx.y; by * COL_BAND < n; by += gridDim.y) col_amax_block(B, n, p, blockIdx.x, by, amax, part);
 }
 
 // --------------------------------------------------- record conditioning --
@@ -613,12 +618,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, TWO ? 1 : 2) void fp8_g
 // C of the members with a split k walk from their chunks' partials, in chunk
 // order and descaled as ring::splitk_reduce_kernel does, 1024 elements per block.
 constexpr int SUM_BLOCK = 1024;
-__global__ __launch_bounds__(256) void fp8_sums_kernel(const Fp8Member *__restrict__ g, int count) {
+__global__ __launch_bounds__(256) void fp8_sums_kernel(const Fp8Member *__restrict__ g, int count, int64_t total) {
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= total) return;
     // sum_first counts the blocks of the members before: the last member that
     // starts at or before this block owns it (an unsplit one takes no blocks)
-    const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::sum_first>(g, count, (int64_t)blockIdx.x));
+    const int k = __builtin_amdgcn_readfirstlane(find_member<&Fp8Member::sum_first>(g, count, block));
     const Fp8Member &d = g[k];
-    const int64_t mp = d.m * d.p, x0 = ((int64_t)blockIdx.x - d.sum_first) * SUM_BLOCK;
+    const int64_t mp = d.m * d.p, x0 = (block - d.sum_first) * SUM_BLOCK;
     if (d.p % 4 == 0 && (uintptr_t)d.op.C % 16 == 0) {
         const int64_t x = x0 + threadIdx.x * 4;
         if (x < mp) {
@@ -666,14 +673,20 @@ Fp8Workspace carve(void *ws, int64_t m, int64_t n, int64_t p, bool two) {
     return w;
 }
 
+// Amax of the columns of X (K x cols) into `amax`, which holds zeros.
+void col_amax(const float *X, int64_t K, int64_t cols, uint32_t *amax, hipStream_t st) {
+    if (K <= 0 || cols <= 0) return;
+    const dim3 grid((unsigned)((cols + 255) / 256), (unsigned)std::min<int64_t>((K + COL_BAND - 1) / COL_BAND, 32768));
+    hipLaunchKernelGGL(col_amax_kernel, grid, dim3(256), 0, st, X, K, cols, amax);
+}
+
 // Exponents of A's rows and amax of B's columns.
 void scales(const float *A, int64_t m, int64_t n, const float *B, int64_t p, int32_t *e, uint32_t *amaxB,
             hipStream_t st) {
     if (p > 0) hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((p + 255) / 256)), dim3(256), 0, st, amaxB, p);
-    if (m > 0) hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)m), dim3(256), 0, st, A, n, e);
-    if (p > 0 && n > 0)
-        hipLaunchKernelGGL(col_amax_kernel, dim3((unsigned)((p + 255) / 256), (unsigned)((n + COL_BAND - 1) / COL_BAND)),
-                           dim3(256), 0, st, B, n, p, amaxB);
+    if (m > 0)
+        hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)std::min(m, ROW_BLOCKS)), dim3(256), 0, st, A, m, n, e);
+    col_amax(B, n, p, amaxB, st);
 }
 
 RowsJob rows_job(const float *X, int64_t rows, int32_t *e, uint8_t *q, uint8_t *l) {
@@ -703,7 +716,8 @@ void row_records(const RowsJob &a, const RowsJob &b, int64_t K, int64_t S, uint3
             hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((count + 255) / 256)), bl, 0, st, clear, count);
         for (const RowsJob *d : {&a, &b}) {
             if (d->blocks == 0) continue;
-            hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)d->rows), bl, 0, st, d->X, K, d->e);
+            hipLaunchKernelGGL(row_exp_kernel, dim3((unsigned)std::min(d->rows, ROW_BLOCKS)), bl, 0, st, d->X, d->rows, K,
+                               d->e);
             const int64_t blocks = std::min<int64_t>((padded_rows(d->rows) * S * 4 + 255) / 256, 65536);
             hipLaunchKernelGGL(pack_rows_fp8_kernel<TWO>, dim3((unsigned)blocks), bl, 0, st, d->X, d->rows, K, S, d->e,
                                d->q, d->l);
@@ -715,9 +729,7 @@ void row_records(const RowsJob &a, const RowsJob &b, int64_t K, int64_t S, uint3
 template <bool TWO>
 void col_records(const float *X, int64_t cols, int64_t K, int64_t S, uint32_t *amax, int32_t *exps, uint8_t *q,
                  uint8_t *l, hipStream_t st) {
-    if (K > 0)
-        hipLaunchKernelGGL(col_amax_kernel, dim3((unsigned)((cols + 255) / 256), (unsigned)((K + COL_BAND - 1) / COL_BAND)),
-                           dim3(256), 0, st, X, K, cols, amax);
+    col_amax(X, K, cols, amax, st);
     // also when S == 0: the epilogue reads the exponents
     const dim3 grid((unsigned)((cols + 63) / 64), (unsigned)(S < 1 ? 1 : S > 65535 ? 65535 : S));
     hipLaunchKernelGGL(pack_cols_fp8_kernel<TWO>, grid, dim3(256), 0, st, X, K, cols, S, amax, exps, q, l);
@@ -917,8 +929,7 @@ hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork
             hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((w.clear_words + 255) / 256)), dim3(256), 0, st,
                                reinterpret_cast<uint32_t *>(base), w.clear_words);
         if (w.row_items > 0) {
-            const int64_t wide = std::min<int64_t>(w.row_items, 1 << 20);
-            const dim3 grid((unsigned)wide, (unsigned)((w.row_items + wide - 1) / wide));
+            const dim3 grid = item_grid(w.row_items);
             if (two) hipLaunchKernelGGL(grouped_rows_kernel<true>, grid, dim3(256), 0, st, dev, count, w.row_items);
             else hipLaunchKernelGGL(grouped_rows_kernel<false>, grid, dim3(256), 0, st, dev, count, w.row_items);
         }
@@ -945,7 +956,7 @@ hipError_t fp8_grouped_enqueue(void *ws, int count, bool two, const Fp8GroupWork
         }
     }
     if (w.sum_items > 0)
-        hipLaunchKernelGGL(fp8_sums_kernel, dim3((unsigned)w.sum_items), dim3(256), 0, st, dev, count);
+        hipLaunchKernelGGL(fp8_sums_kernel, item_grid(w.sum_items), dim3(256), 0, st, dev, count, w.sum_items);
     return hipGetLastError();
 }
 

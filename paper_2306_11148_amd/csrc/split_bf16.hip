@@ -279,11 +279,13 @@ __global__ __launch_bounds__(256, 2) void split_grouped_kernel(const GroupMember
 // Sums of the split members' chunk partials: block b works on the last member
 // whose first_block is at most b, 1024 elements per block.
 constexpr int SUM_BLOCK = 1024;
-__global__ __launch_bounds__(256) void split_sums_kernel(const SplitSum *__restrict__ sums, int count) {
+__global__ __launch_bounds__(256) void split_sums_kernel(const SplitSum *__restrict__ sums, int count, int64_t total) {
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= total) return;
     int k = 0;
-    while (k + 1 < count && sums[k + 1].first_block <= (int64_t)blockIdx.x) ++k;
+    while (k + 1 < count && sums[k + 1].first_block <= block) ++k;
     const SplitSum d = sums[__builtin_amdgcn_readfirstlane(k)];
-    const int64_t x0 = ((int64_t)blockIdx.x - d.first_block) * SUM_BLOCK;
+    const int64_t x0 = (block - d.first_block) * SUM_BLOCK;
     if (d.mp % 4 == 0 && (uintptr_t)d.C % 16 == 0) {
         const int64_t x = x0 + threadIdx.x * 4;
         if (x < d.mp) ring::splitk_sum<4>(d.partials, d.chunks, d.mp, x, d.C, 0, nullptr, d.accumulate);
@@ -728,8 +730,9 @@ hipError_t launch_persistent(void *ws, const SplitGroup &g, const GroupedWork &w
         }
     }
     if (work.sum_blocks > 0)
-        hipLaunchKernelGGL(split_sums_kernel, dim3((unsigned)work.sum_blocks), dim3(256), 0, st,
-                           reinterpret_cast<const SplitSum *>(base + 256 + at.sums), (int)g.sums.size());
+        hipLaunchKernelGGL(split_sums_kernel, item_grid(work.sum_blocks), dim3(256), 0, st,
+                           reinterpret_cast<const SplitSum *>(base + 256 + at.sums), (int)g.sums.size(),
+                           work.sum_blocks);
     return hipGetLastError();
 }
 

@@ -31,6 +31,14 @@ __device__ __forceinline__ f32x4_t row4(const float *__restrict__ row, int64_t k
     return v;
 }
 
+// A grid of one workgroup per item (item = blockIdx.y gridDim.x + blockIdx.x,
+// the last row of it partly past the end): a launch holds fewer than 2^32
+// threads in x.
+inline dim3 item_grid(int64_t items) {
+    const int64_t wide = items < (1 << 20) ? items : 1 << 20;
+    return dim3((unsigned)wide, (unsigned)((items + wide - 1) / wide));
+}
+
 // Workgroups are handed to the 8 XCDs round-robin (workgroup id mod 8). Give
 // each XCD one contiguous range of tile ids so that the tiles sharing rows of
 // A and columns of B run under the same L2. Bijective for any tile count.

@@ -78,3 +78,34 @@ def test_grouped_members_that_split_k(terms):
         moa.moa_gemm_grouped(descs)
         for k, (C, _, R, *_) in enumerate(ops):
             assert torch.equal(C, R), f"member {k}"
+
+
+def test_walks_longer_than_one_grid_of_bands():
+    """n past 65536 bands of 64 rows (a grid's y extent): columns of a row-major B against a column-major one."""
+    m, n, p = 3, 65536 * 64 + 77, 5
+    g = torch.Generator(device=DEV).manual_seed(0)
+    A, B = torch.randn(m, n, generator=g, device=DEV), torch.randn(p, n, generator=g, device=DEV)
+    B[:, -1] = 100.0                                            # the amax of every column is in the last band
+    out = []
+    for b_col in (False, True):
+        C = torch.full((m, p), float("nan"), device=DEV)
+        moa.moa_gemm(A, operand(B.t(), b_col, 0), C, path="fp8", flags=TERMS[1])
+        out.append(C)
+    assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
+
+
+def test_exponents_of_more_rows_than_one_grid():
+    """More rows than the row-exponent kernel's workgroups, which then take several."""
+    m, n = (1 << 20) + 3, 2
+    g = torch.Generator(device=DEV).manual_seed(1)
+    A, B = torch.randn(m, n, generator=g, device=DEV), torch.randn(n, 3, generator=g, device=DEV)
+
+    def exponents(X):
+        u8 = dict(dtype=torch.uint8, device=DEV)
+        e, f = (torch.full((k,), 999, dtype=torch.int32, device=DEV) for k in (X.shape[0], 3))
+        moa.moa_quantise_fp8(X, B, e, torch.empty(X.shape, **u8), f, torch.empty(B.shape, **u8))
+        return e
+
+    e = exponents(A)
+    for at in (0, (1 << 20) - 500, m - 1000):
+        assert torch.equal(e[at:at + 1000], exponents(A[at:at + 1000].contiguous()))
