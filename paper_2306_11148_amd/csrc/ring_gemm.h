@@ -287,14 +287,18 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
     }
 
     // Epilogue: register r of lane l holds C[8(r/4) + 4(l/32) + r%4][l%32] of
-    // each 32x32 block; 32 lanes write one 128-byte run of a row of C. All loads
-    // (exponents; the accumulate form's values of C, a block at a time) come
+    // each 32x32 block; 32 lanes write one 128-byte run of a row of C, and a row's
+    // runs follow each other (a block at a time, 8000 x 100 x 8000 took 97 us in
+    // split-BF16 and 75 in FP8, one term; row by row 81 and 61). All loads
+    // (exponents; the accumulate form's values of C, 8 rows at a time) come
     // before the stores that need them: a load between two stores waits for
-    // both (with the row's exponent loaded before each store the FP8 product
-    // 3001 x 2777 x 1999, one term, took 50 us, now 45). Buffer
-    // resources end at row m, and columns past p get an offset beyond every
-    // range, so no access needs a branch; one resource per 8 rows of C keeps
-    // the offsets below 2^31 up to p = 2^26.
+    // both (with the row's exponent loaded before each store that FP8 product
+    // took 114 us). Buffer resources end at row m, and columns past p get an
+    // offset beyond every range, so no access needs a test of its own; one
+    // resource per 8 rows of C keeps the offsets below 2^31 up to p = 2^26. The
+    // resources are worked out where they are used: kept in arrays, or the
+    // accumulate form's loads moved further ahead, the code grows and small
+    // products pay for fetching it (64^3 in FP32 17.4 us against 15.7).
     float *dst = partial ? partial : op.C;
     const bool descale = Mode::SCALED && !partial;
     const int64_t iw = i0 + wm * WM, jw = j0 + wn * WN;      // the wave's part of C
@@ -325,29 +329,33 @@ __device__ __forceinline__ void tile(const Operands &op, int64_t i0, int64_t j0,
                     ei[g] = __builtin_bit_cast(i32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
                                                             rows, (8 * g + 4 * (lane >> 5)) * 4, 0, 0));
             }
+            int vj[FN];
 #pragma unroll
-            for (int b = 0; b < FN; ++b) {
-                const int64_t j = jw + b * 32 + (lane & 31);
-                const int vj = j < p ? (b * 32 + (lane & 31)) * 4 + vrow : kDeadVoffset;
-                auto c_rows = [&](int g) {                   // rows ia + 8 g .. + 7, from column jw on
-                    const int64_t i = ia + 8 * g, rows = m - i < 8 ? m - i : 8;
-                    return rsrc_of(dst + i * p + jw, rows > 0 ? rows * pb - jw * 4 : 0);
-                };
-                float old[16];
+            for (int b = 0; b < FN; ++b)
+                vj[b] = jw + b * 32 + (lane & 31) < p ? (b * 32 + (lane & 31)) * 4 + vrow : kDeadVoffset;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {                    // rows ia + 8 g .. + 7, from column jw on
+                const int64_t i = ia + 8 * g, live = m - i < 8 ? m - i : 8;
+                const __amdgpu_buffer_rsrc_t c_rows = rsrc_of(dst + i * p + jw, live > 0 ? live * pb - jw * 4 : 0);
+                float old[FN][4];
                 if constexpr (ACC) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        old[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                               c_rows(r >> 2), vj + (r & 3) * pb, 0, 0));
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int b = 0; b < FN; ++b)
+                            old[b][r] = __builtin_bit_cast(
+                                float, __builtin_amdgcn_raw_buffer_load_b32(c_rows, vj[b] + r * pb, 0, 0));
                 }
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float v = acc[a][b][r];
-                    if constexpr (Mode::SCALED) v = ldexpf(v, -(ei[r >> 2][r & 3] + fj[b]));
-                    if constexpr (ACC) v += old[r];
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), c_rows(r >> 2),
-                                                          vj + (r & 3) * pb, 0, 0);
-                }
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int b = 0; b < FN; ++b) {
+                        float v = acc[a][b][4 * g + r];
+                        if constexpr (Mode::SCALED) v = ldexpf(v, -(ei[g][r] + fj[b]));
+                        if constexpr (ACC) v += old[b][r];
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), c_rows, vj[b] + r * pb,
+                                                              0, 0);
+                    }
             }
         }
     };
