@@ -135,6 +135,10 @@ void onf_variant_shape(moa_dtype t, int v, bool staged, Plan *p);
 int onf_ring_variant(moa_dtype t);           // the 128 x 128 block with 32 x 128 waves (row-major operands)
 // Whether the matrix-core kernel's 32-bit offsets hold the operands of `d` (row-major result).
 bool onf_mm_fits(const moa_gemm_desc &d, int variant);
+// Whether the grid of the kernel that runs `variant` holds the product.
+bool onf_launches(const moa_gemm_desc &d, int variant);
+// Rows of the largest block the planner may choose for `d`.
+int onf_largest_rows(const moa_gemm_desc &d, bool ring_ok);
 int onf_default_variant(const moa_gemm_desc &d, bool ring_ok);
 
 // FP32 matrix cores: variants 0, 1 run the record ring (workspace for the

@@ -674,6 +674,26 @@ void onf_variant_shape(moa_dtype t, int v, bool staged, Plan *p) {
 
 int onf_ring_variant(moa_dtype t) { return onf_variant_count(t) - 1; }
 
+static const OnfShape *shapes_of(const moa_gemm_desc &d) { return d.dtype == MOA_F64 ? kF64 : kF32; }
+
+// The planner's candidates: of the two 128 x 128 blocks the row-major variant
+// where it applies; FP64 without it stops at 64 x 128.
+static bool onf_eligible(const moa_gemm_desc &d, int v, bool ring_ok) {
+    const int ring = onf_ring_variant((moa_dtype)d.dtype);
+    return v == ring ? ring_ok : v < ring - 1 || (d.dtype != MOA_F64 && !ring_ok);
+}
+
+int onf_largest_rows(const moa_gemm_desc &d, bool ring_ok) {
+    int v = onf_ring_variant((moa_dtype)d.dtype);
+    while (!onf_eligible(d, v, ring_ok)) --v;
+    return shapes_of(d)[v].tm;
+}
+
+bool onf_launches(const moa_gemm_desc &d, int v) {
+    const OnfShape s = shapes_of(d)[v];
+    return onf_mm_fits(d, v) || (d.m + s.tm - 1) / s.tm <= 65535;
+}
+
 // The planner's block: the one whose workgroups, dealt out over the CUs, leave
 // the busiest CU the least to do -- ceil(blocks / CUs) times the block's area,
 // weighted by the block's measured time per element of C (4096^3: FP64 2.28 ms
@@ -682,18 +702,19 @@ int onf_ring_variant(moa_dtype t) { return onf_variant_count(t) - 1; }
 // matrix cores are shared by a CU's workgroups, so a CU with two blocks takes
 // twice as long as its neighbours with one: 1999 x 1531 x 2113 in FP64 has 272
 // blocks of 128 x 128 and takes 403 us with them, 258 with 64 x 64 and 244 with
-// 32 x 32; 256^3 takes 41, 11 and 4.8 us. Ties go to the larger block. 128 x 128 blocks only where every CU gets
-// one; FP64 without the row-major variant stops at 64 x 128.
+// 32 x 32; 256^3 takes 41, 11 and 4.8 us. Ties go to the larger block. 128 x 128
+// blocks only where every CU gets one. Blocks whose grid does not hold the
+// product (the register-staged kernel's rows of blocks are its grid's y) are
+// not candidates.
 int onf_default_variant(const moa_gemm_desc &d, bool ring_ok) {
     constexpr double kWeight64[] = {1.07, 1.0, 1.0, 1.0, 1.0}, kWeight32[] = {1.13, 1.035, 1.03, 1.0, 1.0};
-    const bool f64 = d.dtype == MOA_F64;
-    const OnfShape *shapes = f64 ? kF64 : kF32;
-    const double *weight = f64 ? kWeight64 : kWeight32;
+    const OnfShape *shapes = shapes_of(d);
+    const double *weight = d.dtype == MOA_F64 ? kWeight64 : kWeight32;
     const int ring = onf_ring_variant((moa_dtype)d.dtype);
     int best = 0;
     double best_cost = 0;
     for (int v = ring; v >= 0; --v) {
-        if (v == ring ? !ring_ok : v == ring - 1 && (f64 || ring_ok)) continue;
+        if (!onf_eligible(d, v, ring_ok) || !onf_launches(d, v)) continue;
         const OnfShape s = shapes[v];
         const int64_t blocks = ((d.m + s.tm - 1) / s.tm) * ((d.p + s.tn - 1) / s.tn);
         if (s.tm * s.tn == 128 * 128 && blocks < kNumCUs) continue;

@@ -217,13 +217,15 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
                 return fail(MOA_ERR_UNSUPPORTED, "the ONF ring variant takes row-major operands whose rows fit "
                             "32-bit offsets");
             v = forced;
-        } else if ((v = tuned_variant(d, pl.path)) >= 0 && (v != ring || ring_ok)) {
+        } else if ((v = tuned_variant(d, pl.path)) >= 0 && (v != ring || ring_ok) && onf_launches(d, v)) {
             pl.tuned = true;
         } else {
             v = onf_default_variant(d, ring_ok);
         }
         onf_variant_shape((moa_dtype)d.dtype, v, !onf_mm_fits(d, v), &pl);
-        if ((d.m + pl.tile_m - 1) / pl.tile_m > 65535)
+        // rows: 65535 blocks of a variant asked for, of the largest block otherwise
+        const int64_t tm = forced >= 0 ? pl.tile_m : onf_largest_rows(d, ring_ok);
+        if ((d.m + tm - 1) / tm > 65535)
             return fail(MOA_ERR_SHAPE, "m = %lld exceeds the ONF grid limit", (long long)d.m);
         break;
     }
