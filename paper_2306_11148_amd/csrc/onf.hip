@@ -691,7 +691,9 @@ int onf_largest_rows(const moa_gemm_desc &d, bool ring_ok) {
 
 bool onf_launches(const moa_gemm_desc &d, int v) {
     const OnfShape s = shapes_of(d)[v];
-    return onf_mm_fits(d, v) || (d.m + s.tm - 1) / s.tm <= 65535;
+    const int64_t rows = (d.m + s.tm - 1) / s.tm, cols = (d.p + s.tn - 1) / s.tn;
+    const int64_t lim = (int64_t(1) << 24) - 1;              // workgroups of 256 threads in x
+    return onf_mm_fits(d, v) ? rows * cols <= lim : rows <= 65535 && cols <= lim;
 }
 
 // The planner's block: the one whose workgroups, dealt out over the CUs, leave
@@ -704,8 +706,8 @@ bool onf_launches(const moa_gemm_desc &d, int v) {
 // blocks of 128 x 128 and takes 403 us with them, 258 with 64 x 64 and 244 with
 // 32 x 32; 256^3 takes 41, 11 and 4.8 us. Ties go to the larger block. 128 x 128
 // blocks only where every CU gets one. Blocks whose grid does not hold the
-// product (the register-staged kernel's rows of blocks are its grid's y) are
-// not candidates.
+// product (fewer than 2^32 threads in x; the register-staged kernel's rows of
+// blocks are its grid's y) are not candidates.
 int onf_default_variant(const moa_gemm_desc &d, bool ring_ok) {
     constexpr double kWeight64[] = {1.07, 1.0, 1.0, 1.0, 1.0}, kWeight32[] = {1.13, 1.035, 1.03, 1.0, 1.0};
     const OnfShape *shapes = shapes_of(d);

@@ -1,8 +1,9 @@
-"""Tall ONF products: which row counts the default plan takes, and rows far down a tall product.
+"""Tall and wide ONF products: which row counts the default plan takes, and rows far down a tall product.
 
 The default block may be any of the table, but how many rows a product may have
 does not depend on it: 65535 blocks of the largest block of its type and layout
-(128 rows; 64 for FP64 with a column-major operand).
+(128 rows; 64 for FP64 with a column-major operand). A launch holds fewer than
+2^32 threads in x, so the block has to leave fewer than 2^24 workgroups.
 """
 import numpy as np
 import pytest
@@ -54,3 +55,22 @@ def test_rows_of_a_tall_product(dtype):
     rows = torch.tensor([0, 1, m // 2, 65535 * 32 - 1, 65535 * 32, 65535 * 32 + 1, m - 2, m - 1], device="cuda:0")
     fma = O.gemm_f64_fma if dtype == np.float64 else O.gemm_f32_fma
     assert np.array_equal(C[rows].cpu().numpy(), fma(np.ascontiguousarray(A[rows].cpu().numpy()), B))
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("m", [1, 32, 33])
+@pytest.mark.parametrize("p", [2 ** 24, 2 ** 29 - 1, 2 ** 29, 2 ** 29 + 5, 2 ** 30, 2 ** 30 + 5])
+def test_wide_products_fit_the_grid(dtype, m, p):
+    q = plan(m, 1, p, dtype)
+    assert q["workgroups"] * q["threads"] < 2 ** 32
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,p", [(torch.float64, 2 ** 29 + 5), (torch.float32, 2 ** 30 + 5)])
+def test_a_wide_product(dtype, p):
+    """One row, k of one step: C[0][j] = A[0][0] B[0][j], one rounding."""
+    A = torch.tensor([[1.1]], device="cuda:0", dtype=dtype)
+    B = torch.randn((1, p), generator=torch.Generator(device="cuda:0").manual_seed(5), device="cuda:0", dtype=dtype)
+    C = torch.full((1, p), float("nan"), device="cuda:0", dtype=dtype)
+    moa.moa_gemm(A, B, C, path="onf")
+    assert torch.equal(C, B * A)
