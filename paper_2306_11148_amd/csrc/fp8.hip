@@ -200,16 +200,17 @@ struct RowsJob {
     uint8_t *q, *l;
 };
 
-// Four rows of n values per workgroup: the rows of one job, then those of a
-// second one (no blocks: none). Clears `count` words at `clear` on the way (the
-// column amax of an operand taken by columns).
+// Four rows of n values per workgroup of an item_grid: the rows of one job, then
+// those of a second one (no blocks: none). Clears `count` words at `clear` on the
+// way (the column amax of an operand taken by columns).
 template <bool TWO, int J>
 __global__ __launch_bounds__(256) void rows_fp8_kernel(RowsJob first, RowsJob second, int64_t n, int64_t S,
                                                        uint32_t *__restrict__ clear, int64_t count) {
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < count; t += (int64_t)gridDim.x * 256) clear[t] = 0u;
-    const bool of_first = blockIdx.x < first.blocks;
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    for (int64_t t = item * 256 + threadIdx.x; t < count; t += (int64_t)gridDim.x * gridDim.y * 256) clear[t] = 0u;
+    const bool of_first = item < first.blocks;
     const RowsJob d = of_first ? first : second;
-    const int64_t i = ((int64_t)blockIdx.x - (of_first ? 0 : first.blocks)) * 4 + (threadIdx.x >> 6);
+    const int64_t i = (item - (of_first ? 0 : first.blocks)) * 4 + (threadIdx.x >> 6);
     if (i < padded_rows(d.rows)) condition_row<TWO, J>(d.X, i, d.rows, n, S, threadIdx.x & 63, d.e, d.q, d.l);
 }
 
@@ -702,7 +703,7 @@ RowsJob rows_job(const float *X, int64_t rows, int32_t *e, uint8_t *q, uint8_t *
 template <bool TWO>
 void row_records(const RowsJob &a, const RowsJob &b, int64_t K, int64_t S, uint32_t *clear, int64_t count,
                  hipStream_t st) {
-    const dim3 grid((unsigned)(a.blocks + b.blocks)), bl(256);
+    const dim3 grid = item_grid(a.blocks + b.blocks), bl(256);
     if (K <= 1024) {
         hipLaunchKernelGGL((rows_fp8_kernel<TWO, 4>), grid, bl, 0, st, a, b, K, S, clear, count);
     } else if (K <= 2048) {
