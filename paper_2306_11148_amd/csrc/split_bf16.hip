@@ -536,17 +536,19 @@ __global__ void zero_counters_kernel(unsigned long long *x) {
 }
 constexpr int GB_M = 128;              // largest grouped block rows
 
-// Persistent kernels of a grouped launch: block, workgroups per CU, time of
-// one slab step of a block on a full CU (us of CU time: the 512 products of the
-// batching workload over their steps, tile changes included) and of a block
-// alone on its CU (512^3 .. 2048^3).
-struct GroupedKernel { int bm, bn, occ; double step_us, alone_us; };
+// Persistent kernels of a grouped launch: block, workgroups per CU, weight of a
+// slab step of a block in groups of short k walks, and for longer ones the time
+// of a launch (us): fixed + step x (slab steps per CU) + walk x (slabs of the
+// longest walk) + wg x (workgroups per CU: they claim their tiles one after
+// another). Fitted to 90 groups of 4 to 396 products of 32 .. 2048 (n to 4096),
+// uniform and mixed.
+struct GroupedKernel { int bm, bn, occ; double weight, fixed, step, walk, wg; };
 constexpr GroupedKernel kGroupedK[] = {
-    {128, 128, 2, 0.60, 0.48},   // 0: five stages
-    {64, 64, 4, 0.25, 0.26},     // 1
-    {128, 128, 2, 0.57, 0.48},   // 2: three stages
-    {64, 128, 3, 0.35, 0.33},    // 3
-    {128, 64, 4, 0.39, 0.33},    // 4
+    {128, 128, 2, 0.60, 18.5, 0.423, 0.303, 6.98},   // 0: five stages
+    {64, 64, 4, 0.25, 17.8, 0.210, 0.128, 8.11},    // 1
+    {128, 128, 2, 0.57, 18.5, 0.423, 0.303, 6.98},   // 2: three stages
+    {64, 128, 3, 0.35, 18.3, 0.284, 0.200, 7.37},   // 3
+    {128, 64, 4, 0.39, 17.8, 0.357, 0.244, 7.19},  // 4
 };
 constexpr int kGroupedVariants = (int)(sizeof(kGroupedK) / sizeof(kGroupedK[0]));
 int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
@@ -605,12 +607,13 @@ int split_grouped_variant_count() { return kGroupedVariants; }
 
 // Static rule. Short k walks (below 32 slabs): the block among 128 x 128, 64 x
 // 128 and 128 x 64 with the fewest slab steps over the items, weighted by the
-// time of a step. Longer ones: the block for which the CUs' share of the steps
-// plus the longest walk of one block is shortest, 64 x 64 among them -- a group
-// that leaves CUs idle is as slow as its longest walk (32 products 100 x 4000 x
-// 100: 115 us with 128 x 128 blocks, 95 with 64 x 128, 81 with 64 x 64; 64
-// products 512^3, which fill the CUs: 85, 106 and 134). Ties to the earlier
-// variant in the list; variant 0 is left to the autotuner.
+// time of a step. Longer ones: the block with the shortest estimated launch, 64 x
+// 64 among them -- a group that leaves CUs idle is as slow as its longest walk
+// (4 products, the longest walk 197 slabs: 97 us with 128 x 128 blocks, 68 with 64 x
+// 64), a large one pays for every step (64 products of 64 .. 2048: 232 us with 128 x 128
+// blocks, 271 with 64 x 128, 348 with 64 x 64). Over the fitted groups the choice
+// takes 2% longer than the best block on average and 16% at most. Ties to the
+// earlier variant in the list; variant 0 is left to the autotuner.
 int split_grouped_default_variant(const SplitGroup &g) {
     int64_t longest = 0;
     for (const SplitItem &d : g.items) longest = std::max(longest, item_slabs(d));
@@ -618,11 +621,16 @@ int split_grouped_default_variant(const SplitGroup &g) {
     double best_cost = 0;
     for (int v : {2, 3, 4, 1}) {
         if (v == 1 && longest < 32) continue;
-        double cost = 0;
-        for (const SplitItem &d : g.items)
-            cost += (double)item_tiles(d, kGroupedK[v].bm, kGroupedK[v].bn) * (double)item_slabs(d);
-        cost *= kGroupedK[v].step_us;
-        if (longest >= 32) cost = cost / kNumCUs + (double)longest * kGroupedK[v].alone_us;
+        const GroupedKernel k = kGroupedK[v];
+        double steps = 0, tiles = 0;
+        for (const SplitItem &d : g.items) {
+            const double t = (double)item_tiles(d, k.bm, k.bn);
+            tiles += t;
+            steps += t * (double)item_slabs(d);
+        }
+        const double cost = longest < 32 ? steps * k.weight
+                                         : k.fixed + k.step * steps / kNumCUs + k.walk * (double)longest +
+                                               k.wg * std::min(tiles / kNumCUs, (double)k.occ);
         if (v == 2 || cost < best_cost) {
             best = v;
             best_cost = cost;
