@@ -85,6 +85,7 @@ moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixe
     Plan pl;
     moa_status s = make_plan(d, &pl);
     if (s != MOA_OK) return s;
+    plan_raw_block(d, &pl);
     if (fixed_ws && pl.workspace_bytes > fixed_bytes)
         return fail(MOA_ERR_NOMEM, "the product needs %lld bytes of scratch, the fixed scratch array holds %lld",
                     (long long)pl.workspace_bytes, (long long)fixed_bytes);

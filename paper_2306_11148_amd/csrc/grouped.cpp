@@ -184,6 +184,9 @@ int64_t partial_bytes(const Partition &pt) {
 // The items of the split-BF16 launch, partials carved from `partials`.
 SplitGroup split_items(const Partition &pt, void *partials) {
     SplitGroup g;
+    size_t count = pt.split.size();
+    for (const auto &c : pt.chunked) count += (size_t)c.second;
+    g.items.reserve(count);
     for (const moa_gemm_desc *d : pt.split) split_group_add(g, *d, 1, nullptr);
     char *at = static_cast<char *>(partials);
     for (const auto &c : pt.chunked) {

@@ -86,6 +86,12 @@ inline int split_k_chunks(int requested, int64_t S) {
 moa_status validate(const moa_gemm_desc &d, bool need_ptrs);
 moa_path resolve_path(const moa_gemm_desc &d);
 moa_status make_plan(const moa_gemm_desc &d, Plan *out);
+// Completes the plan of a product that runs singly: split-BF16 products of few
+// blocks run without conditioning unless a flag or the autotuner names a
+// record-ring block. The other fields stay those of the conditioned form (fixed
+// scratch refuses the same products). Apart from make_plan, which plans every
+// member of a group too.
+void plan_raw_block(const moa_gemm_desc &d, Plan *pl);
 // Chunks into which the plan of `d` cuts its k walk (asked for or chosen by the
 // planner; 1: none).
 inline int planned_split_k(const moa_gemm_desc &d) {

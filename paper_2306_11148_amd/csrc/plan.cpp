@@ -196,6 +196,14 @@ static int split_k_of(const moa_gemm_desc &d, int64_t slabs) {
     return split_k_chunks(req == 0 ? auto_split_k(d.m, d.n, d.p) : req, slabs);
 }
 
+void plan_raw_block(const moa_gemm_desc &d_in, Plan *pl) {
+    const bool forced = (d_in.flags & MOA_FLAG_VARIANT_MASK) != 0;
+    if (pl->path != MOA_PATH_SPLIT_BF16 || forced || pl->tuned) return;
+    const moa_gemm_desc d = row_major_result(d_in);
+    if (pl->split_k > 1) pl->raw_block = split_raw_splitk(d) ? 3 : -1;
+    else if (split_k_requested(d) == 0) pl->raw_block = split_raw_block(d);
+}
+
 moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
     const moa_gemm_desc d = row_major_result(d_in);   // a column-major C is planned as C^T
     Plan pl;
@@ -268,13 +276,6 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
         pl.workspace_bytes = split_bf16_workspace_bytes(d.m, d.n, d.p);
         pl.split_k = split_k_of(d, (d.n + 15) / 16);
         if (pl.split_k > 1) split_bf16_shape(0, &pl);   // split-k runs the first block variant
-        // Products of few blocks run without conditioning unless a flag or the
-        // autotuner names a record-ring block. The plan's other fields stay those
-        // of the conditioned form (fixed scratch refuses the same products).
-        if (forced < 0 && !pl.tuned) {
-            if (pl.split_k > 1) pl.raw_block = split_raw_splitk(d) ? 3 : -1;
-            else if (split_k_requested(d) == 0) pl.raw_block = split_raw_block(d);
-        }
         // 256 record rows of (n/16) 64-byte records must stay below 2^31 bytes
         // (32-bit buffer offsets of one tile).
         if ((d.n + 15) / 16 > 131071)

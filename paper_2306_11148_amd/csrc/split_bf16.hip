@@ -615,22 +615,27 @@ int split_grouped_variant_count() { return kGroupedVariants; }
 // takes 2% longer than the best block on average and 16% at most. Ties to the
 // earlier variant in the list; variant 0 is left to the autotuner.
 int split_grouped_default_variant(const SplitGroup &g) {
+    // slab steps and tiles of every block, in shifts: the rule runs on each call
+    double steps[kGroupedVariants] = {}, tiles[kGroupedVariants] = {};
     int64_t longest = 0;
-    for (const SplitItem &d : g.items) longest = std::max(longest, item_slabs(d));
+    for (const SplitItem &d : g.items) {
+        const int64_t slabs = item_slabs(d);
+        const int64_t m64 = (d.m + 63) / 64, m128 = (d.m + 127) / 128, p64 = (d.p + 63) / 64, p128 = (d.p + 127) / 128;
+        const int64_t t[kGroupedVariants] = {m128 * p128, m64 * p64, m128 * p128, m64 * p128, m128 * p64};
+        longest = std::max(longest, slabs);
+        for (int v = 0; v < kGroupedVariants; ++v) {
+            tiles[v] += (double)t[v];
+            steps[v] += (double)t[v] * (double)slabs;
+        }
+    }
     int best = 2;
     double best_cost = 0;
     for (int v : {2, 3, 4, 1}) {
         if (v == 1 && longest < 32) continue;
         const GroupedKernel k = kGroupedK[v];
-        double steps = 0, tiles = 0;
-        for (const SplitItem &d : g.items) {
-            const double t = (double)item_tiles(d, k.bm, k.bn);
-            tiles += t;
-            steps += t * (double)item_slabs(d);
-        }
-        const double cost = longest < 32 ? steps * k.weight
-                                         : k.fixed + k.step * steps / kNumCUs + k.walk * (double)longest +
-                                               k.wg * std::min(tiles / kNumCUs, (double)k.occ);
+        const double cost = longest < 32 ? steps[v] * k.weight
+                                         : k.fixed + k.step * steps[v] / kNumCUs + k.walk * (double)longest +
+                                               k.wg * std::min(tiles[v] / kNumCUs, (double)k.occ);
         if (v == 2 || cost < best_cost) {
             best = v;
             best_cost = cost;
@@ -647,12 +652,15 @@ int split_grouped_default_variant(const SplitGroup &g) {
 GroupedWork split_grouped_layout(const SplitGroup &g, void *host_staging, int variant) {
     const GroupedKernel gk = kGroupedK[variant];
     const int count = (int)g.items.size();
-    auto cost = [&](int k) {
-        return (double)item_tiles(g.items[k], gk.bm, gk.bn) * (double)item_slabs(g.items[k]);
-    };
+    std::vector<int64_t> member_tiles(count);
+    std::vector<double> cost(count);
     std::vector<int> heavy(count);
-    for (int k = 0; k < count; ++k) heavy[k] = k;
-    std::stable_sort(heavy.begin(), heavy.end(), [&](int a, int b) { return cost(a) > cost(b); });
+    for (int k = 0; k < count; ++k) {
+        heavy[k] = k;
+        member_tiles[k] = item_tiles(g.items[k], gk.bm, gk.bn);
+        cost[k] = (double)member_tiles[k] * (double)item_slabs(g.items[k]);
+    }
+    std::stable_sort(heavy.begin(), heavy.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     std::vector<int> seg_of(count);
     double load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int k : heavy) {
@@ -660,7 +668,7 @@ GroupedWork split_grouped_layout(const SplitGroup &g, void *host_staging, int va
         for (int y = 1; y < 8; ++y)
             if (load[y] < load[x]) x = y;
         seg_of[k] = x;
-        load[x] += cost(k);
+        load[x] += cost[k];
     }
     std::vector<int> order(count);
     for (int k = 0; k < count; ++k) order[k] = k;
@@ -682,7 +690,7 @@ GroupedWork split_grouped_layout(const SplitGroup &g, void *host_staging, int va
         m.item = d;
         m.first_tile = tiles;
         m.tiles_n = (int32_t)((d.p + gk.bn - 1) / gk.bn);
-        const int64_t mt = item_tiles(d, gk.bm, gk.bn);
+        const int64_t mt = member_tiles[order[q]];
         for (int64_t t = 0; t < mt; ++t) tile_owner[tiles + t] = q;
         tiles += mt;
         h[q] = m;
