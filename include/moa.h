@@ -78,7 +78,7 @@ typedef enum moa_dtype {
  *                  matrix cores with FP32 accumulation. F32 only. Products of
  *                  few blocks are split on the way through LDS instead of being
  *                  conditioned first (same bits; moa_plan_query describes the
- *                  conditioned form).
+ *                  conditioned form and names the block that runs).
  *  FP8_SCALED   -- row i of A is scaled by 2^e_i and column j of B by 2^f_j
  *                  (e the largest integer with amax * 2^e <= 448), rounded
  *                  to OCP E4M3, multiplied on FP8 matrix cores with FP32
@@ -180,7 +180,13 @@ typedef struct moa_plan_info {
     int32_t variant;          /* instantiation of the path's kernel table */
     int32_t tuned;            /* 1 if the variant came from the autotuner */
     int32_t split_k;          /* k chunks summed by separate workgroups (1 = none) */
-    int32_t reserved;
+    int32_t direct_block;     /* 0: moa_gemm runs the kernel described above.
+                                 Else it runs split-BF16 without conditioning, in
+                                 blocks of (direct_block >> 16) rows by
+                                 (direct_block & 0xFFFF) columns; tile, workgroups,
+                                 LDS and workspace above are those of the
+                                 conditioned form (its workspace bounds the call's
+                                 scratch, and moa_gemm_noalloc checks it) */
 } moa_plan_info;
 
 /* Eq. 3 on the device. Asynchronous on `stream`.

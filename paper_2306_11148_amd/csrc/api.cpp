@@ -153,6 +153,7 @@ moa_status moa_plan_query(const moa_gemm_desc *desc, moa_plan_info *out) {
         Plan pl;
         s = make_plan(*desc, &pl);
         if (s != MOA_OK) return s;
+        plan_raw_block(*desc, &pl);
         std::memset(out, 0, sizeof *out);
         out->path = pl.path;
         out->kernel = pl.kernel;
@@ -171,6 +172,11 @@ moa_status moa_plan_query(const moa_gemm_desc *desc, moa_plan_info *out) {
         out->variant = pl.variant;
         out->tuned = pl.tuned ? 1 : 0;
         out->split_k = pl.split_k;
+        if (pl.raw_block >= 0) {
+            int rows = 0, cols = 0;
+            split_raw_shape(pl.raw_block, &rows, &cols);
+            out->direct_block = rows << 16 | cols;
+        }
         return MOA_OK;
     } catch (...) {
         return fail(MOA_ERR_DEVICE, "internal error");

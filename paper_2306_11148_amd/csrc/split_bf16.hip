@@ -428,6 +428,11 @@ bool split_raw_splitk(const moa_gemm_desc &d) {
     return ((d.m + 127) / 128) * ((d.p + 127) / 128) <= 3 * kNumCUs && a < lim && b < lim && 9 * d.p < lim;
 }
 
+void split_raw_shape(int block, int *rows, int *cols) {
+    *rows = kRaw[block].bm;
+    *cols = kRaw[block].bn;
+}
+
 int split_bf16_variant_count() { return (int)(sizeof(kSplit) / sizeof(kSplit[0])); }
 
 // Default block: 256 x 256 (one workgroup per CU) once it gives every CU a

@@ -58,7 +58,7 @@ class moa_plan_info(ctypes.Structure):
                 ("lds_bytes", ctypes.c_int32), ("workgroups", ctypes.c_int64),
                 ("workspace_bytes", ctypes.c_int64), ("static_components", ctypes.c_int64),
                 ("variant", ctypes.c_int32), ("tuned", ctypes.c_int32),
-                ("split_k", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+                ("split_k", ctypes.c_int32), ("direct_block", ctypes.c_int32)]
 
 
 class moa_serve_cfg(ctypes.Structure):
