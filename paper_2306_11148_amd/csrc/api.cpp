@@ -327,6 +327,11 @@ moa_status moa_diag_ring_loads(const moa_gemm_desc *desc, int64_t *loads, int64_
             *violations = 0;
             return MOA_OK;
         }
+        plan_raw_block(d, &pl);
+        if (pl.raw_block >= 0) {
+            *violations = split_raw_check(d, pl.raw_block, pl.split_k, loads);
+            return MOA_OK;
+        }
         *violations = ring::check_loads(pl.tile_m, pl.tile_n, pl.wave_m, pl.wave_n, nrec, d.m, d.p, S, loads);
         return MOA_OK;
     } catch (...) {

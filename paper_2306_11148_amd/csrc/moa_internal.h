@@ -165,6 +165,8 @@ int split_bf16_default_variant(int64_t m, int64_t p);   // the planner's default
 int64_t split_bf16_workspace_bytes(int64_t m, int64_t n, int64_t p);
 int split_raw_block(const moa_gemm_desc &d);            // block without conditioning, -1: conditioned
 void split_raw_shape(int block, int *rows, int *cols);
+// Host check of that kernel's direct loads: violations; loads per slab in *loads.
+int64_t split_raw_check(const moa_gemm_desc &d, int block, int chunks, int64_t *loads);
 bool split_raw_splitk(const moa_gemm_desc &d);          // a split-k product without conditioning
 // Grouped split-BF16: all items in one persistent launch. An item is a product
 // or, for a member that splits its k walk, one chunk of it: a window of n of the

@@ -60,7 +60,7 @@ template <int W, bool KC> struct Operand {
 
     // Vector offset of lane `lane` in load g; live: rows of the block inside
     // the operand (KC), ld: bytes from row to row (KC) or from k to k.
-    static __device__ __forceinline__ int voffset(int g, int lane, int64_t live, int64_t ld) {
+    static __host__ __device__ __forceinline__ int voffset(int g, int lane, int64_t live, int64_t ld) {
         if constexpr (KC) {
             const int r = 16 * g + (lane >> 2);
             const int c = (lane & 3) ^ ((lane >> 4) & 3);
@@ -358,6 +358,50 @@ __global__ __launch_bounds__(256, 2) void splitk_kernel(Operands d, int tiles_m,
     d.accumulate = 0;
     block<BM, BN, WM, WN, NST, A_KC, B_KC>(d, (int64_t)__builtin_amdgcn_readfirstlane(tm) * BM,
                                            (int64_t)__builtin_amdgcn_readfirstlane(tn) * BN, lds);
+}
+
+// Host check of the loads of one operand of a launch (or of one chunk of its k
+// walk): `extent` rows or columns in blocks of W, n of k, ld elements from row to
+// row, `size` elements from the operand's first to its end. For every block and
+// the first and last slab: the buffer range ends inside the operand, no lane's
+// 16 bytes pass the 32-bit offsets, and what the block needs (rows inside the
+// operand, k below n) is inside the range. Returns the violations; adds the loads
+// per slab to *loads.
+template <int W, bool KC>
+int64_t check_operand(int64_t extent, int64_t n, int64_t ld, int64_t size, int64_t *loads) {
+    using O = Operand<W, KC>;
+    const int64_t lim31 = 0x7FFFFFFF, S = (n + SLAB - 1) / SLAB;
+    int64_t bad = 0;
+    for (int64_t at = 0; at < extent; at += W) {
+        // as block() lays them out: rows inside the operand, first element, bytes
+        // to the live end and per slab, bytes from row to row or from k to k
+        const int64_t live = std::min<int64_t>(extent - at, W), first = KC ? at * ld : at;
+        const int64_t end = (KC ? (live - 1) * ld + n : n * extent - at) * 4;
+        const int64_t step = (KC ? 1 : extent) * SLAB * 4, pitch = (KC ? ld : extent) * 4;
+        *loads += O::LOADS;
+        if (first * 4 + end > size * 4) ++bad;
+        for (int64_t s = 0; s < S; s += std::max<int64_t>(S - 1, 1)) {
+            const int64_t left = end - s * step, range = std::min(left, lim31);
+            if (left <= 0) ++bad;
+            for (int g = 0; g < O::LOADS; ++g)
+                for (int lane = 0; lane < 64; ++lane) {
+                    // the row (KC) or k of the lane's 16 bytes, and their chunk of it
+                    const int r = KC ? 16 * g + (lane >> 2) : g * (64 / O::CPR) + lane / O::CPR;
+                    const uint32_t v = (uint32_t)O::voffset(g, lane, live, pitch);
+                    if (KC && r >= live) {
+                        if (v <= (uint32_t)lim31) ++bad;    // must pass every range
+                        continue;
+                    }
+                    const int64_t c = ((int64_t)v - r * pitch) / 16;
+                    if (v + 15 > (uint32_t)lim31 || c < 0 || c >= (KC ? 4 : O::CPR)) ++bad;
+                    for (int e = 0; e < 4; ++e) {
+                        const int64_t k = s * SLAB + (KC ? 4 * c + e : r), at_row = KC ? r : 4 * c + e;
+                        if (k < n && at_row < live && (int64_t)v + 4 * e + 4 > range) ++bad;
+                    }
+                }
+        }
+    }
+    return bad;
 }
 
 }  // namespace raw

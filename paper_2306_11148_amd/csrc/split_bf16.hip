@@ -428,6 +428,28 @@ bool split_raw_splitk(const moa_gemm_desc &d) {
     return ((d.m + 127) / 128) * ((d.p + 127) / 128) <= 3 * kNumCUs && a < lim && b < lim && 9 * d.p < lim;
 }
 
+int64_t split_raw_check(const moa_gemm_desc &d, int block, int chunks, int64_t *loads) {
+    const int64_t S = (d.n + SLAB - 1) / SLAB, window = (S + chunks - 1) / chunks * SLAB;
+    const bool a_kc = !(d.flags & MOA_FLAG_A_COL), b_kc = (d.flags & MOA_FLAG_B_COL) != 0;
+    int64_t bad = 0, seen = 0;
+    auto check = [&](int width, bool kc, int64_t extent, int64_t k0, int64_t n) {
+        const int64_t size = kc ? extent * d.n - k0 : extent * (d.n - k0);
+        if (width == 64)
+            bad += kc ? raw::check_operand<64, true>(extent, n, d.n, size, &seen)
+                      : raw::check_operand<64, false>(extent, n, d.n, size, &seen);
+        else
+            bad += kc ? raw::check_operand<128, true>(extent, n, d.n, size, &seen)
+                      : raw::check_operand<128, false>(extent, n, d.n, size, &seen);
+    };
+    for (int64_t c = 0; c < chunks; c += std::max(chunks - 1, 1)) {      // the first chunk and the last
+        const int64_t k0 = c * window, n = std::min(window, d.n - k0);
+        check(kRaw[block].bm, a_kc, d.m, k0, n);
+        check(kRaw[block].bn, b_kc, d.p, k0, n);
+    }
+    if (loads) *loads = seen;
+    return bad;
+}
+
 void split_raw_shape(int block, int *rows, int *cols) {
     *rows = kRaw[block].bm;
     *cols = kRaw[block].bn;

@@ -290,7 +290,7 @@ def moa_plan_query(desc: moa_gemm_desc) -> dict:
 
 
 def moa_diag_ring_loads(desc: moa_gemm_desc) -> tuple[int, int]:
-    """(loads checked per slab, violations) of the record-ring launch of desc's plan."""
+    """(loads checked per slab, violations) of the direct-to-LDS loads of desc's plan."""
     loads, bad = ctypes.c_int64(), ctypes.c_int64()
     _check(lib().moa_diag_ring_loads(ctypes.byref(desc), ctypes.byref(loads), ctypes.byref(bad)),
            "moa_diag_ring_loads")

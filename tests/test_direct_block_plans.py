@@ -23,3 +23,21 @@ def test_block_that_runs(shape, block):
 def test_column_major_result_is_planned_transposed():
     q = plan(5440, 65, 384, flags=moa.MOA_FLAG_C_COL)
     assert (q["direct_block"] >> 16, q["direct_block"] & 0xFFFF) == (128, 64)
+
+
+@pytest.mark.parametrize("flags", range(8))
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 16, 65), (65, 17, 63), (130, 33, 257), (192, 320, 160), (384, 65, 5440),
+                                   (1530, 65, 1236), (2000, 48, 2040), (100, 20000, 100), (3, 16 * 131071, 5),
+                                   (1000, 4, 90000)])
+def test_direct_loads_stay_in_bounds(shape, flags):
+    """Every load of the kernel that runs, in every layout: inside the operand and its 32-bit offsets, and covering
+    what the block needs."""
+    d = moa.moa_gemm_desc(m=shape[0], n=shape[1], p=shape[2], dtype=moa.MOA_F32, path=moa.MOA_PATH_SPLIT_BF16, A=None,
+                          B=None, C=None, accumulate=0, flags=flags << 24)
+    q = moa.moa_plan_query(d)
+    loads, bad = moa.moa_diag_ring_loads(d)
+    assert loads > 0 and bad == 0
+    if q["direct_block"] and q["split_k"] == 1:
+        m, p = (shape[2], shape[0]) if flags & 4 else (shape[0], shape[2])
+        rows, cols = q["direct_block"] >> 16, q["direct_block"] & 0xFFFF
+        assert loads == -(-m // rows) * rows // 16 + -(-p // cols) * cols // 16
