@@ -323,19 +323,24 @@ moa_status moa_plan_query(const moa_gemm_desc *desc, moa_plan_info *out);
 
 /* Autotuner. The planner starts from the static rule (below) and picks a
  * kernel instantiation from shape alone; moa_autotune times every
- * instantiation of desc's path on the caller's buffers (C is overwritten;
- * `reps` >= 1 timed runs each, after one warm-up) on `stream`, waits for
- * them, and records the fastest for desc's shape class -- (dtype, path,
- * FP8 term count, ceil(log2 m), ceil(log2 n), ceil(log2 p)). moa_gemm,
+ * instantiation of desc's path -- and, where the planner would take it, the
+ * split-BF16 kernel without conditioning -- on the caller's buffers (C is
+ * overwritten; `reps` >= 1 timed runs each, after one warm-up) on `stream`,
+ * waits for them, and records the fastest for desc's shape class -- (dtype,
+ * path, FP8 term count, ceil(log2 m), ceil(log2 n), ceil(log2 p)). moa_gemm,
  * moa_gemm_grouped's single launches and moa_plan_query then use the
  * recorded instantiation for every product of that class unless
- * MOA_FLAG_VARIANT forces one. `chosen` (may be null) receives the plan and
+ * MOA_FLAG_VARIANT forces one; where the kernel without conditioning was the
+ * fastest, products of the class keep the planner's choice of it and the
+ * fastest instantiation is recorded for the others. `chosen` (may be null) receives the plan and
  * `best_ms` (may be null) the time per run of the winner. Errors: as
  * moa_gemm; MOA_ERR_INVALID for reps < 1. */
 moa_status moa_autotune(const moa_gemm_desc *desc, int32_t reps, void *stream,
                         moa_plan_info *chosen, double *best_ms);
 /* Writes the recorded classes to a text file (one class per line) /
- * merges a file written by moa_autotune_save / forgets every record. */
+ * merges a file written by moa_autotune_save / forgets every record. Records
+ * written before the kernel without conditioning was timed lack their last
+ * field and leave the planner's choice of that kernel in place. */
 moa_status moa_autotune_save(const char *path);
 moa_status moa_autotune_load(const char *path);
 moa_status moa_autotune_clear(void);

@@ -79,13 +79,9 @@ moa_status validate(const moa_gemm_desc &d, bool need_ptrs) {
     return MOA_OK;
 }
 
-moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixed_ws, int64_t fixed_bytes) {
-    if (d_in.m == 0 || d_in.p == 0) return MOA_OK;
-    const moa_gemm_desc d = row_major_result(d_in);
-    Plan pl;
-    moa_status s = make_plan(d, &pl);
-    if (s != MOA_OK) return s;
-    plan_raw_block(d, &pl);
+// Runs `d` (row-major result) as planned.
+static moa_status run_planned(const moa_gemm_desc &d, Plan pl, hipStream_t stream, void *fixed_ws, int64_t fixed_bytes) {
+    moa_status s = MOA_OK;
     if (fixed_ws && pl.workspace_bytes > fixed_bytes)
         return fail(MOA_ERR_NOMEM, "the product needs %lld bytes of scratch, the fixed scratch array holds %lld",
                     (long long)pl.workspace_bytes, (long long)fixed_bytes);
@@ -117,6 +113,16 @@ moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixe
     if (s != MOA_OK) return s;
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return MOA_OK;
+}
+
+moa_status run_gemm_in(const moa_gemm_desc &d_in, hipStream_t stream, void *fixed_ws, int64_t fixed_bytes) {
+    if (d_in.m == 0 || d_in.p == 0) return MOA_OK;
+    const moa_gemm_desc d = row_major_result(d_in);
+    Plan pl;
+    const moa_status s = make_plan(d, &pl);
+    if (s != MOA_OK) return s;
+    plan_raw_block(d, &pl);
+    return run_planned(d, pl, stream, fixed_ws, fixed_bytes);
 }
 
 moa_status run_gemm(const moa_gemm_desc &d, hipStream_t stream) { return run_gemm_in(d, stream, nullptr, 0); }
@@ -201,35 +207,51 @@ moa_status moa_autotune(const moa_gemm_desc *desc, int32_t reps, void *stream, m
                 if (a) (void)hipEventDestroy(a);
                 return hip_fail(e, "hipEventCreate");
             }
+            // mean time of `reps` runs after one warm-up
+            auto timed = [&](auto run, float *ms) {
+                moa_status r = run();
+                if (r != MOA_OK) return r;
+                (void)hipEventRecord(a, st);
+                for (int k = 0; k < reps && r == MOA_OK; ++k) r = run();
+                (void)hipEventRecord(b, st);
+                if ((e = hipEventSynchronize(b)) != hipSuccess) return hip_fail(e, "autotune timing");
+                (void)hipEventElapsedTime(ms, a, b);
+                *ms /= (float)reps;
+                return r;
+            };
             int best = -1;
-            float best_t = 0.0f;
+            float best_t = 0.0f, ms = 0.0f;
+            moa_gemm_desc d = *desc;
+            d.path = path;
             for (int v = 0; v < nv && s == MOA_OK; ++v) {
-                moa_gemm_desc d = *desc;
-                d.path = path;
                 d.flags = (d.flags & ~MOA_FLAG_VARIANT_MASK) | MOA_FLAG_VARIANT(v);
                 Plan pl;
                 if (make_plan(d, &pl) != MOA_OK) continue;       // e.g. a grid limit
-                if ((s = run_gemm(d, st)) != MOA_OK) break;      // warm-up
-                (void)hipEventRecord(a, st);
-                for (int r = 0; r < reps && s == MOA_OK; ++r) s = run_gemm(d, st);
-                (void)hipEventRecord(b, st);
-                if ((e = hipEventSynchronize(b)) != hipSuccess) {
-                    s = hip_fail(e, "autotune timing");
-                    break;
-                }
-                float ms = 0.0f;
-                (void)hipEventElapsedTime(&ms, a, b);
-                ms /= (float)reps;
-                if (best < 0 || ms < best_t) {
+                s = timed([&] { return run_gemm(d, st); }, &ms);
+                if (s == MOA_OK && (best < 0 || ms < best_t)) {
                     best = v;
                     best_t = ms;
+                }
+            }
+            // the kernel without conditioning, where the planner would take it
+            d.flags &= ~MOA_FLAG_VARIANT_MASK;
+            const moa_gemm_desc row = row_major_result(d);
+            bool direct = true;
+            Plan pl;
+            if (s == MOA_OK && best >= 0 && make_plan(row, &pl) == MOA_OK) {
+                pl.direct = true;                                // whatever an earlier record says
+                plan_raw_block(row, &pl);
+                if (pl.raw_block >= 0) {
+                    s = timed([&] { return run_planned(row, pl, st, nullptr, 0); }, &ms);
+                    direct = ms <= best_t;
+                    if (direct) best_t = ms;
                 }
             }
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
             if (s != MOA_OK) return s;
             if (best < 0) return fail(MOA_ERR_UNSUPPORTED, "no variant of path %d can run this shape", (int)path);
-            record_tuned_variant(*desc, path, best, best_t);
+            record_tuned_variant(*desc, path, best, best_t, direct);
             if (best_ms) *best_ms = best_t;
         }
         if (chosen) return moa_plan_query(desc, chosen);

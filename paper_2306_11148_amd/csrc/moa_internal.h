@@ -45,6 +45,7 @@ struct Plan {
     int64_t workspace_bytes = 0;
     int64_t static_components = 0;
     bool tuned = false;
+    bool direct = true;       // split-BF16: a single product may run without conditioning
     int split_k = 1;          // k chunks summed by separate workgroups (ring paths)
     int64_t partial_offset = 0;   // byte offset of the split-k partials in the workspace
     int raw_block = -1;       // split-BF16 without conditioning: its block (-1: conditioned)
@@ -87,8 +88,8 @@ moa_status validate(const moa_gemm_desc &d, bool need_ptrs);
 moa_path resolve_path(const moa_gemm_desc &d);
 moa_status make_plan(const moa_gemm_desc &d, Plan *out);
 // Completes the plan of a product that runs singly: split-BF16 products of few
-// blocks run without conditioning unless a flag or the autotuner names a
-// record-ring block. The other fields stay those of the conditioned form (fixed
+// blocks run without conditioning unless a flag names a record-ring block or the
+// autotuner timed one faster. The other fields stay those of the conditioned form (fixed
 // scratch refuses the same products). Apart from make_plan, which plans every
 // member of a group too.
 void plan_raw_block(const moa_gemm_desc &d, Plan *pl);
@@ -107,9 +108,10 @@ constexpr int kNumXCDs = 8;
 
 int64_t static_block_components(int64_t budget, int64_t elem, int64_t nblocks);
 
-// Autotuner table: shape class -> variant (-1 if none recorded).
-int tuned_variant(const moa_gemm_desc &d, moa_path path);
-void record_tuned_variant(const moa_gemm_desc &d, moa_path path, int variant, double ms);
+// Autotuner table: shape class -> variant (-1 if none recorded), and whether
+// products of the class may still run without conditioning.
+int tuned_variant(const moa_gemm_desc &d, moa_path path, bool *direct = nullptr);
+void record_tuned_variant(const moa_gemm_desc &d, moa_path path, int variant, double ms, bool direct);
 int variant_count(const moa_gemm_desc &d, moa_path path);
 moa_status autotune_save(const char *path);
 moa_status autotune_load(const char *path);

@@ -27,7 +27,9 @@ namespace moa {
 namespace {
 
 using ClassKey = std::array<int, 6>;
-struct Tuned { int variant; double ms; };
+// `direct`: products of the class that the planner runs without conditioning
+// still do (nothing timed faster than that); else the variant replaces it.
+struct Tuned { int variant; double ms; bool direct; };
 std::mutex g_tune_mu;
 std::map<ClassKey, Tuned> g_tuned;
 
@@ -72,7 +74,7 @@ int tuned_group_variant(const moa_gemm_desc *const *members, int count) {
 void record_tuned_group_variant(const moa_gemm_desc *const *members, int count, int variant, double ms) {
     if (count <= 0) return;
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[group_key(members, count)] = {variant, ms};
+    g_tuned[group_key(members, count)] = {variant, ms, true};
 }
 
 int split_grouped_choose(const moa_gemm_desc *const *members, int count, const SplitGroup &g, int forced,
@@ -87,15 +89,16 @@ int split_grouped_choose(const moa_gemm_desc *const *members, int count, const S
     return split_grouped_default_variant(g);
 }
 
-int tuned_variant(const moa_gemm_desc &d, moa_path path) {
+int tuned_variant(const moa_gemm_desc &d, moa_path path, bool *direct) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(class_key(d, path));
+    if (direct) *direct = it == g_tuned.end() || it->second.direct;
     return it == g_tuned.end() ? -1 : it->second.variant;
 }
 
-void record_tuned_variant(const moa_gemm_desc &d, moa_path path, int variant, double ms) {
+void record_tuned_variant(const moa_gemm_desc &d, moa_path path, int variant, double ms, bool direct) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[class_key(d, path)] = {variant, ms};
+    g_tuned[class_key(d, path)] = {variant, ms, direct};
 }
 
 int variant_count(const moa_gemm_desc &d, moa_path path) {
@@ -112,11 +115,11 @@ moa_status autotune_save(const char *path) {
     FILE *f = std::fopen(path, "w");
     if (!f) return fail(MOA_ERR_INVALID, "cannot write %s", path);
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    std::fprintf(f, "# moa autotune v1: dtype path terms log2m log2n log2p variant ms "
+    std::fprintf(f, "# moa autotune v1: dtype path terms log2m log2n log2p variant ms direct "
                     "(path %d: grouped split-BF16, fields count and median m, n, p)\n", kGroupClass);
     for (const auto &kv : g_tuned)
-        std::fprintf(f, "%d %d %d %d %d %d %d %.6f\n", kv.first[0], kv.first[1], kv.first[2], kv.first[3],
-                     kv.first[4], kv.first[5], kv.second.variant, kv.second.ms);
+        std::fprintf(f, "%d %d %d %d %d %d %d %.6f %d\n", kv.first[0], kv.first[1], kv.first[2], kv.first[3],
+                     kv.first[4], kv.first[5], kv.second.variant, kv.second.ms, (int)kv.second.direct);
     std::fclose(f);
     return MOA_OK;
 }
@@ -130,8 +133,11 @@ moa_status autotune_load(const char *path) {
         if (line[0] == '#') continue;
         ClassKey k;
         Tuned t;
-        if (std::sscanf(line, "%d %d %d %d %d %d %d %lf", &k[0], &k[1], &k[2], &k[3], &k[4], &k[5], &t.variant,
-                        &t.ms) != 8) {
+        // records without the last field were not timed against the product
+        // without conditioning, and leave it in place
+        int direct = 1;
+        if (std::sscanf(line, "%d %d %d %d %d %d %d %lf %d", &k[0], &k[1], &k[2], &k[3], &k[4], &k[5], &t.variant,
+                        &t.ms, &direct) < 8) {
             std::fclose(f);
             return fail(MOA_ERR_INVALID, "malformed line in %s: %s", path, line);
         }
@@ -147,6 +153,7 @@ moa_status autotune_load(const char *path) {
             std::fclose(f);
             return fail(MOA_ERR_INVALID, "out-of-range entry in %s: %s", path, line);
         }
+        t.direct = direct != 0;
         add[k] = t;
     }
     std::fclose(f);
@@ -198,7 +205,7 @@ static int split_k_of(const moa_gemm_desc &d, int64_t slabs) {
 
 void plan_raw_block(const moa_gemm_desc &d_in, Plan *pl) {
     const bool forced = (d_in.flags & MOA_FLAG_VARIANT_MASK) != 0;
-    if (pl->path != MOA_PATH_SPLIT_BF16 || forced || pl->tuned) return;
+    if (pl->path != MOA_PATH_SPLIT_BF16 || forced || !pl->direct) return;
     const moa_gemm_desc d = row_major_result(d_in);
     if (pl->split_k > 1) pl->raw_block = split_raw_splitk(d) ? 3 : -1;
     else if (split_k_requested(d) == 0) pl->raw_block = split_raw_block(d);
@@ -267,7 +274,7 @@ moa_status make_plan(const moa_gemm_desc &d_in, Plan *out) {
         if (forced >= 0) {
             if (forced >= nv) return fail(MOA_ERR_INVALID, "variant %d out of range (SPLIT_BF16 has %d)", forced, nv);
             v = forced;
-        } else if ((v = tuned_variant(d, pl.path)) >= 0) {
+        } else if ((v = tuned_variant(d, pl.path, &pl.direct)) >= 0) {
             pl.tuned = true;
         } else {
             v = split_bf16_default_variant(d.m, d.p);
