@@ -340,7 +340,9 @@ moa_status moa_autotune(const moa_gemm_desc *desc, int32_t reps, void *stream,
 /* Writes the recorded classes to a text file (one class per line) /
  * merges a file written by moa_autotune_save / forgets every record. Records
  * written before the kernel without conditioning was timed lack their last
- * field and leave the planner's choice of that kernel in place. */
+ * field and leave the planner's choice of that kernel in place. Grouped
+ * records of a file headed "moa autotune v1" name kernels that have been
+ * replaced: they are checked and passed over (the static rule applies). */
 moa_status moa_autotune_save(const char *path);
 moa_status moa_autotune_load(const char *path);
 moa_status moa_autotune_clear(void);

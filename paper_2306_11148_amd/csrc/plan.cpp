@@ -15,6 +15,7 @@
 #include <vector>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <mutex>
 
@@ -115,7 +116,7 @@ moa_status autotune_save(const char *path) {
     FILE *f = std::fopen(path, "w");
     if (!f) return fail(MOA_ERR_INVALID, "cannot write %s", path);
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    std::fprintf(f, "# moa autotune v1: dtype path terms log2m log2n log2p variant ms direct "
+    std::fprintf(f, "# moa autotune v2: dtype path terms log2m log2n log2p variant ms direct "
                     "(path %d: grouped split-BF16, fields count and median m, n, p)\n", kGroupClass);
     for (const auto &kv : g_tuned)
         std::fprintf(f, "%d %d %d %d %d %d %d %.6f %d\n", kv.first[0], kv.first[1], kv.first[2], kv.first[3],
@@ -129,8 +130,12 @@ moa_status autotune_load(const char *path) {
     if (!f) return fail(MOA_ERR_INVALID, "cannot read %s", path);
     char line[256];
     std::map<ClassKey, Tuned> add;
+    bool v1 = false;                    // the file's grouped variants are other kernels than today's
     while (std::fgets(line, sizeof line, f)) {
-        if (line[0] == '#') continue;
+        if (line[0] == '#') {
+            v1 = v1 || std::strncmp(line, "# moa autotune v1", 17) == 0;
+            continue;
+        }
         ClassKey k;
         Tuned t;
         // records without the last field were not timed against the product
@@ -154,7 +159,7 @@ moa_status autotune_load(const char *path) {
             return fail(MOA_ERR_INVALID, "out-of-range entry in %s: %s", path, line);
         }
         t.direct = direct != 0;
-        add[k] = t;
+        if (!(group && v1)) add[k] = t;
     }
     std::fclose(f);
     std::lock_guard<std::mutex> lk(g_tune_mu);
