@@ -219,7 +219,7 @@ moa_status moa_gemm_noalloc(const moa_gemm_desc *desc, void *stream);
  * that walks a shared tile list and splits the FP32 operands into hi/lo BF16
  * on the way through LDS (no conditioning pass; a member that splits its k
  * walk puts one item per chunk on the list, and its partials are summed
- * behind the launch); scaled-FP8 members are conditioned together and
+ * behind the launch; beyond a gigabyte of partials further launches follow); scaled-FP8 members are conditioned together and
  * contracted by one persistent launch per term count (split k walks likewise);
  * members on the ONF and FP32 matrix-core paths and members with a
  * column-major operand run as single launches on the same stream. No

@@ -831,12 +831,6 @@ namespace {
 int64_t partial_bytes(const Fp8Product &x) {
     return x.split_k > 1 ? align256((int64_t)x.split_k * x.d->m * x.d->p * 4) : 0;
 }
-int64_t member_bytes(const Fp8Product &x, bool two) {
-    const moa_gemm_desc &d = *x.d;
-    const int64_t S = (d.n + SLAB8 - 1) / SLAB8;
-    const int64_t rec = align256(ring::array_bytes(d.m, S)) + align256(ring::array_bytes(d.p, S));
-    return align256(4 * d.m) + align256(4 * d.p) + (two ? 2 : 1) * rec + partial_bytes(x);
-}
 int64_t header_bytes(const Fp8Product *members, int count) {
     int64_t cols = 0;
     for (int k = 0; k < count; ++k) cols += members[k].d->p;
@@ -844,9 +838,16 @@ int64_t header_bytes(const Fp8Product *members, int count) {
 }
 }  // namespace
 
+int64_t fp8_member_bytes(const Fp8Product &x, bool two) {
+    const moa_gemm_desc &d = *x.d;
+    const int64_t S = (d.n + SLAB8 - 1) / SLAB8;
+    const int64_t rec = align256(ring::array_bytes(d.m, S)) + align256(ring::array_bytes(d.p, S));
+    return align256(4 * d.m) + align256(4 * d.p) + (two ? 2 : 1) * rec + partial_bytes(x);
+}
+
 int64_t fp8_grouped_workspace_bytes(const Fp8Product *members, int count, bool two) {
     int64_t b = header_bytes(members, count) + align256(fp8_grouped_desc_bytes(count));
-    for (int k = 0; k < count; ++k) b += member_bytes(members[k], two);
+    for (int k = 0; k < count; ++k) b += fp8_member_bytes(members[k], two);
     return b;
 }
 

@@ -150,7 +150,7 @@ moa_status run_persistent(int64_t desc_bytes, int64_t need, Launch launch, hipSt
 struct Partition {
     std::vector<const moa_gemm_desc *> single, split;
     std::vector<Fp8Product> fp8[2];
-    std::vector<std::pair<const moa_gemm_desc *, int>> chunked;
+    std::vector<std::pair<const moa_gemm_desc *, int>> chunked;   // in order, cut into launches by their scratch
 };
 
 Partition partition(const moa_gemm_desc *descs, int64_t count, const int *split_k = nullptr) {
@@ -174,26 +174,72 @@ Partition partition(const moa_gemm_desc *descs, int64_t count, const int *split_
     return pt;
 }
 
-// Bytes of the chunked members' partials, 256-byte aligned each.
-int64_t partial_bytes(const Partition &pt) {
-    int64_t b = 0;
-    for (const auto &c : pt.chunked) b += align256((int64_t)c.second * c.first->m * c.first->p * 4);
-    return b;
+// Members that split their k walk share launches up to so much scratch of their
+// own (partials, and the records of FP8 ones); a member that needs more has a
+// launch to itself. Such members had run one after another, each on the scratch
+// of the one before: a launch for all of a large group would need them all at
+// once. A gigabyte of partials is about 16000 workgroups, so a further launch
+// costs little.
+constexpr int64_t kSplitScratch = int64_t(1000) << 20;
+
+using Chunked = std::pair<const moa_gemm_desc *, int>;
+int64_t partial_bytes(const Chunked &c) { return align256((int64_t)c.second * c.first->m * c.first->p * 4); }
+
+// Cuts 0 .. count - 1 into runs [first, last) whose `bytes` stay within kSplitScratch.
+template <class Bytes> std::vector<std::pair<size_t, size_t>> runs(size_t count, Bytes bytes) {
+    std::vector<std::pair<size_t, size_t>> out;
+    size_t first = 0;
+    int64_t sum = 0;
+    for (size_t k = 0; k < count; ++k) {
+        const int64_t b = bytes(k);
+        if (b > 0 && sum > 0 && sum + b > kSplitScratch) {
+            out.push_back({first, k});
+            first = k;
+            sum = 0;
+        }
+        sum += b;
+    }
+    out.push_back({first, count});
+    return out;
 }
 
-// The items of the split-BF16 launch, partials carved from `partials`.
-SplitGroup split_items(const Partition &pt, void *partials) {
+// A split-BF16 launch: the chunked members first .. last - 1, and with `unsplit`
+// all the others; partials carved from `partials`.
+SplitGroup split_items(const Partition &pt, size_t first, size_t last, bool unsplit, void *partials) {
     SplitGroup g;
-    size_t count = pt.split.size();
-    for (const auto &c : pt.chunked) count += (size_t)c.second;
+    size_t count = unsplit ? pt.split.size() : 0;
+    for (size_t k = first; k < last; ++k) count += (size_t)pt.chunked[k].second;
     g.items.reserve(count);
-    for (const moa_gemm_desc *d : pt.split) split_group_add(g, *d, 1, nullptr);
+    if (unsplit)
+        for (const moa_gemm_desc *d : pt.split) split_group_add(g, *d, 1, nullptr);
     char *at = static_cast<char *>(partials);
-    for (const auto &c : pt.chunked) {
+    for (size_t k = first; k < last; ++k) {
+        const Chunked &c = pt.chunked[k];
         split_group_add(g, *c.first, c.second, reinterpret_cast<float *>(at));
-        if (at) at += align256((int64_t)c.second * c.first->m * c.first->p * 4);
+        if (at) at += partial_bytes(c);
     }
     return g;
+}
+SplitGroup split_items(const Partition &pt) { return split_items(pt, 0, pt.chunked.size(), true, nullptr); }
+
+// Workspace of a split-BF16 launch: tables, then the partials of its chunked members.
+struct SplitLaunch {
+    SplitGroup g;
+    int64_t tables, bytes;
+};
+SplitLaunch split_launch(const Partition &pt, const std::pair<size_t, size_t> &run) {
+    SplitLaunch l{split_items(pt, run.first, run.second, run.first == 0, nullptr), 0, 0};
+    l.tables = l.bytes = align256(split_grouped_workspace_bytes(l.g));
+    for (size_t k = run.first; k < run.second; ++k) l.bytes += partial_bytes(pt.chunked[k]);
+    return l;
+}
+std::vector<std::pair<size_t, size_t>> split_runs(const Partition &pt) {
+    if (pt.split.empty() && pt.chunked.empty()) return {};
+    return runs(pt.chunked.size(), [&](size_t k) { return partial_bytes(pt.chunked[k]); });
+}
+std::vector<std::pair<size_t, size_t>> fp8_runs(const std::vector<Fp8Product> &list, bool two) {
+    if (list.empty()) return {};
+    return runs(list.size(), [&](size_t k) { return list[k].split_k > 1 ? fp8_member_bytes(list[k], two) : 0; });
 }
 
 }  // namespace
@@ -202,11 +248,11 @@ int64_t grouped_scratch_bytes(const moa_gemm_desc *descs, int64_t count) {
     const Partition pt = partition(descs, count);
     int64_t total = 0;
     for (const moa_gemm_desc *d : pt.single) total += align256(gemm_workspace_bytes(*d));
-    if (!pt.split.empty() || !pt.chunked.empty())
-        total += align256(align256(split_grouped_workspace_bytes(split_items(pt, nullptr))) + partial_bytes(pt));
+    for (const auto &run : split_runs(pt)) total += align256(split_launch(pt, run).bytes);
     for (int two = 0; two < 2; ++two)
-        if (!pt.fp8[two].empty())
-            total += align256(fp8_grouped_workspace_bytes(pt.fp8[two].data(), (int)pt.fp8[two].size(), two != 0));
+        for (const auto &run : fp8_runs(pt.fp8[two], two != 0))
+            total += align256(fp8_grouped_workspace_bytes(pt.fp8[two].data() + run.first, (int)(run.second - run.first),
+                                                          two != 0));
     return total;
 }
 
@@ -227,30 +273,38 @@ moa_status run_grouped(const moa_gemm_desc *descs, int64_t count, hipStream_t st
         if (s != MOA_OK) return s;
     }
     moa_status s = MOA_OK;
-    if (!pt.split.empty() || !pt.chunked.empty()) {
-        SplitGroup g = split_items(pt, nullptr);
-        if (g.items.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
-        const int v = split_grouped_choose(pt.split.data(), (int)pt.split.size(), g, split_variant, nullptr);
-        const int64_t tables = align256(split_grouped_workspace_bytes(g));
+    const auto split = split_runs(pt);
+    int v = 0;
+    for (const auto &run : split) {
+        SplitLaunch l = split_launch(pt, run);
+        if (l.g.items.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
+        if (run.first == 0)             // one choice, over the members of every run
+            v = split_grouped_choose(pt.split.data(), (int)pt.split.size(), split.size() == 1 ? l.g : split_items(pt),
+                                     split_variant, nullptr);
         s = run_persistent(
-            split_grouped_table_bytes(g), tables + partial_bytes(pt),
+            split_grouped_table_bytes(l.g), l.bytes,
             [&](void *ws, void *host, void *host_dev) {
-                if (!pt.chunked.empty()) g = split_items(pt, static_cast<char *>(ws) + tables);
-                return launch_split_grouped(g, v, ws, host, host_dev, stream);
+                if (run.first < run.second)
+                    l.g = split_items(pt, run.first, run.second, run.first == 0, static_cast<char *>(ws) + l.tables);
+                return launch_split_grouped(l.g, v, ws, host, host_dev, stream);
             },
             stream, arena);
+        if (s != MOA_OK) return s;
     }
-    for (int two = 0; two < 2 && s == MOA_OK; ++two) {
+    for (int two = 0; two < 2; ++two) {
         const auto &list = pt.fp8[two];
-        if (list.empty()) continue;
         if (list.size() > (size_t)INT32_MAX) return fail(MOA_ERR_INVALID, "too many members");
-        const int c = (int)list.size();
-        s = run_persistent(
-            fp8_grouped_desc_bytes(c), fp8_grouped_workspace_bytes(list.data(), c, two != 0),
-            [&](void *ws, void *host, void *host_dev) {
-                return launch_fp8_grouped(list.data(), c, two != 0, ws, host, host_dev, stream);
-            },
-            stream, arena);
+        for (const auto &run : fp8_runs(list, two != 0)) {
+            const Fp8Product *first = list.data() + run.first;
+            const int c = (int)(run.second - run.first);
+            s = run_persistent(
+                fp8_grouped_desc_bytes(c), fp8_grouped_workspace_bytes(first, c, two != 0),
+                [&](void *ws, void *host, void *host_dev) {
+                    return launch_fp8_grouped(first, c, two != 0, ws, host, host_dev, stream);
+                },
+                stream, arena);
+            if (s != MOA_OK) return s;
+        }
     }
     return s;
 }
@@ -309,7 +363,7 @@ extern "C" moa_status moa_grouped_plan_query(const moa_gemm_desc *descs, int64_t
         bool t = false;
         const int64_t members = (int64_t)(pt.split.size() + pt.chunked.size());
         const int v = members == 0 ? -1 : split_grouped_choose(pt.split.data(), (int)pt.split.size(),
-                                                               split_items(pt, nullptr), -1, &t);
+                                                               split_items(pt), -1, &t);
         if (variant) *variant = v;
         if (tuned) *tuned = t ? 1 : 0;
         if (persistent_members) *persistent_members = members;

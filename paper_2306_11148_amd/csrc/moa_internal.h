@@ -251,6 +251,7 @@ struct Fp8GroupWork {
     int64_t table_offset;               // byte offset of the member table in the workspace
 };
 int64_t fp8_grouped_workspace_bytes(const Fp8Product *members, int count, bool two_term);
+int64_t fp8_member_bytes(const Fp8Product &member, bool two_term);   // one member's share of it
 int64_t fp8_grouped_desc_bytes(int count);
 Fp8GroupWork fp8_grouped_layout(const Fp8Product *members, int count, bool two_term, void *workspace,
                                 void *host_staging);
