@@ -564,10 +564,13 @@ __device__ __forceinline__ void onf_mm_block(const T *__restrict__ A, const T *_
         }
 }
 
-// Workgroups per CU: two, which keep the matrix cores fed through each other's
-// barriers (the 128 x 128 FP64 block holds 128 accumulator registers).
+// Workgroups per CU the registers must allow: two, which keep the matrix cores
+// fed through each other's barriers (the 128 x 128 FP64 block holds 128
+// accumulator registers); one where the ring leaves no room in LDS for a second
+// (FP64 64 x 64: four sub-slabs x three stages are 96 KiB).
+template <class G> constexpr int mm_workgroups() { return 2 * G::LDS <= 160 * 1024 ? 2 : 1; }
 template <typename T, int TM, int TN, int WM, int WN, int SUB, int NST, int GK, bool A_COL, bool B_COL>
-__global__ __launch_bounds__(256, 2) void onf_mm_kernel(const T *__restrict__ A, const T *__restrict__ B,
+__global__ __launch_bounds__(256, (mm_workgroups<MmCfg<T, TM, TN, WM, WN, SUB, NST>>())) void onf_mm_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                         T *__restrict__ C, int64_t m, int64_t n, int64_t p,
                                                         int accumulate, int tiles_m, int tiles_n) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[MmCfg<T, TM, TN, WM, WN, SUB, NST>::LDS];
