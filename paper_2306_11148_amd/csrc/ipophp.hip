@@ -143,10 +143,15 @@ hipError_t launch_kronecker(int64_t m, int64_t n, int64_t p, int64_t q, moa_dtyp
     const int64_t cols = n * q, rows = m * p;
     const int N = dt == MOA_F64 ? 2 : 4;
     const bool wide = q % N == 0 && (uintptr_t)C % 16 == 0 && (uintptr_t)B % 16 == 0;
-    // all column chunks of a row; rows in runs for about 16384 workgroups
-    // (8192^2 FP32: 46 us, 52 with 4096, of fewer and longer runs)
+    // All column chunks of a row; rows in runs for about 16384 workgroups (8192^2
+    // FP32: 46 us, 52 with 4096, of fewer and longer runs). Small products: single
+    // rows up to 1024 workgroups, then runs of up to four rows, more where a chunk
+    // has less than 2 KiB (20 x 10 (x) 20 x 16, 400 rows: 2.9 us in single rows, 3.4
+    // in runs of four; 50 x 8 (x) 80 x 20, 4000 rows: 7.3 and 4.4)
     const int64_t gx = std::min<int64_t>((cols + 256 * N - 1) / (256 * N), 64);
-    const int64_t run = std::max<int64_t>(4, std::max<int64_t>(rows * gx / 16384, (rows + 65534) / 65535));
+    const int64_t chunk_bytes = std::min<int64_t>(cols, 256 * N) * (16 / N);
+    const int64_t few = std::min<int64_t>(std::max<int64_t>(4, 8192 / chunk_bytes), rows * gx / 1024);
+    const int64_t run = std::max<int64_t>({1, few, rows * gx / 16384, (rows + 65534) / 65535});
     const dim3 grid((unsigned)gx, (unsigned)((rows + run - 1) / run));
     TraceScope ts(MOA_K_KRONECKER, st);
 #define MOA_KRONECKER(T, W)                                                                                        \
