@@ -58,18 +58,21 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const T *A, const T *B, T
 // q), found once in 32-bit arithmetic (the entry point keeps n q below 2^31),
 // and its N values of A stay in registers until i changes; (i, k) advance by
 // counting, one 64-bit division per workgroup. What is left per row is reading
-// B and the store, so the kernel is bound by writing C. WIDE: q and C in whole
+// B and the store, so the kernel is bound by writing C. Wide: q and C in whole
 // 16-byte vectors and B aligned, so a thread's columns share j, run along l and
-// move as one vector; else its columns are 256 apart, so that the lanes of each
-// 4- or 8-byte access are consecutive. 64^2 (x) 128^2 in FP32 (8192^2): 95 us
-// with a 64-bit division and eight scalar reads per row and 16 bytes, 46-48 us
-// (5.7 TB/s written; a plain fill of that size reaches 6.9) this way.
-template <typename T, bool WIDE>
+// move as one vector; Scalar: its columns are 256 apart, so that the lanes of each
+// 4- or 8-byte access are consecutive; Gather: rows of C in whole vectors,
+// written so from values of B read one by one. 64^2 (x) 128^2 in FP32 (8192^2):
+// 95 us with a 64-bit division and eight scalar reads per row and 16 bytes, 46-48
+// us (5.7 TB/s written; a plain fill of that size reaches 6.9) this way.
+enum class Row { Scalar, Gather, Wide };
+template <typename T, Row R>
 __global__ __launch_bounds__(256) void kronecker_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                         T *__restrict__ C, int64_t m, int64_t n, int64_t p,
                                                         int64_t q, int64_t run, int accumulate) {
     using V = typename Vec16<T>::type;
     constexpr int N = Vec16<T>::N;
+    constexpr bool VEC = R != Row::Scalar;
     const int64_t rows = m * p;
     const int cols = (int)(n * q), qq = (int)q;
     const int64_t r0 = (int64_t)blockIdx.y * run, r1 = min(r0 + run, rows);
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(256) void kronecker_kernel(const T *__restrict__ A,
         bool live[N];
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            c[e] = WIDE ? base + (int64_t)threadIdx.x * N + e : base + e * 256 + threadIdx.x;
+            c[e] = VEC ? base + (int64_t)threadIdx.x * N + e : base + e * 256 + threadIdx.x;
             live[e] = c[e] < cols;
             const int cc = live[e] ? (int)c[e] : 0;
             jj[e] = cc / qq;
@@ -92,15 +95,21 @@ __global__ __launch_bounds__(256) void kronecker_kernel(const T *__restrict__ A,
 #pragma unroll
             for (int e = 0; e < N; ++e) a[e] = A[i * n + jj[e]];
         };
-        if (!live[0]) continue;          // WIDE: the whole vector; else every later column too
+        if (!live[0]) continue;          // the whole vector, or every later column too
         row_of_a();
 #pragma unroll 4
         for (int64_t r = r0; r < r1; ++r) {
             T *crow = C + r * (int64_t)cols;
             const T *brow = B + k * q;
-            if constexpr (WIDE) {
-                const V bv = *reinterpret_cast<const V *>(brow + ll[0]);
-                const T *pb = reinterpret_cast<const T *>(&bv);
+            if constexpr (VEC) {
+                V bv;
+                T *pb = reinterpret_cast<T *>(&bv);
+                if constexpr (R == Row::Wide) {
+                    bv = *reinterpret_cast<const V *>(brow + ll[0]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < N; ++e) pb[e] = brow[ll[e]];
+                }
                 V out = accumulate ? *reinterpret_cast<const V *>(crow + c[0]) : V{};
                 T *po = reinterpret_cast<T *>(&out);
 #pragma unroll
@@ -143,6 +152,10 @@ hipError_t launch_kronecker(int64_t m, int64_t n, int64_t p, int64_t q, moa_dtyp
     const int64_t cols = n * q, rows = m * p;
     const int N = dt == MOA_F64 ? 2 : 4;
     const bool wide = q % N == 0 && (uintptr_t)C % 16 == 0 && (uintptr_t)B % 16 == 0;
+    // Gather for rows of one or two chunks, where columns 256 apart leave most of
+    // the last chunk empty (kernel alone, FP32: 64 x 64 (x) 100 x 17 13 us against
+    // 14.7, but 64 x 64 (x) 127 x 127 73 against 51)
+    const bool gather = cols < 2048 && cols % N == 0 && (uintptr_t)C % 16 == 0;
     // All column chunks of a row; rows in runs for about 16384 workgroups (8192^2
     // FP32: 46 us, 52 with 4096, of fewer and longer runs). Small products: single
     // rows up to 1024 workgroups, then runs of up to four rows, more where a chunk
@@ -154,15 +167,17 @@ hipError_t launch_kronecker(int64_t m, int64_t n, int64_t p, int64_t q, moa_dtyp
     const int64_t run = std::max<int64_t>({1, few, rows * gx / 16384, (rows + 65534) / 65535});
     const dim3 grid((unsigned)gx, (unsigned)((rows + run - 1) / run));
     TraceScope ts(MOA_K_KRONECKER, st);
-#define MOA_KRONECKER(T, W)                                                                                        \
-    hipLaunchKernelGGL((kronecker_kernel<T, W>), grid, dim3(256), 0, st, static_cast<const T *>(A),                \
+#define MOA_KRONECKER(T, R)                                                                                        \
+    hipLaunchKernelGGL((kronecker_kernel<T, R>), grid, dim3(256), 0, st, static_cast<const T *>(A),                \
                        static_cast<const T *>(B), static_cast<T *>(C), m, n, p, q, run, accumulate)
     if (dt == MOA_F64) {
-        if (wide) MOA_KRONECKER(double, true);
-        else MOA_KRONECKER(double, false);
+        if (wide) MOA_KRONECKER(double, Row::Wide);
+        else if (gather) MOA_KRONECKER(double, Row::Gather);
+        else MOA_KRONECKER(double, Row::Scalar);
     } else {
-        if (wide) MOA_KRONECKER(float, true);
-        else MOA_KRONECKER(float, false);
+        if (wide) MOA_KRONECKER(float, Row::Wide);
+        else if (gather) MOA_KRONECKER(float, Row::Gather);
+        else MOA_KRONECKER(float, Row::Scalar);
     }
 #undef MOA_KRONECKER
     return hipGetLastError();
