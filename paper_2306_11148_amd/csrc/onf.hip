@@ -512,18 +512,20 @@ __device__ __forceinline__ void onf_mm_block(const T *__restrict__ A, const T *_
     const int64_t S = (n + STEP_K - 1) / STEP_K, full = n / STEP_K;
     if (S > 0)
         for (int q = 0; q < NST - 1; ++q) issue_next(lds + q * G::STAGE);
-    // the accumulate form starts from C, read while the ring fills
+    // The accumulate form starts from C, read while the ring fills. Rows and
+    // columns past the end read the last one instead (such elements are never
+    // stored): without a branch per element all loads are in flight together.
     if (accumulate) {
+        int64_t col[FN];
+#pragma unroll
+        for (int b = 0; b < FN; ++b) col[b] = min(j0 + wn * WN + b * 16 + lr, p - 1);
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
-            for (int b = 0; b < FN; ++b) {
-                const int64_t j = j0 + wn * WN + b * 16 + lr;
+            for (int r = 0; r < 4; ++r) {
+                const T *row = C + min(i0 + wm * WM + a * 16 + M::row(r, lane), m - 1) * p;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t i = i0 + wm * WM + a * 16 + M::row(r, lane);
-                    if (i < m && j < p) acc[a][b][r] = C[i * p + j];
-                }
+                for (int b = 0; b < FN; ++b) acc[a][b][r] = row[col[b]];
             }
         __builtin_amdgcn_s_waitcnt(ring::waitcnt_vm(0));
     }
@@ -550,18 +552,23 @@ __device__ __forceinline__ void onf_mm_block(const T *__restrict__ A, const T *_
         }
     }
 
+    auto store = [&](auto whole_form) {
+        constexpr bool WHOLE = decltype(whole_form)::value;  // no row or column past the end
 #pragma unroll
-    for (int a = 0; a < FM; ++a)
+        for (int a = 0; a < FM; ++a)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t i = i0 + wm * WM + a * 16 + M::row(r, lane);
-            if (i >= m) continue;
+            for (int r = 0; r < 4; ++r) {
+                const int64_t i = i0 + wm * WM + a * 16 + M::row(r, lane);
+                if (!WHOLE && i >= m) continue;
 #pragma unroll
-            for (int b = 0; b < FN; ++b) {
-                const int64_t j = j0 + wn * WN + b * 16 + lr;
-                if (j < p) C[i * p + j] = acc[a][b][r];
+                for (int b = 0; b < FN; ++b) {
+                    const int64_t j = j0 + wn * WN + b * 16 + lr;
+                    if (WHOLE || j < p) C[i * p + j] = acc[a][b][r];
+                }
             }
-        }
+    };
+    if (i0 + TM <= m && j0 + TN <= p) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 // Workgroups per CU the registers must allow: two, which keep the matrix cores
