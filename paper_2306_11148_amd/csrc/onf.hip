@@ -707,21 +707,31 @@ bool onf_launches(const moa_gemm_desc &d, int v) {
 }
 
 // The planner's block: the one whose workgroups, dealt out over the CUs, leave
-// the busiest CU the least to do -- ceil(blocks / CUs) times the block's area,
-// weighted by the block's measured time per element of C (4096^3: FP64 2.28 ms
+// the busiest CU the least to do -- ceil(blocks / CUs) times the block's k steps,
+// its area weighted by its measured time per element of C (4096^3: FP64 2.28 ms
 // with 32 x 32 blocks, 2.12 with 64 x 64 and the larger ones; FP32 1.13 ms with
-// 32 x 64, 1.03 with 64 x 64, 1.02 with 64 x 128, 0.99 with 128 x 128). The
-// matrix cores are shared by a CU's workgroups, so a CU with two blocks takes
-// twice as long as its neighbours with one: 1999 x 1531 x 2113 in FP64 has 272
-// blocks of 128 x 128 and takes 403 us with them, 258 with 64 x 64 and 244 with
-// 32 x 32; 256^3 takes 41, 11 and 4.8 us. Ties go to the larger block. 128 x 128
-// blocks only where every CU gets one. Blocks whose grid does not hold the
-// product (fewer than 2^32 threads in x; the register-staged kernel's rows of
-// blocks are its grid's y) are not candidates.
+// 32 x 64, 1.03 with 64 x 64, 1.02 with 64 x 128, 0.99 with 128 x 128), and what a
+// block takes outside its k walk: filling the ring and writing C (with the
+// accumulate form reading it), which larger blocks hide better. That is counted
+// in k steps, fitted to 23 shapes with n from 8 to 300; in FP64, where it is
+// mostly C's traffic, for the part of the block inside C. The matrix cores are
+// shared by a CU's workgroups, so a CU with two blocks takes twice as long as its
+// neighbours with one: 1999 x 1531 x 2113 in FP64 has 272 blocks of 128 x 128 and
+// takes 403 us with them, 258 with 64 x 64 and 244 with 32 x 32; 256^3 takes 41, 11
+// and 4.8 us. With a short walk it is the other way round: 6000 x 30 x 6000 in FP64
+// 75 us with 128 x 128, 123 with 64 x 64 and 110 with 32 x 32. Ties go to the larger
+// block. 128 x 128 blocks only where every CU gets one. Blocks whose grid does not
+// hold the product (fewer than 2^32 threads in x; the register-staged kernel's rows
+// of blocks are its grid's y) are not candidates.
 int onf_default_variant(const moa_gemm_desc &d, bool ring_ok) {
     constexpr double kWeight64[] = {1.07, 1.0, 1.0, 1.0, 1.0}, kWeight32[] = {1.13, 1.035, 1.03, 1.0, 1.0};
+    // k steps' worth of time outside the walk: overwrite, accumulate
+    constexpr int kEdge64[][5] = {{72, 78, 48, 34, 40}, {125, 138, 92, 76, 78}};
+    constexpr int kEdge32[][5] = {{67, 56, 33, 34, 35}, {95, 95, 57, 68, 72}};
+    const bool f64 = d.dtype == MOA_F64;
     const OnfShape *shapes = shapes_of(d);
-    const double *weight = d.dtype == MOA_F64 ? kWeight64 : kWeight32;
+    const double *weight = f64 ? kWeight64 : kWeight32;
+    const int *edge = (f64 ? kEdge64 : kEdge32)[d.accumulate ? 1 : 0];
     const int ring = onf_ring_variant((moa_dtype)d.dtype);
     int best = 0;
     double best_cost = 0;
@@ -730,7 +740,9 @@ int onf_default_variant(const moa_gemm_desc &d, bool ring_ok) {
         const OnfShape s = shapes[v];
         const int64_t blocks = ((d.m + s.tm - 1) / s.tm) * ((d.p + s.tn - 1) / s.tn);
         if (s.tm * s.tn == 128 * 128 && blocks < kNumCUs) continue;
-        const double cost = (double)((blocks + kNumCUs - 1) / kNumCUs) * s.tm * s.tn * weight[v];
+        const double area = s.tm * s.tn, live = f64 ? (double)d.m * (double)d.p / (double)blocks : area;
+        const double cost = (double)((blocks + kNumCUs - 1) / kNumCUs) * weight[v] *
+                            (area * (double)d.n + live * (double)edge[v]);
         if (best_cost == 0 || cost < best_cost) {
             best = v;
             best_cost = cost;
