@@ -756,7 +756,7 @@ def block_sweep(args, torch, moa):
             ms = tot / reps
             e = energy_per_call(f, min(args.energy_seconds, 1.0), ms, energy, torch)
             print(json.dumps({"block_sweep": "ONF FP64", "N": N, "variant": v,
-                              "staging": "direct-to-LDS ring" if plan["tile_k"] == 8 else "registers",
+                              "wave": [plan["wave_m"], plan["wave_n"]],
                               "block": [plan["tile_m"], plan["tile_n"]],
                               "components": plan["tile_m"] * plan["tile_n"], "ms": round(ms, 4),
                               "tflops": round(2.0 * N ** 3 / ms / 1e9, 3), "energy": e}), flush=True)

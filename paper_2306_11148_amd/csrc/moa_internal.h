@@ -279,9 +279,10 @@ moa_status run_gemm(const moa_gemm_desc &d, hipStream_t stream);
 moa_status run_gemm_in(const moa_gemm_desc &d, hipStream_t stream, void *fixed_ws, int64_t fixed_bytes);
 
 // Grouped products (validated by the caller): split-BF16 members (split-k ones
-// chunk by chunk) in one persistent launch sequence, scaled-FP8 members in one
-// per term count, the others (and column-major or split-k FP8 members) one
-// after another.
+// chunk by chunk) in one persistent launch sequence, scaled-FP8 members (likewise)
+// in one per term count, the others (ONF, FP32 matrix cores, column-major
+// operands) one after another. Members that split k go on to further launches
+// where a launch's scratch for them would pass a gigabyte.
 // A caller-owned block of device memory that a grouped launch carves its
 // scratch from (256-byte aligned pieces, in launch order) instead of the
 // scratch cache.

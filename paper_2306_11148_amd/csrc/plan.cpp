@@ -8,9 +8,10 @@
 // (32 x 32, as on the V100) and 2048 FP32 components (32 x 64). That block is
 // the first entry of each ONF instantiation table. Larger blocks, staged in
 // the 160 KB LDS with the C block held in registers, are the neighbours the
-// planner (and the autotuner) choose among: a launch must also cover the 256
-// CUs several times over, so the planner takes the largest block that still
-// yields at least one workgroup per CU and falls back to the smallest.
+// planner (and the autotuner) choose among. A launch must also spread over the 256
+// CUs: the ONF planner takes the block whose busiest CU is done first (onf.hip),
+// the matrix-core paths the largest block that gives every CU one, with smaller or
+// rectangular ones where the last round of CUs would be short.
 #include <array>
 #include <vector>
 #include <cstdio>
