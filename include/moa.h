@@ -243,9 +243,9 @@ moa_status moa_gemm_grouped(const moa_gemm_desc *descs, int64_t count,
  *   4  128 x 64 blocks, four per CU.
  * moa_gemm_grouped and moa_group_create use the autotuner's record for the
  * members' class if there is one, else the static rule: the block among 2, 3
- * and 4 with the fewest slab steps over the members, weighted by the
- * measured time of one slab step of that block; where the longest k walk has
- * 32 slabs or more, the block among 1 to 4 with the shortest estimated finish.
+ * and 4 with the fewest slab steps over the members, half blocks weighted
+ * 0.8; where the longest k walk has 32 slabs or more, the block among 1 to 4
+ * with the shortest estimated launch.
  * moa_gemm_grouped_variant runs
  * moa_gemm_grouped with `variant` forced (-1: that choice); MOA_ERR_INVALID
  * for a variant outside -1 .. 4. */

@@ -571,11 +571,11 @@ constexpr int GB_M = 128;              // largest grouped block rows
 // uniform and mixed.
 struct GroupedKernel { int bm, bn, occ; double weight, fixed, step, walk, wg; };
 constexpr GroupedKernel kGroupedK[] = {
-    {128, 128, 2, 0.60, 18.5, 0.423, 0.303, 6.98},   // 0: five stages
-    {64, 64, 4, 0.25, 17.8, 0.210, 0.128, 8.11},    // 1
-    {128, 128, 2, 0.57, 18.5, 0.423, 0.303, 6.98},   // 2: three stages
-    {64, 128, 3, 0.35, 18.3, 0.284, 0.200, 7.37},   // 3
-    {128, 64, 4, 0.39, 17.8, 0.357, 0.244, 7.19},  // 4
+    {128, 128, 2, 1.0, 18.5, 0.423, 0.303, 6.98},   // 0: five stages
+    {64, 64, 4, 0.0, 17.8, 0.210, 0.128, 8.11},     // 1 (longer walks only)
+    {128, 128, 2, 1.0, 18.5, 0.423, 0.303, 6.98},   // 2: three stages
+    {64, 128, 3, 0.8, 18.3, 0.284, 0.200, 7.37},    // 3
+    {128, 64, 4, 0.8, 17.8, 0.357, 0.244, 7.19},    // 4
 };
 constexpr int kGroupedVariants = (int)(sizeof(kGroupedK) / sizeof(kGroupedK[0]));
 int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
@@ -633,8 +633,11 @@ int64_t split_grouped_workspace_bytes(const SplitGroup &g) { return 256 + split_
 int split_grouped_variant_count() { return kGroupedVariants; }
 
 // Static rule. Short k walks (below 32 slabs): the block among 128 x 128, 64 x
-// 128 and 128 x 64 with the fewest slab steps over the items, weighted by the
-// time of a step. Longer ones: the block with the shortest estimated launch, 64 x
+// 128 and 128 x 64 with the fewest slab steps over the items, weighted by what a
+// tile takes: half a block costs 0.8 of a whole one or more, C and the change of
+// tiles included (43 products of 137 x 67 x 1192: 47.5 us with 128 x 128 blocks, 59
+// with 64 x 128, which have 1.5 times the tiles; 62 of 43 x 14 x 967, the same
+// tiles, 40.3 and 39.5). Longer ones: the block with the shortest estimated launch, 64 x
 // 64 among them -- a group that leaves CUs idle is as slow as its longest walk
 // (4 products, the longest walk 197 slabs: 97 us with 128 x 128 blocks, 68 with 64 x
 // 64), a large one pays for every step (64 products of 64 .. 2048: 232 us with 128 x 128

@@ -29,6 +29,9 @@ def mixed(count, seed):
     ([(861, 681, 259)] * 17, 2),            # 84, 57, 67, 67
     ([(293, 1001, 675)] * 50, 2),           # 199, 136, 150, 174
     (mixed(4, 66), 1),                      # 79, 110, 90, 103
+    ([(137, 67, 1192)] * 43, 2),            # 75, 48, 59, 73: short k walks
+    ([(159, 50, 613)] * 111, 2),            # 79, 49, 61, 75
+    ([(43, 14, 967)] * 62, 3),              # 64, 40.3, 39.5, 64
 ])
 def test_measured_best_block(shapes, variant):
     descs = []
